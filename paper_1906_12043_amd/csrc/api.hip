@@ -387,28 +387,33 @@ int cocod_create(const cocod_config *cfg, cocod_ctx **out)
             if (e == hipSuccess)
                 e = hipMemcpy(ctx->d_sigma_w, sigma_w.data(), sigma_w.size() * sizeof(float), hipMemcpyHostToDevice);
         }
-        if (e == hipSuccess && cfg->grad == COCOD_GRAD_MLP) {      // one work-space block, carved below
-            const size_t wb = static_cast<size_t>(cfg->W) * cfg->mlp_batch;
-            const size_t n_x = wb * cfg->mlp_in, n_h = wb * cfg->mlp_hidden, n_z = wb * cocod::mlp_dz_pitch();
-            e = hipMalloc(reinterpret_cast<void **>(&ctx->mlp_ws), (2 * n_x + 2 * n_h + n_z + 2 * wb) * sizeof(float));
-            if (e == hipSuccess) {
-                float *at = ctx->mlp_ws;
-                ctx->mlp_X[0] = at; at += n_x;
-                ctx->mlp_X[1] = at; at += n_x;
-                ctx->mlp.H = at;  at += n_h;
-                ctx->mlp.dA = at; at += n_h;
-                ctx->mlp.dZ = at; at += n_z;
-                ctx->mlp_y[0] = reinterpret_cast<int32_t *>(at); at += wb;
-                ctx->mlp_y[1] = reinterpret_cast<int32_t *>(at);
-                ctx->mlp.X = ctx->mlp_X[0];
-                ctx->mlp.y = ctx->mlp_y[0];
-            }
-        }
         if (e == hipSuccess) {
             int dev = 0, cus = 0;
             e = hipGetDevice(&dev);
             if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
             ctx->compute_units = cus > 0 ? static_cast<uint32_t>(cus) : 0u;
+        }
+        if (e == hipSuccess && cfg->grad == COCOD_GRAD_MLP) {      // one work-space block, carved below
+            const size_t wb = static_cast<size_t>(cfg->W) * cfg->mlp_batch;
+            const size_t n_x = wb * cfg->mlp_in, n_h = wb * cfg->mlp_hidden, n_z = wb * cocod::mlp_dz_pitch();
+            const size_t n_m = cfg->W * cocod::mlp_max_groups(cfg->mlp_batch);
+            const uint32_t splits = cocod::mlp_forward_splits(cfg->W, cfg->mlp_in, cfg->mlp_hidden, cfg->mlp_batch, ctx->compute_units);
+            e = hipMalloc(reinterpret_cast<void **>(&ctx->mlp_ws), (2 * n_x + (1 + splits) * n_h + n_z + 2 * wb + n_m) * sizeof(float));
+            if (e == hipSuccess) {
+                float *at = ctx->mlp_ws;
+                ctx->mlp_X[0] = at; at += n_x;
+                ctx->mlp_X[1] = at; at += n_x;
+                ctx->mlp.fwd_splits = splits;
+                ctx->mlp.H = at;  at += n_h;
+                ctx->mlp.H_part = at; at += (splits - 1) * n_h;
+                ctx->mlp.dA = at; at += n_h;
+                ctx->mlp.dZ = at; at += n_z;
+                ctx->mlp_y[0] = reinterpret_cast<int32_t *>(at); at += wb;
+                ctx->mlp_y[1] = reinterpret_cast<int32_t *>(at); at += wb;
+                ctx->mlp.dA_max = at;
+                ctx->mlp.X = ctx->mlp_X[0];
+                ctx->mlp.y = ctx->mlp_y[0];
+            }
         }
         if (e == hipSuccess) e = scratch_for_current_device(&ctx->static_scratch);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_snap, hipEventDisableTiming);

@@ -102,14 +102,20 @@ struct MlpParams {
     float *X_next;            // same shape, the other batch buffer: the step also draws the NEXT step's
     int32_t *y_next;          //   mini-batch and labels into these (null: it does not)
     bool have_batch;          // X and y already hold this step's mini-batch (drawn by the previous step)
-    float *H;                 // [W][batch][n_hid]  relu output
+    float *H;                 // [W][batch][n_hid]  relu output (between the forward product and the output layer: K split 0 of X W1)
+    float *H_part;            // [fwd_splits - 1][W][batch][n_hid]  the other K splits
+    uint32_t fwd_splits;      // mlp_forward_splits of the shape
     float *dA;                // [W][batch][n_hid]  gradient at the hidden pre-activation
+    float *dA_max;            // [W][mlp_max_groups(batch)]  largest |dA| of each group of samples
     float *dZ;                // [W][batch][mlp_dz_pitch()]  gradient at the logits
     int32_t *y;               // [W][batch] labels
 };
 
 bool mlp_shape_supported(uint32_t n_in, uint32_t n_hid, uint32_t n_out, uint32_t batch);
 size_t mlp_dz_pitch();
+size_t mlp_max_groups(uint32_t batch);
+// K splits of the forward product (chosen once per context: their sums need work space)
+uint32_t mlp_forward_splits(uint32_t W, uint32_t n_in, uint32_t n_hid, uint32_t batch, uint32_t compute_units);
 // start / stop (may be null) receive the start timestamp of the step's first kernel and the end timestamp of its last
 hipError_t launch_mlp_step(hipStream_t stream, const MlpParams &p, hipEvent_t start, hipEvent_t stop);
 

@@ -4,26 +4,29 @@
 //
 // One local step = four launches on the compute stream (five for a step whose mini-batch no earlier
 // step has drawn: gen_batch in front):
-//   gemm<FWD>      H = relu(X W1 + b1)                         [B x in] x [in x hid]   fp32 MFMA
-//   head           Z = H W2 + b2, softmax, dZ = (P - onehot)/B, dA = (dZ W2^T) * [H > 0]
-//                  (one wave per sample, wave reductions, W2 in LDS)
+//   gemm<FWD>      X W1, in K splits                           [B x in] x [in x hid]
+//   head           H = relu(X W1 + b1), Z = H W2 + b2, softmax, dZ = (P - onehot)/B, dA = (dZ W2^T) * [H > 0]
+//                  (sixteen samples per block, fp32 matrix instructions)
 //   head_update    dW2 = H^T dZ, db2, db1 = colsum(dA); momentum-SGD update of W2, b2, b1;
 //                  further blocks of the same launch draw the NEXT step's X and labels from the
 //                  counter-based generator into the other of two batch buffers (vector ALU work
 //                  beside a kernel that is a short chain of dependent loads)
 //   gemm<BWD>      dW1 = X^T dA with the momentum-SGD update of W1 fused into the epilogue
-//                  (the 12.6 MB gradient of W1 never goes to memory)   [in x B] x [B x hid]  fp32 MFMA
-// The two big contractions (98 % of the flops) run on the matrix cores; the output layer has
-// 10 columns and stays on the vector units.
+//                  (the 12.6 MB gradient of W1 never goes to memory)   [in x B] x [B x hid]
 //
-// GEMM kernel: 64 x 128 output tile per 512-thread block (8 waves, one 32x32 accumulator each; 64 x 64
-// with 4 waves when the hidden width is not a multiple of 128).  K goes through LDS in slices
-// of 32 with register prefetch and two buffers (one barrier per slice); a wave reads all fragments
-// of a slice before it starts the slice's chain of 16 MFMAs.  The forward product reads
-// its A operand K-contiguous; the backward product needs X^T and gets it by staging X through LDS
-// transposed, so no transposed copy of the mini-batch is ever written.  After the K loop the
-// accumulators pass through LDS once more so that the epilogue touches memory in 16-byte pieces
-// along rows (256 contiguous bytes per row per wave) instead of 4-byte pieces along columns.
+// The two big contractions (98 % of the flops) run on the 16-bit matrix instructions at fp32 accuracy: every fp32
+// operand is split into two fp16 values (its leading 11 bits and the remainder's), scaled by a power of two into the
+// middle of the fp16 range, and three of the four partial products are formed with fp32 accumulation.  Against 64 bits
+// (W = 16, 3072-1024-10, batch 128) H = relu(X W1 + b1) is off by 3.2e-7 and dW1 by 1.44e-7 of their norms; the fp32
+// matrix instruction, whose chain of additions is longer, gave 1.0e-6 and 1.47e-7, and the other shapes measured move the same way.
+// The fp32 instruction peaks at 157 TFLOP/s; three fp16 products per fp32 product cost a fifth of its time, and the
+// contractions are then bound by their streams: the forward one by W1 (201 MB at that shape), the backward one by
+// its fused update (805 MB).
+//
+// GEMM kernel: 256 threads, four waves of 64 x 64 (forward, 128 x 128 block tile) or 32 x 64 (backward, 64 x 128).
+// K goes through LDS in slices of 32, two buffers and one barrier per slice: a slice is loaded as fp32, split
+// in registers on its way into LDS and read back as 16-byte operand pieces.  Neither operand needs to be K-contiguous
+// in memory: a thread stages 8 consecutive k of its row or column, so no transposed copy is ever written.
 #include "internal.hpp"
 #include "philox.hpp"
 
@@ -39,9 +42,10 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f16v __attribute__((ext_vector_type(16)));
 
 constexpr int kBK = 32;               // K slice staged through LDS
-constexpr int kAPitch = kBK + 1;      // odd pitch: conflict-free fragment reads
 constexpr int kShapeM = 128, kShapeN = 64;   // shape contract: n_in, batch multiples of 128; n_hid of 64
 constexpr int kMaxOut = 16;
+constexpr uint32_t kXcds = 8;                // accelerator complex dies of the MI355X
+constexpr uint64_t kMaxHiddenOut = 32768;    // and n_hid * (n_out rounded up to odd) is at most this
 
 struct Offsets { uint64_t W1, b1, W2, b2; };
 __host__ __device__ inline Offsets offsets_of(const MlpParams &p)
@@ -104,288 +108,6 @@ __global__ __launch_bounds__(256) void gen_batch_kernel(const MlpParams p)
     gen_batch_block(p, blockIdx.x, threadIdx.x, blockIdx.y, step, p.X, p.y);
 }
 
-// ---- the two big contractions ---------------------------------------------------------------------
-enum { kFwd = 0, kBwd = 1, kBwdTail = 2 };   // kBwdTail: the backward product of a round's last step (line 6 in its epilogue)
-constexpr uint32_t kXcds = 8;      // accelerator complex dies of the MI355X
-
-// NWM x NWN waves per block, one 32x32 accumulator per wave: block tile (32 NWM) x (32 NWN).
-template <int EPI, int NWM, int NWN>
-__global__ __launch_bounds__(64 * NWM * NWN) void mlp_gemm_kernel(const MlpParams p)
-{
-    constexpr int BM = 32 * NWM, BN = 32 * NWN, THREADS = 64 * NWM * NWN;
-    constexpr int BPITCH = BN + 4, CPITCH = BN + 4;            // rows stay 16-byte aligned
-    constexpr int STAGE = 2 * BM * kAPitch + 2 * kBK * BPITCH, TILE = BM * CPITCH;
-    __shared__ __attribute__((aligned(16))) float smem[STAGE > TILE ? STAGE : TILE];
-    float (*As)[BM][kAPitch] = reinterpret_cast<float (*)[BM][kAPitch]>(smem);                    // [buf][m][k]
-    float (*Bs)[kBK][BPITCH] = reinterpret_cast<float (*)[kBK][BPITCH]>(smem + 2 * BM * kAPitch);  // [buf][k][n]
-    float (*Ct)[CPITCH] = reinterpret_cast<float (*)[CPITCH]>(smem);                               // epilogue tile
-
-    // Workgroups go to the 8 XCDs (each with its own L2) round-robin by linear id.  Renumber them so
-    // that every XCD owns a CONTIGUOUS run of tiles (n fastest, then m, then worker): the tiles that
-    // share an operand panel (all n-tiles of an m-tile share its X panel, all m-tiles of an n-tile its
-    // W1 / dA panel) then meet in one L2 instead of fetching the panel once per XCD.
-    uint32_t bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
-    {
-        const uint32_t total = gridDim.x * gridDim.y * gridDim.z;
-        if (total % kXcds == 0) {
-            const uint32_t linear = bx + gridDim.x * (by + gridDim.y * bz);
-            const uint32_t logical = (linear % kXcds) * (total / kXcds) + linear / kXcds;
-            bx = logical % gridDim.x;
-            by = (logical / gridDim.x) % gridDim.y;
-            bz = logical / (gridDim.x * gridDim.y);
-        }
-    }
-    const uint32_t worker = bz;
-    const uint32_t m0 = by * BM, n0 = bx * BN;
-    const Offsets o = offsets_of(p);
-    const uint32_t t = threadIdx.x;
-    const uint32_t ldb = p.n_hid;
-    const float *Xw = p.X + static_cast<uint64_t>(worker) * p.batch * p.n_in;
-
-    // Global -> register staging of one K slice, in 16-byte quads.
-    //   forward : A = X [batch][n_in], K-contiguous: a quad is 4 consecutive k of one row m
-    //   backward: A = X^T, read from X M-contiguous: a quad is 4 consecutive rows m of one sample k
-    //   B tile  : kBK x BN, N-contiguous (W1 rows, or dA rows)
-    // (a tile with fewer A quads than threads is staged by the block's first A_QUADS threads: whole waves)
-    constexpr int A_QUADS = BM * kBK / 4, PA = A_QUADS >= THREADS ? A_QUADS / THREADS : 1;
-    constexpr int B_QUADS = kBK * BN / 4, PB = B_QUADS / THREADS;
-    constexpr bool A_ALL = A_QUADS >= THREADS;
-    static_assert((A_ALL ? PA * THREADS == A_QUADS : A_QUADS % 64 == 0) && PB * THREADS == B_QUADS, "tile must split evenly over the block");
-    static_assert(EPI != kFwd || (PA <= 2 && PB <= 4), "the forward loop spreads the staging traffic over fixed slots of the MFMA chain");
-    constexpr int A_MINOR = (EPI == kFwd) ? kBK / 4 : BM / 4;   // quads along the contiguous direction
-    constexpr int A_MAJOR_PER_PASS = THREADS / A_MINOR;
-    constexpr int B_K_PER_PASS = THREADS / (BN / 4);
-    const uint32_t a_minor = (t % A_MINOR) * 4, a_major = t / A_MINOR;
-    const uint32_t b_n = (t % (BN / 4)) * 4, b_k = t / (BN / 4);
-    const float *a_src, *b_src;
-    uint64_t a_slice, a_pass;    // element strides of A per K slice and per staging pass
-    uint32_t K;
-    if (EPI == kFwd) {
-        a_src = Xw + static_cast<uint64_t>(m0 + a_major) * p.n_in + a_minor;
-        a_slice = kBK; a_pass = static_cast<uint64_t>(A_MAJOR_PER_PASS) * p.n_in;
-        K = p.n_in;
-        b_src = p.x_in + static_cast<uint64_t>(worker) * p.stride + o.W1;                 // W1 [n_in][n_hid]
-    } else {
-        a_src = Xw + static_cast<uint64_t>(a_major) * p.n_in + m0 + a_minor;
-        a_slice = static_cast<uint64_t>(kBK) * p.n_in; a_pass = static_cast<uint64_t>(A_MAJOR_PER_PASS) * p.n_in;
-        K = p.batch;
-        b_src = p.dA + static_cast<uint64_t>(worker) * p.batch * p.n_hid;                 // dA [batch][n_hid]
-    }
-    b_src += static_cast<uint64_t>(b_k) * ldb + n0 + b_n;
-
-    // Forward product: four sets of staging registers, so global loads run four K slices ahead of their
-    // use; that covers the HBM latency of the weight stream (one slice of MFMAs is shorter than it).
-    // One block of 8 waves per CU leaves 256 registers per lane: the sets cost nothing in occupancy.
-    // Backward product: K is only the batch (4 slices); one set keeps the registers, and with them
-    // the number of resident blocks, where the memory-bound epilogue wants them.
-    constexpr int NSETS = (EPI == kFwd) ? 4 : 1;
-    f4 ra[NSETS][PA], rb[NSETS][PB];
-    auto load_slice = [&](auto set, uint32_t slice) {
-        constexpr int S = decltype(set)::value;
-        if (A_ALL || t < A_QUADS) {
-            #pragma unroll
-            for (int i = 0; i < PA; ++i) ra[S][i] = *reinterpret_cast<const f4 *>(a_src + slice * a_slice + i * a_pass);
-        }
-        #pragma unroll
-        for (int i = 0; i < PB; ++i)
-            rb[S][i] = *reinterpret_cast<const f4 *>(b_src + (static_cast<uint64_t>(slice) * kBK + static_cast<uint64_t>(i) * B_K_PER_PASS) * ldb);
-    };
-    auto stage_to_lds = [&](auto set, uint32_t buf) {
-        constexpr int S = decltype(set)::value;
-        if (A_ALL || t < A_QUADS) {
-            #pragma unroll
-            for (int i = 0; i < PA; ++i) {
-                const uint32_t major = a_major + i * A_MAJOR_PER_PASS;
-                #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (EPI == kFwd) As[buf][major][a_minor + j] = ra[S][i][j];      // (row, k)
-                    else             As[buf][a_minor + j][major] = ra[S][i][j];      // transposed on the way in
-                }
-            }
-        }
-        #pragma unroll
-        for (int i = 0; i < PB; ++i) *reinterpret_cast<f4 *>(&Bs[buf][b_k + i * B_K_PER_PASS][b_n]) = rb[S][i];
-    };
-    using Set0 = std::integral_constant<int, 0>;
-    using Set1 = std::integral_constant<int, 1>;
-
-    const uint32_t wave = t / 64, lane = t % 64;
-    const uint32_t wm = wave % NWM, wn = wave / NWM;             // wave owns rows 32 wm .., columns 32 wn ..
-    const uint32_t frag_m = wm * 32 + lane % 32, frag_k = lane / 32, frag_n = wn * 32 + lane % 32;
-    f16v acc = {0};
-
-    // Backward product: the epilogue updates this block's tile of W1 and its momentum.  Vector loads
-    // return in order, so these 64 KB must be the YOUNGEST loads in flight or every operand slice
-    // behind them would wait for them: they are issued right after the loads of the last K slice
-    // and land under the remaining multiplies.
-    constexpr int EPI_ITERS = (BM * BN / 4) / THREADS;
-    f4 x_old[EPI_ITERS], v_old[EPI_ITERS], snap_old[EPI_ITERS];
-    auto prefetch_tile = [&]() {
-        #pragma unroll
-        for (int it = 0; it < EPI_ITERS; ++it) {
-            const uint32_t idx = it * THREADS + t;
-            const uint64_t at = static_cast<uint64_t>(worker) * p.stride + o.W1 +
-                                static_cast<uint64_t>(m0 + idx / (BN / 4)) * p.n_hid + n0 + (idx % (BN / 4)) * 4;
-            x_old[it] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p.x_in + at));
-            v_old[it] = p.momentum != 0.0f ? __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p.v + at)) : f4{0.f, 0.f, 0.f, 0.f};
-            if (EPI == kBwdTail) snap_old[it] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p.snap + at));
-        }
-    };
-
-    // Software pipeline over the K slices (their number is a multiple of 4 by the shape contract).
-    // At the top of iteration s: slice s sits in LDS buffer s&1, visible to all waves; slice s+1
-    // sits in a register set; with two sets the loads of slice s+2 into the other set are in flight.
-    // The iteration reads its fragments, pushes slice s+1 into the other LDS buffer and starts the
-    // loads of the next slice to fetch BEFORE the chain of 16 MFMAs, so all of that runs under the
-    // multiplies; one barrier per slice.
-    const uint32_t n_slices = K / kBK;
-    auto iteration = [&](auto next_set, uint32_t s, auto stage, auto load) {
-        const uint32_t cur = s & 1;
-        float af[kBK / 2], bf[kBK / 2];
-        #pragma unroll
-        for (int i = 0; i < kBK / 2; ++i) {
-            af[i] = As[cur][frag_m][2 * i + frag_k];
-            bf[i] = Bs[cur][2 * i + frag_k][frag_n];
-        }
-        // compile-time switches, not run-time conditions (see the forward loop)
-        if constexpr (decltype(stage)::value) stage_to_lds(next_set, cur ^ 1);   // buffer last read in iteration s-1, before its barrier
-        if constexpr (decltype(load)::value) load_slice(next_set, s + 2);
-        #pragma unroll
-        for (int i = 0; i < kBK / 2; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i], bf[i], acc, 0, 0, 0);
-        __syncthreads();        // slice s+1 visible; everyone is done reading buffer cur
-    };
-    load_slice(Set0{}, 0);
-    if constexpr (NSETS == 4) {
-        // Forward product, one stage deeper: the fragments of slice s+1 are read from LDS during the MFMA
-        // chain of slice s (two fragment sets), so the matrix pipe does not idle while both waves of a
-        // SIMD sit in their LDS-read phase (there is one block of 8 waves per CU: nothing else to run).
-        // Top of iteration s: fragments of slice s in set s&1; slice s+1 in LDS buffer (s+1)&1, visible;
-        // slices s+2 .. s+5 in (or on their way into) the four staging sets.
-        float af2[2][kBK / 2], bf2[2][kBK / 2];
-        const uint32_t last = n_slices - 1;
-        auto read_frags = [&](auto par, uint32_t buf) {
-            constexpr int F = decltype(par)::value;
-            #pragma unroll
-            for (int i = 0; i < kBK / 2; ++i) {
-                af2[F][i] = As[buf][frag_m][2 * i + frag_k];
-                bf2[F][i] = Bs[buf][2 * i + frag_k][frag_n];
-            }
-        };
-        // slice t lives in staging set t % 4; iteration s stages slice s+2 and refills that set with slice s+6
-        auto deep_iteration = [&](auto par, auto other, auto set, uint32_t s) {
-            constexpr int F = decltype(par)::value, O = decltype(other)::value, S = decltype(set)::value;
-            // No run-time conditions in the loop body: past the end the same steps run on the last slice
-            // again and their results are never used.  (With steps under `if`, the number of loads in
-            // flight at a given point depends on the path taken, and the compiler must then wait for ALL
-            // of them before the first use of any.)
-            // Issue order: the 16 multiplies form a dependent chain (each waits 64 cycles for the one
-            // before) and a wave issues in order, so the memory instructions go INTO the gaps of the
-            // chain: after multiply i, element i of the next slice's fragments, and one piece of the
-            // staging traffic.  A scheduling fence after every group pins that order; left to itself the
-            // scheduler sinks each fragment read to its first use (which undoes the pipeline) or issues
-            // the memory instructions in one lump (then both waves of a SIMD sit in that phase together,
-            // right after the barrier, and the matrix pipe idles).
-            const uint32_t nb = (s + 1) & 1, wb = s & 1;          // buffers: next fragments from nb, slice s+2 into wb
-            const uint32_t refill = s + 6 < n_slices ? s + 6 : last;
-            #pragma unroll
-            for (int i = 0; i < kBK / 2; ++i) {
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af2[F][i], bf2[F][i], acc, 0, 0, 0);
-                af2[O][i] = As[nb][frag_m][2 * i + frag_k];
-                bf2[O][i] = Bs[nb][2 * i + frag_k][frag_n];
-                if (i >= 2 && i < 2 + PA) {                       // A quad of slice s+2 -> LDS (buffer last read in iteration s-1)
-                    const int a = i - 2;
-                    const uint32_t major = a_major + a * A_MAJOR_PER_PASS;
-                    #pragma unroll
-                    for (int j = 0; j < 4; ++j) As[wb][major][a_minor + j] = ra[S][a][j];
-                }
-                if (i >= 4 && i < 4 + PB) {                       // B quads of slice s+2 -> LDS
-                    const int bq = i - 4;
-                    *reinterpret_cast<f4 *>(&Bs[wb][b_k + bq * B_K_PER_PASS][b_n]) = rb[S][bq];
-                }
-                if (i >= 8 && i < 8 + PA)                         // refill the staging set: slice s+6
-                    ra[S][i - 8] = *reinterpret_cast<const f4 *>(a_src + refill * a_slice + (i - 8) * a_pass);
-                if (i >= 10 && i < 10 + PB)
-                    rb[S][i - 10] = *reinterpret_cast<const f4 *>(b_src + (static_cast<uint64_t>(refill) * kBK + static_cast<uint64_t>(i - 10) * B_K_PER_PASS) * ldb);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            __syncthreads();
-        };
-        using Set2 = std::integral_constant<int, 2>;
-        using Set3 = std::integral_constant<int, 3>;
-        load_slice(Set1{}, 1);
-        load_slice(Set2{}, 2);
-        load_slice(Set3{}, 3);
-        // slices 4 and 5 do not exist when K = 128 (four slices): like the in-loop refill, the prefetch then
-        // reads the last slice again (never used) instead of running past the operands
-        stage_to_lds(Set0{}, 0);
-        load_slice(Set0{}, 4 < n_slices ? 4 : last);
-        __syncthreads();
-        read_frags(Set0{}, 0);
-        stage_to_lds(Set1{}, 1);
-        load_slice(Set1{}, 5 < n_slices ? 5 : last);
-        __syncthreads();
-        for (uint32_t s = 0; s < n_slices; s += 4) {        // the slice count is a multiple of 4
-            deep_iteration(Set0{}, Set1{}, Set2{}, s);
-            deep_iteration(Set1{}, Set0{}, Set3{}, s + 1);
-            deep_iteration(Set0{}, Set1{}, Set0{}, s + 2);
-            deep_iteration(Set1{}, Set0{}, Set1{}, s + 3);
-        }
-    } else {
-        stage_to_lds(Set0{}, 0);
-        load_slice(Set0{}, 1);
-        __syncthreads();
-        uint32_t s = 0;
-        for (; s + 2 < n_slices; ++s) iteration(Set0{}, s, std::true_type{}, std::true_type{});
-        prefetch_tile();
-        iteration(Set0{}, s, std::true_type{}, std::false_type{});
-        iteration(Set0{}, s + 1, std::false_type{}, std::false_type{});
-    }
-
-    // accumulators -> LDS tile.  Register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32 of the 32x32 block.
-    // (the loop's last barrier already guarantees that the staging buffers are dead)
-    #pragma unroll
-    for (int r = 0; r < 16; ++r)
-        Ct[wm * 32 + 8 * (r / 4) + 4 * (lane / 32) + (r % 4)][wn * 32 + lane % 32] = acc[r];
-    __syncthreads();
-
-    // epilogue over the tile in row-major quads: BN/4 lanes cover one row
-    #pragma unroll
-    for (int it = 0; it < EPI_ITERS; ++it) {
-        const uint32_t idx = it * THREADS + t;
-        const uint32_t row = idx / (BN / 4), col = (idx % (BN / 4)) * 4;
-        const f4 val = *reinterpret_cast<const f4 *>(&Ct[row][col]);
-        if (EPI == kFwd) {
-            const f4 bias = *reinterpret_cast<const f4 *>(p.x_in + static_cast<uint64_t>(worker) * p.stride + o.b1 + n0 + col);
-            f4 h = val + bias;
-            h.x = fmaxf(h.x, 0.f); h.y = fmaxf(h.y, 0.f); h.z = fmaxf(h.z, 0.f); h.w = fmaxf(h.w, 0.f);
-            *reinterpret_cast<f4 *>(p.H + (static_cast<uint64_t>(worker) * p.batch + m0 + row) * p.n_hid + n0 + col) = h;
-        } else {
-            const uint64_t at = static_cast<uint64_t>(worker) * p.stride + o.W1 + static_cast<uint64_t>(m0 + row) * p.n_hid + n0 + col;
-            f4 g = val + p.weight_decay * x_old[it];
-            if (p.momentum != 0.0f) {
-                g = p.momentum * v_old[it] + g;
-                __builtin_nontemporal_store(g, reinterpret_cast<f4 *>(p.v + at));
-            }
-            f4 x_new = x_old[it] - p.lr * g;
-            if (EPI == kBwdTail) {       // line 6 of Algorithm 1 on the fresh model, same operation order as the separate kernel
-                const f4 mean = *reinterpret_cast<const f4 *>(p.mean + o.W1 + static_cast<uint64_t>(m0 + row) * p.n_hid + n0 + col);
-                x_new = mean + (x_new - snap_old[it]);
-            }
-            __builtin_nontemporal_store(x_new, reinterpret_cast<f4 *>(p.x_out + at));
-        }
-    }
-}
-
-template <int EPI, int NWM, int NWN>
-void launch_gemm(hipStream_t stream, const MlpParams &p, hipEvent_t start = nullptr, hipEvent_t stop = nullptr)
-{
-    const uint32_t M = (EPI == kFwd) ? p.batch : p.n_in;
-    const dim3 grid(p.n_hid / (32 * NWN), M / (32 * NWM), p.W), block(64 * NWM * NWN);
-    // the events, if any, take the kernel's own start / end timestamps (no marker of their own in the queue)
-    if (start || stop) hipExtLaunchKernelGGL((mlp_gemm_kernel<EPI, NWM, NWN>), grid, block, 0, stream, start, stop, 0, p);
-    else               hipLaunchKernelGGL((mlp_gemm_kernel<EPI, NWM, NWN>), grid, block, 0, stream, p);
-}
-
 // ---- output layer -----------------------------------------------------------------------------------
 __device__ __forceinline__ float wave_sum(float v)
 {
@@ -394,142 +116,191 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
-// Output layer, forward and backward, one wave per sample (eight waves and samples per block, so that two
-// waves share a SIMD: a wave's loop is a chain of memory round trips and shuffles):
-//   Z = H W2 + b2 by a strided dot product over the hidden units and a butterfly reduction, softmax
-//   (row maximum subtracted), dZ = (P - onehot(y)) / batch, then dA = (dZ W2^T) * [H > 0] for the
-//   wave's own hidden units.  W2 of the block's worker sits in LDS (row pitch n_out + 1 when n_out
-//   is even, so the 64 lanes of a wave, which read 64 consecutive rows, spread over the banks).
-//   The output width is a template parameter: with it known, the loops over the classes unroll into
-//   straight-line code (as a run-time bound they became a branch per class and per hidden unit).
-constexpr int kHeadSamples = 8;        // per block: one wave each
-constexpr int kHeadBatch = 8;          // independent loads in flight per lane
-constexpr int kHeadKeep = 2;           // head: batches of a sample's H row that stay in registers (1024 hidden units)
+// Output layer, forward and backward, for sixteen samples of one worker per block:
+//   H = relu(sum of the forward product's K splits + b1), Z = H W2 + b2, softmax (row maximum subtracted),
+//   dZ = (P - onehot(y)) / batch, dA = (dZ W2^T) * [H > 0], and the largest |dA| of the block.
+// Memory is touched a row at a time: a wave takes one sample's row in 1 KiB pieces and puts it into LDS, and dA leaves
+// the same way (reading the rows straight into the products' operand layout, 64 bytes from each of 16 rows 4 KiB
+// apart, took 25 us instead of 17 us at W = 16, 3072-1024-10, batch 128, four K splits).  Both products run on the fp32 matrix
+// instruction 16x16x4; a wave owns every sixteenth block of 16 hidden units, and a lane's four consecutive units of
+// one sample are at once the A operand of Z = H W2 (quarter j of a block's 16 k in instruction j) and the result
+// of dA^T = W2 dZ^T, so one LDS tile serves H, both products, the relu mask and dA.
+typedef float f4v __attribute__((ext_vector_type(4)));
+constexpr int kHeadSamples = 16;       // per block
+constexpr int kHeadWaves = 16;
+constexpr uint32_t kHeadChunk = 2048;  // hidden units held in LDS at a time (132 KB); more pass through it chunk by chunk
+constexpr int kHeadGroup = 4;          // 1 KiB pieces of a row, and
+constexpr int kHeadTerms = 4;          //   terms of H (K splits beside the first, bias) that are requested together
 constexpr int kUpdateWaves = 8;                 // head_update: waves per block, each sums an eighth of the batch
 constexpr int kDzGroup = 16, kDzBatch = 16;     //   samples per staged group of dZ rows, and per batch of H / dA loads
-constexpr uint32_t kHeadLdsBytes = 128u << 10;
-__host__ __device__ inline uint32_t head_w2_pitch(uint32_t n_out) { return n_out % 2 == 0 ? n_out + 1 : n_out; }
-template <int NOUT>
-__global__ __launch_bounds__(64 * kHeadSamples) void head_kernel(const MlpParams p)
+__host__ __device__ inline uint32_t head_pitch(uint32_t n_hid) { return (n_hid < kHeadChunk ? n_hid : kHeadChunk) + 4; }
+
+__global__ __launch_bounds__(64 * kHeadWaves) void head_kernel(const MlpParams p)
 {
-    constexpr uint32_t THREADS = 64 * kHeadSamples;
-    constexpr uint32_t w2_pitch = NOUT % 2 == 0 ? NOUT + 1 : NOUT;
-    extern __shared__ float w2s[];     // [n_hid][w2_pitch]
-    const uint32_t worker = blockIdx.y;
+    static_assert(kHeadWaves == kHeadSamples, "one wave per row");
+    extern __shared__ __attribute__((aligned(16))) float tile[];                // [kHeadSamples][head_pitch]: a chunk of H, then of dA
+    __shared__ float zs[kHeadWaves][kHeadSamples][kMaxOut];
+    __shared__ float dzs[kHeadSamples][kMaxOut + 1];
+    __shared__ float wave_max[kHeadWaves];
+    const uint32_t worker = blockIdx.y, group = blockIdx.x, pitch = head_pitch(p.n_hid);
     const uint32_t lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+    const uint32_t s16 = lane % 16, g = lane / 16;
     const Offsets o = offsets_of(p);
     const float *theta = p.x_in + static_cast<uint64_t>(worker) * p.stride;
-    // The wave's sample, and the first kHeadKeep batches of its H row: requested before anything else (they
-    // arrive while W2 is staged) and kept in registers for the second pass.
-    const uint32_t b = blockIdx.x * kHeadSamples + wave;
-    const bool have_sample = b < p.batch;                              // wave-uniform
-    const uint64_t sample = static_cast<uint64_t>(worker) * p.batch + (have_sample ? b : 0u);
-    const float *Hrow = p.H + sample * p.n_hid;
-    float hkeep[kHeadKeep][kHeadBatch];
-    #pragma unroll
-    for (int it = 0; it < kHeadKeep; ++it) {
+    const float *W2 = theta + o.W2;
+    const uint64_t sample = static_cast<uint64_t>(worker) * p.batch + group * kHeadSamples + wave;     // the wave's row
+    float *Hrow = p.H + sample * p.n_hid;
+    const uint64_t part = static_cast<uint64_t>(p.W) * p.batch * p.n_hid;      // one K split of the forward product
+    const float *Prow = p.H_part + sample * p.n_hid;
+    // the softmax's thread per sample and class
+    const uint32_t smp = (threadIdx.x / kMaxOut) % kHeadSamples, c = threadIdx.x % kMaxOut;
+    const uint64_t row = static_cast<uint64_t>(worker) * p.batch + group * kHeadSamples + smp;
+    const bool real = c < p.n_out;
+    const int label = p.y[row];
+    const float b2 = real ? theta[o.b2 + c] : 0.0f;
+
+    // operands of W2 for kHeadGroup blocks of a wave, requested ahead of the barriers that their use stands behind
+    float w2[kHeadGroup][4];
+    auto load_w2_rows = [&](uint32_t c0, uint32_t blk0, uint32_t n_blocks) {           // k = hidden unit, column = class
         #pragma unroll
-        for (int u = 0; u < kHeadBatch; ++u) {
-            const uint32_t n = lane + 64u * (u + kHeadBatch * it);
-            hkeep[it][u] = n < p.n_hid ? Hrow[n] : 0.0f;
+        for (int i = 0; i < kHeadGroup; ++i) {
+            const uint32_t blk = blk0 + kHeadWaves * i;
+            #pragma unroll
+            for (int j = 0; j < 4; ++j)
+                w2[i][j] = blk < n_blocks && s16 < p.n_out ? W2[static_cast<uint64_t>(c0 + 16 * blk + 4 * g + j) * p.n_out + s16] : 0.0f;
         }
-    }
-    // W2 -> LDS in 16-byte pieces, four loads in flight per thread (the matrix starts on a 16-byte
-    // boundary and holds a multiple of 4 elements, by the shape contract)
-    const uint32_t n_quads = p.n_hid * NOUT / 4;
-    for (uint32_t q0 = threadIdx.x; q0 < n_quads; q0 += THREADS * 4) {
-        f4 r[4];
+    };
+    auto load_w2_classes = [&](uint32_t c0, uint32_t blk0, uint32_t n_blocks) {        // row = hidden unit, k = class
         #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            r[u] = q0 + THREADS * u < n_quads ? *reinterpret_cast<const f4 *>(theta + o.W2 + 4ull * (q0 + THREADS * u)) : f4{0.f, 0.f, 0.f, 0.f};
-        #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (q0 + THREADS * u < n_quads) {
+        for (int i = 0; i < kHeadGroup; ++i) {
+            const uint32_t blk = blk0 + kHeadWaves * i;
+            #pragma unroll
+            for (int q = 0; q < 4; ++q)
+                w2[i][q] = blk < n_blocks && 4 * q + g < p.n_out ? W2[static_cast<uint64_t>(c0 + 16 * blk + s16) * p.n_out + 4 * q + g] : 0.0f;
+        }
+    };
+
+    f4v z = {0.f, 0.f, 0.f, 0.f};
+    for (uint32_t c0 = 0; c0 < p.n_hid; c0 += kHeadChunk) {
+        const uint32_t width = p.n_hid - c0 < kHeadChunk ? p.n_hid - c0 : kHeadChunk;
+        if (c0 != 0) __syncthreads();                          // the chunk before has been multiplied
+        for (uint32_t n0 = 4 * lane; n0 < width; n0 += 256 * kHeadGroup) {
+            f4 h[kHeadGroup];
+            #pragma unroll
+            for (int i = 0; i < kHeadGroup; ++i) {
+                const uint32_t n = n0 + 256 * i;
+                h[i] = n < width ? *reinterpret_cast<const f4 *>(Hrow + c0 + n) : f4{0.f, 0.f, 0.f, 0.f};
+            }
+            for (uint32_t t0 = 1; t0 <= p.fwd_splits; t0 += kHeadTerms) {      // the other K splits in order, then the bias
+                f4 q[kHeadTerms][kHeadGroup];
                 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t i = 4 * (q0 + THREADS * u) + j;
-                    w2s[(i / NOUT) * w2_pitch + i % NOUT] = r[u][j];
+                for (int s = 0; s < kHeadTerms; ++s) {
+                    const float *src = t0 + s < p.fwd_splits ? Prow + (t0 + s - 1) * part : theta + o.b1;
+                    #pragma unroll
+                    for (int i = 0; i < kHeadGroup; ++i) {
+                        const uint32_t n = n0 + 256 * i;
+                        q[s][i] = t0 + s <= p.fwd_splits && n < width ? *reinterpret_cast<const f4 *>(src + c0 + n) : f4{0.f, 0.f, 0.f, 0.f};
+                    }
+                }
+                #pragma unroll
+                for (int s = 0; s < kHeadTerms; ++s)
+                    #pragma unroll
+                    for (int i = 0; i < kHeadGroup; ++i) h[i] += q[s][i];
+            }
+            #pragma unroll
+            for (int i = 0; i < kHeadGroup; ++i) {
+                const uint32_t n = n0 + 256 * i;
+                if (n < width) {
+                    f4 a = h[i];
+                    a.x = fmaxf(a.x, 0.f); a.y = fmaxf(a.y, 0.f); a.z = fmaxf(a.z, 0.f); a.w = fmaxf(a.w, 0.f);
+                    *reinterpret_cast<f4 *>(Hrow + c0 + n) = a;
+                    *reinterpret_cast<f4 *>(tile + wave * pitch + n) = a;
                 }
             }
+        }
+        const uint32_t n_blocks = width / 16;
+        load_w2_rows(c0, wave, n_blocks);
+        __syncthreads();
+        for (uint32_t blk0 = wave; blk0 < n_blocks; blk0 += kHeadWaves * kHeadGroup) {
+            if (blk0 != wave) load_w2_rows(c0, blk0, n_blocks);
+            #pragma unroll
+            for (int i = 0; i < kHeadGroup; ++i) {
+                const uint32_t blk = blk0 + kHeadWaves * i;
+                if (blk < n_blocks) {                          // wave-uniform
+                    const f4 h = *reinterpret_cast<const f4 *>(tile + s16 * pitch + 16 * blk + 4 * g);
+                    #pragma unroll
+                    for (int j = 0; j < 4; ++j) z = __builtin_amdgcn_mfma_f32_16x16x4f32(h[j], w2[i][j], z, 0, 0, 0);
+                }
+            }
+        }
+    }
+    load_w2_classes(0, wave, (p.n_hid < kHeadChunk ? p.n_hid : kHeadChunk) / 16);
+    #pragma unroll
+    for (int r = 0; r < 4; ++r) zs[wave][4 * g + r][s16] = z[r];
+    __syncthreads();
+    if (threadIdx.x < kHeadSamples * kMaxOut) {                // one thread per sample and class
+        float a = 0.0f;
+        #pragma unroll
+        for (int w = 0; w < kHeadWaves; ++w) a += zs[w][smp][c];
+        a = real ? a + b2 : -INFINITY;
+        float zmax = a;
+        #pragma unroll
+        for (int off = 8; off > 0; off >>= 1) zmax = fmaxf(zmax, __shfl_xor(zmax, off, 16));
+        const float e = real ? expf(a - zmax) : 0.0f;
+        float denom = e;
+        #pragma unroll
+        for (int off = 8; off > 0; off >>= 1) denom += __shfl_xor(denom, off, 16);
+        const float dz = real ? (e / denom - (label == static_cast<int>(c) ? 1.0f : 0.0f)) * (1.0f / static_cast<float>(p.batch)) : 0.0f;
+        dzs[smp][c] = dz;
+        p.dZ[row * kMaxOut + c] = dz;
     }
     __syncthreads();
-    const float inv_b = 1.0f / static_cast<float>(p.batch);
-    {
-        if (!have_sample) return;                                  // behind the only barrier
-        float z[NOUT];
-        #pragma unroll
-        for (int c = 0; c < NOUT; ++c) z[c] = 0.0f;
-        #pragma unroll
-        for (int it = 0; it < kHeadKeep; ++it) {
+    float dz[kMaxOut / 4];
+    #pragma unroll
+    for (int q = 0; q < kMaxOut / 4; ++q) dz[q] = dzs[s16][4 * q + g];
+    const uint32_t steps = (p.n_out + 3) / 4;
+    float most = 0.0f;
+    float *dArow = p.dA + sample * p.n_hid;
+    for (uint32_t c0 = 0; c0 < p.n_hid; c0 += kHeadChunk) {
+        const uint32_t width = p.n_hid - c0 < kHeadChunk ? p.n_hid - c0 : kHeadChunk;
+        if (p.n_hid > kHeadChunk) {                            // H did not stay in LDS (the wave's own row: same lanes wrote it)
+            for (uint32_t n = 4 * lane; n < width; n += 256)
+                *reinterpret_cast<f4 *>(tile + wave * pitch + n) = *reinterpret_cast<const f4 *>(Hrow + c0 + n);
+            __syncthreads();
+        }
+        const uint32_t n_blocks = width / 16;
+        for (uint32_t blk0 = wave; blk0 < n_blocks; blk0 += kHeadWaves * kHeadGroup) {
+            if (c0 != 0 || blk0 != wave) load_w2_classes(c0, blk0, n_blocks);
             #pragma unroll
-            for (int u = 0; u < kHeadBatch; ++u) {
-                const uint32_t n = lane + 64u * (u + kHeadBatch * it);
-                if (n < p.n_hid) {
-                    const float *w2 = w2s + n * w2_pitch;
+            for (int i = 0; i < kHeadGroup; ++i) {
+                const uint32_t blk = blk0 + kHeadWaves * i;
+                if (blk < n_blocks) {                          // wave-uniform
+                    f4 *at = reinterpret_cast<f4 *>(tile + s16 * pitch + 16 * blk + 4 * g);
+                    const f4 h = *at;
+                    f4v d = {0.f, 0.f, 0.f, 0.f};
                     #pragma unroll
-                    for (int c = 0; c < NOUT; ++c) z[c] += hkeep[it][u] * w2[c];
+                    for (int q = 0; q < kMaxOut / 4; ++q)
+                        if (static_cast<uint32_t>(q) < steps) d = __builtin_amdgcn_mfma_f32_16x16x4f32(w2[i][q], dz[q], d, 0, 0, 0);
+                    *at = f4{h.x > 0.0f ? d[0] : 0.0f, h.y > 0.0f ? d[1] : 0.0f, h.z > 0.0f ? d[2] : 0.0f, h.w > 0.0f ? d[3] : 0.0f};
                 }
             }
         }
-        // hidden units beyond the kept ones in batches of kHeadBatch loads in flight (one load at a time
-        // would make the loop a chain of memory latencies)
-        for (uint32_t n0 = lane + 64u * kHeadBatch * kHeadKeep; n0 < p.n_hid; n0 += 64 * kHeadBatch) {
-            float hv[kHeadBatch];
-            #pragma unroll
-            for (int u = 0; u < kHeadBatch; ++u) hv[u] = n0 + 64 * u < p.n_hid ? Hrow[n0 + 64 * u] : 0.0f;
-            #pragma unroll
-            for (int u = 0; u < kHeadBatch; ++u) {
-                if (n0 + 64 * u < p.n_hid) {
-                    const float *w2 = w2s + (n0 + 64 * u) * w2_pitch;
-                    #pragma unroll
-                    for (int c = 0; c < NOUT; ++c) z[c] += hv[u] * w2[c];
-                }
-            }
+        __syncthreads();
+        for (uint32_t n = 4 * lane; n < width; n += 256) {
+            const f4 a = *reinterpret_cast<const f4 *>(tile + wave * pitch + n);
+            *reinterpret_cast<f4 *>(dArow + c0 + n) = a;
+            most = fmaxf(most, fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))));
         }
-        float zmax = -INFINITY;
+        if (c0 + kHeadChunk < p.n_hid) __syncthreads();
+    }
+    #pragma unroll
+    for (int off = 32; off > 0; off >>= 1) most = fmaxf(most, __shfl_xor(most, off, 64));
+    if (lane == 0) wave_max[wave] = most;
+    __syncthreads();
+    if (threadIdx.x == 0) {
         #pragma unroll
-        for (int c = 0; c < NOUT; ++c) {
-            z[c] = wave_sum(z[c]) + theta[o.b2 + c];
-            zmax = fmaxf(zmax, z[c]);
-        }
-        float denom = 0.0f;
-        #pragma unroll
-        for (int c = 0; c < NOUT; ++c) { z[c] = expf(z[c] - zmax); denom += z[c]; }
-        const int label = p.y[sample];
-        #pragma unroll
-        for (int c = 0; c < NOUT; ++c) {
-            z[c] = (z[c] / denom - (label == c ? 1.0f : 0.0f)) * inv_b;                // dZ, the same in every lane
-            if (lane == static_cast<uint32_t>(c)) p.dZ[sample * kMaxOut + c] = z[c];
-        }
-        #pragma unroll
-        for (int it = 0; it < kHeadKeep; ++it) {
-            #pragma unroll
-            for (int u = 0; u < kHeadBatch; ++u) {
-                const uint32_t n = lane + 64u * (u + kHeadBatch * it);
-                if (n < p.n_hid) {
-                    const float *w2 = w2s + n * w2_pitch;
-                    float dh = 0.0f;
-                    #pragma unroll
-                    for (int c = 0; c < NOUT; ++c) dh += z[c] * w2[c];
-                    p.dA[sample * p.n_hid + n] = hkeep[it][u] > 0.0f ? dh : 0.0f;
-                }
-            }
-        }
-        for (uint32_t n0 = lane + 64u * kHeadBatch * kHeadKeep; n0 < p.n_hid; n0 += 64 * kHeadBatch) {
-            float hv[kHeadBatch];
-            #pragma unroll
-            for (int u = 0; u < kHeadBatch; ++u) hv[u] = n0 + 64 * u < p.n_hid ? Hrow[n0 + 64 * u] : 0.0f;
-            #pragma unroll
-            for (int u = 0; u < kHeadBatch; ++u) {
-                if (n0 + 64 * u < p.n_hid) {
-                    const float *w2 = w2s + (n0 + 64 * u) * w2_pitch;
-                    float dh = 0.0f;
-                    #pragma unroll
-                    for (int c = 0; c < NOUT; ++c) dh += z[c] * w2[c];
-                    p.dA[sample * p.n_hid + n0 + 64 * u] = hv[u] > 0.0f ? dh : 0.0f;
-                }
-            }
-        }
+        for (int w = 1; w < kHeadWaves; ++w) most = fmaxf(most, wave_max[w]);
+        p.dA_max[worker * gridDim.x + group] = most;
     }
 }
 
@@ -645,16 +416,379 @@ __global__ __launch_bounds__(64 * kUpdateWaves) void head_update_kernel(const Ml
     }
 }
 
-// The two output-layer kernels, instantiated for every supported output width 1..kMaxOut.
-template <int NOUT>
-hipError_t launch_heads_for(hipStream_t stream, const MlpParams &p)
+// ---- the two big contractions ---------------------------------------------------------------------
+enum { kFwd = 0, kBwd = 1, kBwdTail = 2 };   // kBwdTail: the backward product of a round's last step (line 6 in its epilogue)
+
+typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+
+// Eight values, scaled into the upper half of the fp16 range, as two fp16 vectors: the value rounded to 11 bits and
+// the (in fp32 exact) remainder rounded to 11 bits.
+struct Planes { u4 p[2]; };
+__device__ __forceinline__ Planes split8(const float (&a)[8], float scale)
 {
-    // more than the default 64 KB of dynamic LDS for wide hidden layers
-    static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(head_kernel<NOUT>),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, kHeadLdsBytes);
-    if (lds_ok != hipSuccess) return lds_ok;
-    hipLaunchKernelGGL(head_kernel<NOUT>, dim3((p.batch + kHeadSamples - 1) / kHeadSamples, p.W), dim3(64 * kHeadSamples),
-                       static_cast<size_t>(p.n_hid) * head_w2_pitch(NOUT) * sizeof(float), stream, p);
+    #pragma clang fp contract(off)
+    Planes out;
+    #pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float x0 = a[2 * i] * scale, x1 = a[2 * i + 1] * scale;
+        const h2 hi = {static_cast<_Float16>(x0), static_cast<_Float16>(x1)};
+        const h2 lo = {static_cast<_Float16>(x0 - static_cast<float>(hi.x)), static_cast<_Float16>(x1 - static_cast<float>(hi.y))};
+        out.p[0][i] = __builtin_bit_cast(unsigned int, hi);
+        out.p[1][i] = __builtin_bit_cast(unsigned int, lo);
+    }
+    return out;
+}
+
+// The power of two that takes a value of magnitude m to [2^target, 2^(target+1)); kept where it and its inverse
+// are normal numbers.
+__device__ __forceinline__ float scale_to(float m, uint32_t target)
+{
+    const uint32_t f = 254u + target - (__float_as_uint(m) >> 23);
+    return __uint_as_float((f < 240u ? f : 240u) << 23);
+}
+__device__ __forceinline__ float inverse_scale(float s) { return __uint_as_float((254u << 23) - __float_as_uint(s)); }
+
+// The mini-batch is drawn by this library: |x| <= sqrt(-2 ln 2^-24) = 5.77, times 2^12 below the largest fp16.
+constexpr float kXScale = 4096.0f;
+constexpr int kGemmThreads = 256;
+
+// The operand planes of one K slice in LDS, in the order in which the matrix instruction's lanes read them:
+// [plane][32-row block][k octet][slot] pieces of 16 bytes (8 consecutive k of one row or column).  A fragment read is
+// then 1 KiB contiguous per wave.  The slot of a row is chosen so that the eight lanes that write together also hit
+// eight different 16-byte bank groups: rows staged column-wise (two adjacent rows per thread) swap neighbours in
+// every other group of eight, rows staged k-wise (four octets of one row in four lanes) rotate by the octet.
+template <int ROWS>
+struct OperandTile {
+    u4 q[2][ROWS / 32][4][32];
+    static __device__ __forceinline__ uint32_t slot_col(uint32_t r) { return r ^ ((r >> 3) & 1u); }
+    static __device__ __forceinline__ uint32_t slot_k(uint32_t r, uint32_t o) { return (r + 2 * o) & 31u; }
+};
+
+// BM x BN block tile, four waves of (BM/2) x (BN/2).
+template <int EPI, int BM, int BN>
+__global__ __launch_bounds__(kGemmThreads, EPI == kBwd ? 3 : 2) void mlp_gemm_kernel(const MlpParams p)
+{
+    constexpr int MB = BM / 64, NB = BN / 64;                  // 32-blocks per wave and direction
+    constexpr int CPITCH = BN + 4;
+    struct Operands { OperandTile<BM> a; OperandTile<BN> b; };
+    constexpr int OPERANDS = 2 * sizeof(Operands), TILE = EPI == kFwd ? 0 : BM * CPITCH * 4;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[OPERANDS > TILE ? OPERANDS : TILE];
+    __shared__ float col_max[EPI == kFwd ? 4 : 1][EPI == kFwd ? BN : 1];
+    Operands *ops = reinterpret_cast<Operands *>(smem);                                            // two buffers
+    float (*Ct)[CPITCH] = reinterpret_cast<float (*)[CPITCH]>(smem);                               // epilogue tile
+
+    // Workgroups go to the 8 XCDs (each with its own L2) round-robin by linear id.  Renumber them so
+    // that every XCD owns a CONTIGUOUS run of tiles (n fastest, then m, then K split, then worker): the tiles that
+    // share an operand panel (all n-tiles of an m-tile share its X panel, all m-tiles of an n-tile its
+    // W1 / dA panel) then meet in one L2 instead of fetching the panel once per XCD.
+    uint32_t bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
+    {
+        const uint32_t total = gridDim.x * gridDim.y * gridDim.z;
+        const uint32_t linear = bx + gridDim.x * (by + gridDim.y * bz);
+        if (total % kXcds == 0) {
+            const uint32_t logical = (linear % kXcds) * (total / kXcds) + linear / kXcds;
+            bx = logical % gridDim.x;
+            by = (logical / gridDim.x) % gridDim.y;
+            bz = logical / (gridDim.x * gridDim.y);
+        }
+    }
+    const uint32_t splits = EPI == kFwd ? p.fwd_splits : 1u;
+    const uint32_t worker = bz / splits, split = bz % splits;
+    const uint32_t m0 = by * BM, n0 = bx * BN;
+    const Offsets o = offsets_of(p);
+    const uint32_t t = threadIdx.x, wave = t / 64, lane = t % 64;
+    const uint32_t ldb = p.n_hid;
+    const float *Xw = p.X + static_cast<uint64_t>(worker) * p.batch * p.n_in;
+
+    // Global -> register staging of one K slice: 8 consecutive k of one row or column per piece.
+    //   forward : A = X [batch][n_in], K-contiguous: lane t takes octet t % 4 of row t / 4 (+ 64)
+    //   backward: A = X^T, read from X M-contiguous: wave w takes octet w, lane l its BM/64 columns
+    //   B       : K-major (W1 rows, or dA rows): wave w takes octet w, lane l its BN/64 columns
+    constexpr int AP = BM / 64, BP = BN / 64;                  // pieces per thread
+    const float *a_src, *b_base, *b_src;
+    uint32_t slice0 = 0, n_slices;                             // this block's K slices: an even number, at least two
+    if (EPI == kFwd) {
+        const uint32_t pairs = p.n_in / kBK / 2;
+        slice0 = 2 * (pairs * split / splits);
+        n_slices = 2 * (pairs * (split + 1) / splits) - slice0;
+        a_src = Xw + static_cast<uint64_t>(m0 + t / 4) * p.n_in + (t % 4) * 8;
+        b_base = p.x_in + static_cast<uint64_t>(worker) * p.stride + o.W1;                // W1 [n_in][n_hid]
+    } else {
+        n_slices = p.batch / kBK;
+        a_src = Xw + static_cast<uint64_t>(wave) * 8 * p.n_in + m0 + lane * AP;
+        b_base = p.dA + static_cast<uint64_t>(worker) * p.batch * p.n_hid;                // dA [batch][n_hid]
+    }
+    auto column = [&](uint32_t c) { return n0 + c; };
+    b_src = b_base + static_cast<uint64_t>(wave) * 8 * ldb + column(lane * BP);
+
+    // forward: two sets of staging registers, global loads run two K slices ahead of their use; backward: one, the
+    // registers belong to the update's loads
+    constexpr int SETS = EPI == kFwd ? 2 : 1;
+    float ra[SETS][AP][8], rb[SETS][BP][8];
+    auto load_cols = [&](auto &r, const float *src, uint64_t ld) {      // 8 rows x (1 or 2) columns
+        constexpr int C = sizeof(r) / sizeof(r[0]);
+        #pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if constexpr (C == 2) {
+                const float2 q = *reinterpret_cast<const float2 *>(src + j * ld);
+                r[0][j] = q.x; r[1][j] = q.y;
+            } else {
+                r[0][j] = src[j * ld];
+            }
+        }
+    };
+    auto load_slice = [&](auto set, uint32_t slice) {
+        constexpr int S = decltype(set)::value % SETS;
+        const uint64_t s = slice0 + slice;
+        if (EPI == kFwd) {
+            #pragma unroll
+            for (int i = 0; i < AP; ++i) {
+                const float *src = a_src + s * kBK + static_cast<uint64_t>(i) * 64 * p.n_in;
+                const f4 lo = *reinterpret_cast<const f4 *>(src), hi = *reinterpret_cast<const f4 *>(src + 4);
+                #pragma unroll
+                for (int j = 0; j < 4; ++j) { ra[S][i][j] = lo[j]; ra[S][i][4 + j] = hi[j]; }
+            }
+        } else {
+            load_cols(ra[S], a_src + s * kBK * p.n_in, p.n_in);
+        }
+        load_cols(rb[S], b_src + s * kBK * ldb, ldb);
+    };
+    float b_scale[BP];
+    auto stage_slice = [&](auto set) {                          // register set s -> LDS buffer s
+        constexpr int S = decltype(set)::value, R = S % SETS;
+        #pragma unroll
+        for (int i = 0; i < AP; ++i) {
+            const uint32_t row = EPI == kFwd ? t / 4 + 64 * i : lane * AP + i, oct = EPI == kFwd ? t % 4 : wave;
+            const uint32_t slot = EPI == kFwd ? ops[S].a.slot_k(row % 32, oct) : ops[S].a.slot_col(row % 32);
+            const Planes s = split8(ra[R][i], kXScale);
+            #pragma unroll
+            for (int pl = 0; pl < 2; ++pl) ops[S].a.q[pl][row / 32][oct][slot] = s.p[pl];
+        }
+        #pragma unroll
+        for (int i = 0; i < BP; ++i) {
+            const uint32_t row = lane * BP + i;
+            const Planes s = split8(rb[R][i], b_scale[i]);
+            #pragma unroll
+            for (int pl = 0; pl < 2; ++pl) ops[S].b.q[pl][row / 32][wave][ops[S].b.slot_col(row % 32)] = s.p[pl];
+        }
+    };
+
+    // The product is formed transposed (W1 columns as the instruction's rows): a lane then holds four consecutive
+    // columns of one row of the result.  The product of the two remainders (2^-22 of the whole at most) is left out;
+    // the small products are added first.
+    const uint32_t wm = wave % 2, wn = wave / 2;                // wave owns rows (BM/2) wm .., columns (BN/2) wn ..
+    f16v acc[MB][NB];
+    auto multiply_slice = [&](auto set) {
+        constexpr int S = decltype(set)::value;
+        #pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            const uint32_t oct = 2 * kb + lane / 32, r = lane % 32;
+            const uint32_t slot_a = EPI == kFwd ? ops[S].a.slot_k(r, oct) : ops[S].a.slot_col(r), slot_b = ops[S].b.slot_col(r);
+            h8 a[2][MB], b[2][NB];
+            #pragma unroll
+            for (int pl = 0; pl < 2; ++pl) {
+                #pragma unroll
+                for (int i = 0; i < MB; ++i) a[pl][i] = __builtin_bit_cast(h8, ops[S].a.q[pl][wm * MB + i][oct][slot_a]);
+                #pragma unroll
+                for (int j = 0; j < NB; ++j) b[pl][j] = __builtin_bit_cast(h8, ops[S].b.q[pl][wn * NB + j][oct][slot_b]);
+            }
+            constexpr int PA[3] = {1, 0, 0}, PB[3] = {0, 1, 0};
+            #pragma unroll
+            for (int q = 0; q < 3; ++q)
+                #pragma unroll
+                for (int i = 0; i < MB; ++i)
+                    #pragma unroll
+                    for (int j = 0; j < NB; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(b[PB[q]][j], a[PA[q]][i], acc[i][j], 0, 0, 0);
+        }
+    };
+
+    // Backward product: the epilogue updates this block's tile of W1 and its momentum.  Vector loads
+    // return in order, so these loads must be the YOUNGEST in flight or every operand slice
+    // behind them would wait for them: they are issued right after the loads of the last K slice
+    // and land under the remaining multiplies.
+    constexpr int EPI_ITERS = (BM * BN / 4) / kGemmThreads, ROWS_PER_PASS = kGemmThreads / (BN / 4);
+    const uint32_t tile_row = t / (BN / 4), tile_col = (t % (BN / 4)) * 4;
+    const uint64_t row_at = o.W1 + static_cast<uint64_t>(m0 + tile_row) * p.n_hid + column(tile_col);
+    const uint64_t tile_at = static_cast<uint64_t>(worker) * p.stride + row_at;
+    f4 x_old[EPI_ITERS], v_old[EPI_ITERS], snap_old[EPI_ITERS];
+    auto prefetch_x = [&]() {
+        #pragma unroll
+        for (int it = 0; it < EPI_ITERS; ++it)
+            x_old[it] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p.x_in + tile_at + static_cast<uint64_t>(it * ROWS_PER_PASS) * p.n_hid));
+    };
+    auto prefetch_v = [&]() {
+        #pragma unroll
+        for (int it = 0; it < EPI_ITERS; ++it) {
+            const uint64_t at = tile_at + static_cast<uint64_t>(it * ROWS_PER_PASS) * p.n_hid;
+            v_old[it] = p.momentum != 0.0f ? __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p.v + at)) : f4{0.f, 0.f, 0.f, 0.f};
+            if (EPI == kBwdTail) snap_old[it] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p.snap + at));
+        }
+    };
+
+    // The scale of the B operand.  Backward: the largest |dA| of the worker (found by the output-layer kernel) goes to
+    // 2^14.  Forward: W1 is the caller's and nothing is known of it, so every column takes its scale from the first 32
+    // of its elements that this block reads (the largest goes to 2^6, a thousandth of the range); a column that later
+    // leaves the range gives an infinity, and the block starts again with the true maximum of its columns at 2^14.
+    using Set0 = std::integral_constant<int, 0>;
+    using Set1 = std::integral_constant<int, 1>;
+    bool finite = true;
+    for (int attempt = 0; attempt < (EPI == kFwd ? 2 : 1); ++attempt) {
+        load_slice(Set0{}, 0);
+        if (SETS == 2) load_slice(Set1{}, 1);
+        if (EPI == kFwd) {
+            #pragma unroll
+            for (int c = 0; c < BP; ++c) {
+                float m = 0.0f;
+                #pragma unroll
+                for (int j = 0; j < 8; ++j) m = fmaxf(m, fabsf(rb[0][c][j]));
+                if (attempt != 0)
+                    for (uint32_t k = slice0 * kBK + wave; k < (slice0 + n_slices) * kBK; k += 4)
+                        m = fmaxf(m, fabsf(b_base[static_cast<uint64_t>(k) * ldb + n0 + lane * BP + c]));
+                col_max[wave][lane * BP + c] = m;
+            }
+            __syncthreads();
+            #pragma unroll
+            for (int c = 0; c < BP; ++c) {
+                const uint32_t n = lane * BP + c;
+                b_scale[c] = scale_to(fmaxf(fmaxf(col_max[0][n], col_max[1][n]), fmaxf(col_max[2][n], col_max[3][n])), attempt == 0 ? 6 : 14);
+            }
+        } else {
+            float m = lane < p.batch / kHeadSamples ? p.dA_max[worker * (p.batch / kHeadSamples) + lane] : 0.0f;
+            #pragma unroll
+            for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+            #pragma unroll
+            for (int c = 0; c < BP; ++c) b_scale[c] = scale_to(m, 14);
+        }
+        #pragma unroll
+        for (int i = 0; i < MB; ++i)
+            #pragma unroll
+            for (int j = 0; j < NB; ++j) acc[i][j] = f16v{0};
+        for (uint32_t s = 0; s + 2 < n_slices; s += 2) {      // one barrier per slice: waves stage one buffer while others multiply the other
+            stage_slice(Set0{});
+            load_slice(Set0{}, s + SETS);
+            __syncthreads();
+            multiply_slice(Set0{});
+            stage_slice(Set1{});
+            load_slice(Set1{}, s + SETS + 1);
+            __syncthreads();
+            multiply_slice(Set1{});
+        }
+        stage_slice(Set0{});
+        if (SETS == 1) load_slice(Set1{}, n_slices - 1);
+        if (EPI != kFwd) prefetch_x();
+        __syncthreads();
+        multiply_slice(Set0{});
+        stage_slice(Set1{});
+        if (EPI != kFwd) prefetch_v();
+        __syncthreads();
+        multiply_slice(Set1{});
+
+        bool mine = true;
+        #pragma unroll
+        for (int i = 0; i < MB; ++i)
+            #pragma unroll
+            for (int j = 0; j < NB; ++j)
+                #pragma unroll
+                for (int r = 0; r < 16; ++r) mine &= fabsf(acc[i][j][r]) < INFINITY;
+        finite = !__syncthreads_or(!mine);
+        if (finite) break;
+    }
+    // undo the scales: lane l, register r of a 32 x 32 block is row l % 32, column 8 (r / 4) + 4 (l / 32) + r % 4
+    if (EPI == kFwd) {
+        if (wave == 0) {
+            #pragma unroll
+            for (int c = 0; c < BP; ++c) col_max[0][lane * BP + c] = inverse_scale(b_scale[c]) * (1.0f / kXScale);
+        }
+        __syncthreads();
+    }
+    #pragma unroll
+    for (int j = 0; j < NB; ++j)
+        #pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float inv = EPI == kFwd ? col_max[0][(wn * NB + j) * 32 + 8 * (r / 4) + 4 * (lane / 32) + r % 4]
+                                          : inverse_scale(b_scale[0]) * (1.0f / kXScale);
+            #pragma unroll
+            for (int i = 0; i < MB; ++i) acc[i][j][r] *= inv;
+        }
+    if (!finite) {
+        // Infinities or NaN among the operands (or a product beyond fp32): with fp32 products throughout, which give
+        // inf, NaN or neither just as the fp32 arithmetic of the rest of the step.  Not a path that a run stays on.
+        const uint32_t K0 = slice0 * kBK, K1 = K0 + n_slices * kBK;
+        #pragma unroll
+        for (int i = 0; i < MB; ++i)
+            #pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const uint32_t m = m0 + (wm * MB + i) * 32 + lane % 32, n = column((wn * NB + j) * 32 + lane % 32);
+                const float *am = EPI == kFwd ? Xw + static_cast<uint64_t>(m) * p.n_in : Xw + m;
+                const uint64_t lda = EPI == kFwd ? 1 : p.n_in;
+                f16v sum = {0};
+                #pragma unroll 1
+                for (uint32_t k = K0 + lane / 32; k < K1; k += 2)
+                    sum = __builtin_amdgcn_mfma_f32_32x32x2f32(b_base[static_cast<uint64_t>(k) * ldb + n], am[k * lda], sum, 0, 0, 0);
+                acc[i][j] = sum;
+            }
+    }
+
+    if (EPI == kFwd) {
+        // raw sums of this K split; bias and relu follow where the splits are added (head_kernel)
+        float *out = (split == 0 ? p.H : p.H_part + static_cast<uint64_t>(split - 1) * p.W * p.batch * p.n_hid) +
+                     (static_cast<uint64_t>(worker) * p.batch + m0) * p.n_hid + n0;
+        #pragma unroll
+        for (int i = 0; i < MB; ++i)
+            #pragma unroll
+            for (int j = 0; j < NB; ++j)
+                #pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    *reinterpret_cast<f4 *>(out + static_cast<uint64_t>((wm * MB + i) * 32 + lane % 32) * p.n_hid + (wn * NB + j) * 32 + 8 * g + 4 * (lane / 32)) =
+                        f4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+        return;
+    }
+    // accumulators -> LDS tile (the operand buffers are dead: the vote above was a barrier), then the update over
+    // the tile in row-major quads: BN/4 lanes cover one row
+    #pragma unroll
+    for (int i = 0; i < MB; ++i)
+        #pragma unroll
+        for (int j = 0; j < NB; ++j)
+            #pragma unroll
+            for (int g = 0; g < 4; ++g)
+                *reinterpret_cast<f4 *>(&Ct[(wm * MB + i) * 32 + lane % 32][(wn * NB + j) * 32 + 8 * g + 4 * (lane / 32)]) =
+                    f4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+    __syncthreads();
+    #pragma unroll
+    for (int it = 0; it < EPI_ITERS; ++it) {
+        const f4 val = *reinterpret_cast<const f4 *>(&Ct[tile_row + it * ROWS_PER_PASS][tile_col]);
+        const uint64_t at = tile_at + static_cast<uint64_t>(it * ROWS_PER_PASS) * p.n_hid;
+        f4 g = val + p.weight_decay * x_old[it];
+        if (p.momentum != 0.0f) {
+            g = p.momentum * v_old[it] + g;
+            __builtin_nontemporal_store(g, reinterpret_cast<f4 *>(p.v + at));
+        }
+        f4 x_new = x_old[it] - p.lr * g;
+        if (EPI == kBwdTail) {       // line 6 of Algorithm 1 on the fresh model, same operation order as the separate kernel
+            const f4 mean = *reinterpret_cast<const f4 *>(p.mean + row_at + static_cast<uint64_t>(it * ROWS_PER_PASS) * p.n_hid);
+            x_new = mean + (x_new - snap_old[it]);
+        }
+        __builtin_nontemporal_store(x_new, reinterpret_cast<f4 *>(p.x_out + at));
+    }
+}
+
+template <int EPI, int BM, int BN>
+void launch_gemm(hipStream_t stream, const MlpParams &p, hipEvent_t start = nullptr, hipEvent_t stop = nullptr)
+{
+    const uint32_t M = (EPI == kFwd) ? p.batch : p.n_in;
+    const dim3 grid(p.n_hid / BN, M / BM, p.W * (EPI == kFwd ? p.fwd_splits : 1u)), block(kGemmThreads);
+    // the events, if any, take the kernel's own start / end timestamps (no marker of their own in the queue)
+    if (start || stop) hipExtLaunchKernelGGL((mlp_gemm_kernel<EPI, BM, BN>), grid, block, 0, stream, start, stop, 0, p);
+    else               hipLaunchKernelGGL((mlp_gemm_kernel<EPI, BM, BN>), grid, block, 0, stream, p);
+}
+
+// The update of the small parameters, instantiated for every supported output width 1..kMaxOut.
+template <int NOUT>
+hipError_t launch_update_for(hipStream_t stream, const MlpParams &p)
+{
     const uint32_t gen_blocks = p.X_next ? (gen_batch_blocks(p) + kUpdateWaves / 4 - 1) / (kUpdateWaves / 4) : 0u;
     const uint64_t update_blocks = (static_cast<uint64_t>((p.n_hid + 63) / 64) + gen_blocks) * p.W;
     if (update_blocks > 0x7fffffffull) return hipErrorInvalidValue;      // a mini-batch of terabytes: its work space was never allocated
@@ -663,10 +797,10 @@ hipError_t launch_heads_for(hipStream_t stream, const MlpParams &p)
 }
 
 template <int... I>
-hipError_t launch_heads(hipStream_t stream, const MlpParams &p, std::integer_sequence<int, I...>)
+hipError_t launch_update(hipStream_t stream, const MlpParams &p, std::integer_sequence<int, I...>)
 {
     hipError_t rc = hipErrorInvalidValue;
-    (void)((p.n_out == static_cast<uint32_t>(I + 1) ? (rc = launch_heads_for<I + 1>(stream, p), true) : false) || ...);
+    (void)((p.n_out == static_cast<uint32_t>(I + 1) ? (rc = launch_update_for<I + 1>(stream, p), true) : false) || ...);
     return rc;
 }
 
@@ -677,10 +811,24 @@ bool mlp_shape_supported(uint32_t n_in, uint32_t n_hid, uint32_t n_out, uint32_t
     return n_in >= static_cast<uint32_t>(kShapeM) && n_in % kShapeM == 0 && n_hid >= static_cast<uint32_t>(kShapeN) &&
            n_hid % kShapeN == 0 && n_out >= 1 && n_out <= static_cast<uint32_t>(kMaxOut) &&
            batch >= static_cast<uint32_t>(kShapeM) && batch % kShapeM == 0 && batch <= 1024 &&
-           static_cast<uint64_t>(n_hid) * head_w2_pitch(n_out) * sizeof(float) <= kHeadLdsBytes;   // W2 lives in LDS
+           static_cast<uint64_t>(n_hid) * (n_out | 1u) <= kMaxHiddenOut;
 }
 
 size_t mlp_dz_pitch() { return kMaxOut; }
+size_t mlp_max_groups(uint32_t batch) { return batch / kHeadSamples; }
+
+// K splits of the forward product: the fewest that give every compute unit a block, at least four K slices each.
+// More of them feed the chip better (W = 16, 3072-1024-10, batch 128, 128 tiles: the product takes 109 us at one
+// split, 67 at two, 62 at four) but every split writes and reads H once more and the round does not gain: 539 us at one
+// split, 537 at two, 548 at four, 559 at six.  W = 6, 1024-2048-10, batch 512, 384 tiles: round 207 us at one split, 216
+// at two, 240 at four.
+uint32_t mlp_forward_splits(uint32_t W, uint32_t n_in, uint32_t n_hid, uint32_t batch, uint32_t compute_units)
+{
+    const uint64_t tiles = static_cast<uint64_t>(W) * (batch / 128) * (n_hid / (n_hid % 128 == 0 ? 128 : 64));
+    const uint64_t want = ((compute_units ? compute_units : 256u) + tiles - 1) / tiles;
+    const uint64_t most = n_in / kBK / 4 < 8u ? n_in / kBK / 4 : 8u;
+    return static_cast<uint32_t>(want < most ? want : most);
+}
 
 hipError_t launch_mlp_step(hipStream_t stream, const MlpParams &p, hipEvent_t start, hipEvent_t stop)
 {
@@ -690,11 +838,18 @@ hipError_t launch_mlp_step(hipStream_t stream, const MlpParams &p, hipEvent_t st
         else       hipLaunchKernelGGL(gen_batch_kernel, dim3(gen_batch_blocks(p), p.W), dim3(256), 0, stream, p);
         start = nullptr;
     }
-    if (wide) launch_gemm<kFwd, 2, 4>(stream, p, start); else launch_gemm<kFwd, 2, 2>(stream, p, start);
-    const hipError_t head_rc = launch_heads(stream, p, std::make_integer_sequence<int, kMaxOut>{});
-    if (head_rc != hipSuccess) return head_rc;
-    if (p.snap) { if (wide) launch_gemm<kBwdTail, 2, 4>(stream, p, nullptr, stop); else launch_gemm<kBwdTail, 2, 2>(stream, p, nullptr, stop); }
-    else        { if (wide) launch_gemm<kBwd, 2, 4>(stream, p, nullptr, stop); else launch_gemm<kBwd, 2, 2>(stream, p, nullptr, stop); }
+    if (wide) launch_gemm<kFwd, 128, 128>(stream, p, start); else launch_gemm<kFwd, 128, 64>(stream, p, start);
+    const size_t head_lds = kHeadSamples * head_pitch(p.n_hid) * sizeof(float);
+    // more than the default 64 KB of dynamic LDS for wide hidden layers
+    static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(head_kernel),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                         kHeadSamples * (kHeadChunk + 4) * sizeof(float));
+    if (lds_ok != hipSuccess) return lds_ok;
+    hipLaunchKernelGGL(head_kernel, dim3(p.batch / kHeadSamples, p.W), dim3(64 * kHeadWaves), head_lds, stream, p);
+    const hipError_t update_rc = launch_update(stream, p, std::make_integer_sequence<int, kMaxOut>{});
+    if (update_rc != hipSuccess) return update_rc;
+    if (p.snap) { if (wide) launch_gemm<kBwdTail, 64, 128>(stream, p, nullptr, stop); else launch_gemm<kBwdTail, 64, 64>(stream, p, nullptr, stop); }
+    else        { if (wide) launch_gemm<kBwd, 64, 128>(stream, p, nullptr, stop); else launch_gemm<kBwd, 64, 64>(stream, p, nullptr, stop); }
     return hipGetLastError();
 }
 

@@ -1,0 +1,107 @@
+"""The perceptron workers' two big contractions (fp16 pairs on the matrix cores at fp32 accuracy) at the sizes and
+values where their splitting, scaling, K splits, tiles and chunks can go wrong, against 64 bits on the device's own
+operands."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1906_12043_amd as P
+import synth_inputs
+from tests.gpu_harness import GpuMlp
+
+pytestmark = pytest.mark.gpu
+HYPER = dict(lr=0.05, momentum=0.9, weight_decay=0.0, seed=0x5EED0009)
+
+
+def theta_of(shape, seed=3):
+    theta = synth_inputs.mlp_he_init(seed, *shape).astype(np.float64)
+    theta += 0.05 * np.random.default_rng(seed).standard_normal(theta.size)
+    return theta.astype(np.float32)
+
+
+def one_step(W, shape, batch, theta):
+    """(work space, v) of one step from v = 0 and weight decay 0: v is then the gradient itself."""
+    g = GpuMlp(W, shape, batch, theta, **HYPER)
+    g.ctx.local_steps(1)
+    ws, v, x = g.workspace(), g.vel(), g.x()
+    g.close()
+    return ws, v, x
+
+
+def bound(K, a, b):
+    """Largest error of an element of a @ b: every operand carries 22 bits (2^-23 each), one of four partial products
+    (2^-22) is left out, and 3 K / 16 sums of 16 products are rounded to fp32, each a few times inside."""
+    return (2.0**-21 + 3 * K / 16 * 4 * 2.0**-24) * (np.abs(a) @ np.abs(b))
+
+
+# one and several K splits; 64- and 128-column tiles; one and several m-tiles; a hidden layer that passes through the
+# output kernel's LDS in two chunks (the second one short); every octet of classes
+@pytest.mark.parametrize("W,shape,batch", [(1, (128, 64, 1), 128), (2, (384, 192, 4), 256), (3, (1024, 128, 5), 128),
+                                           (1, (256, 2176, 10), 384), (2, (640, 320, 16), 1024), (5, (2048, 256, 9), 128)])
+def test_contractions_and_small_gradients_against_64_bits(W, shape, batch):
+    n_in, n_hidden, n_out = shape
+    theta = theta_of(shape)
+    ws, v, _ = one_step(W, shape, batch, theta)
+    th = theta.astype(np.float64)
+    a, b, c = n_in * n_hidden, n_in * n_hidden + n_hidden, n_in * n_hidden + n_hidden + n_hidden * n_out
+    W1, b1, W2 = th[:a].reshape(n_in, n_hidden), th[a:b], th[b:c].reshape(n_hidden, n_out)
+    for i in range(W):
+        X, H, dA, dZ = ws["X"][i], ws["H"][i], ws["dA"][i], ws["dZ"][i]
+        H64 = np.maximum(X @ W1 + b1, 0)
+        assert np.all(np.abs(H - H64) <= bound(n_in, X, W1) + 2.0**-22 * (np.abs(b1) + np.abs(H64)))
+        assert np.all(np.abs(dA - np.where(H > 0, dZ @ W2.T, 0)) <= 2.0**-21 * (np.abs(dZ) @ np.abs(W2.T)))
+        assert np.all(np.abs(v[i, :a].reshape(n_in, n_hidden) - X.T @ dA) <= bound(batch, X.T, dA))
+        small = (batch + 8) * 2.0**-24                       # a chain of fp32 additions over the batch
+        assert np.all(np.abs(v[i, a:b] - dA.sum(0)) <= small * np.abs(dA).sum(0))
+        assert np.all(np.abs(v[i, b:c].reshape(n_hidden, n_out) - H.T @ dZ) <= small * (np.abs(H.T) @ np.abs(dZ)))
+        assert np.all(np.abs(v[i, c:] - dZ.sum(0)) <= small * np.abs(dZ).sum(0))
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e-12, 1e12])
+def test_weights_of_any_magnitude(scale):
+    """A worker's W1 far from 1: the columns' scales follow it (bias 0, so that H shows the product itself)."""
+    W, shape, batch = 1, (512, 128, 3), 128
+    theta = theta_of(shape)
+    a = shape[0] * shape[1]
+    theta[:a] *= np.float32(scale)
+    theta[a:a + shape[1]] = 0
+    ws, _, _ = one_step(W, shape, batch, theta)
+    W1 = theta[:a].astype(np.float64).reshape(shape[0], shape[1])
+    X = ws["X"][0]
+    assert np.all(np.abs(ws["H"][0] - np.maximum(X @ W1, 0)) <= bound(shape[0], X, W1))
+
+
+def test_columns_that_outgrow_their_first_rows():
+    """The scale of a column comes from its first 32 rows; one that then grows a millionfold, one whose first rows are
+    zero and one that is zero throughout must still be exact to the bound (their block starts again with the true
+    maximum)."""
+    W, shape, batch = 1, (512, 256, 3), 128
+    theta = theta_of(shape)
+    a = shape[0] * shape[1]
+    W1 = theta[:a].reshape(shape[0], shape[1])
+    W1[40:, 5] *= 1e6
+    W1[:64, 70] = 0
+    W1[:, 131] = 0
+    theta[a:a + shape[1]] = 0
+    ws, _, _ = one_step(W, shape, batch, theta)
+    X, W64 = ws["X"][0], W1.astype(np.float64)
+    assert np.all(np.abs(ws["H"][0] - np.maximum(X @ W64, 0)) <= bound(shape[0], X, W64))
+
+
+def test_infinities_and_nan_in_the_weights_go_where_fp32_takes_them():
+    """An infinite weight makes its column's pre-activation +-inf by the sign of the input (0 or inf after the relu), a
+    NaN weight makes it NaN (0 after the relu's maximum); the other columns are untouched."""
+    W, shape, batch = 1, (256, 128, 3), 128
+    clean = theta_of(shape)
+    a = shape[0] * shape[1]
+    theta = clean.copy()
+    W1 = theta[:a].reshape(shape[0], shape[1])
+    W1[7, 3], W1[200, 9], W1[100, 64] = np.inf, -np.inf, np.nan
+    ws, _, _ = one_step(W, shape, batch, theta)
+    X, H = ws["X"][0], ws["H"][0]
+    assert np.array_equal(H[:, 3], np.where(X[:, 7] > 0, np.inf, 0)) and np.array_equal(H[:, 9], np.where(X[:, 200] < 0, np.inf, 0))
+    assert np.all(H[:, 64] == 0)
+    rest = [n for n in range(shape[1]) if n not in (3, 9, 64)]
+    C1 = clean[:a].astype(np.float64).reshape(shape[0], shape[1])[:, rest]
+    b1 = clean[a:a + shape[1]].astype(np.float64)[rest]
+    assert np.all(np.abs(H[:, rest] - np.maximum(X @ C1 + b1, 0)) <= bound(shape[0], X, C1) + 2.0**-21 * (1 + np.abs(b1)))
