@@ -487,7 +487,13 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kBwd ? 3 : 2) void mlp_gemm_ke
     {
         const uint32_t total = gridDim.x * gridDim.y * gridDim.z;
         const uint32_t linear = bx + gridDim.x * (by + gridDim.y * bz);
-        if (total % kXcds == 0) {
+        if (EPI == kBwdTail && gridDim.y % kXcds == 0) {
+            // the mean is read by every worker: an XCD owns the same eighth of the rows of W1 for all of them
+            const uint32_t rows = gridDim.y / kXcds, r = linear / kXcds;
+            bx = r % gridDim.x;
+            by = (linear % kXcds) * rows + (r / gridDim.x) % rows;
+            bz = r / (gridDim.x * rows);
+        } else if (total % kXcds == 0) {
             const uint32_t logical = (linear % kXcds) * (total / kXcds) + linear / kXcds;
             bx = logical % gridDim.x;
             by = (logical / gridDim.x) % gridDim.y;
@@ -520,7 +526,16 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kBwd ? 3 : 2) void mlp_gemm_ke
         a_src = Xw + static_cast<uint64_t>(wave) * 8 * p.n_in + m0 + lane * AP;
         b_base = p.dA + static_cast<uint64_t>(worker) * p.batch * p.n_hid;                // dA [batch][n_hid]
     }
-    auto column = [&](uint32_t c) { return n0 + c; };
+    // Columns of this block's tile.  The update streams x, v (and the stored model) in rows of BN floats, and rows that
+    // start off a 128-byte line cost it 40 % (W = 16, 3072-1024-10: the stream alone takes 124 us on lines and 174 us
+    // off them).  A worker's W1 starts wherever its row of the model buffer does, so the columns are counted from the
+    // first one that lies on a line; the last tile wraps around to the columns before it.
+    uint32_t first_col = n0;
+    if (EPI != kFwd) {
+        const uint64_t at = reinterpret_cast<uintptr_t>(p.x_out) / 4 + static_cast<uint64_t>(worker) * p.stride;
+        first_col += static_cast<uint32_t>(-at & 31u);
+    }
+    auto column = [&](uint32_t c) { const uint32_t n = first_col + c; return n < p.n_hid ? n : n - p.n_hid; };
     b_src = b_base + static_cast<uint64_t>(wave) * 8 * ldb + column(lane * BP);
 
     // forward: two sets of staging registers, global loads run two K slices ahead of their use; backward: one, the

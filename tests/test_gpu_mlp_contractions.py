@@ -105,3 +105,31 @@ def test_infinities_and_nan_in_the_weights_go_where_fp32_takes_them():
     C1 = clean[:a].astype(np.float64).reshape(shape[0], shape[1])[:, rest]
     b1 = clean[a:a + shape[1]].astype(np.float64)[rest]
     assert np.all(np.abs(H[:, rest] - np.maximum(X @ C1 + b1, 0)) <= bound(shape[0], X, C1) + 2.0**-21 * (1 + np.abs(b1)))
+
+
+@pytest.mark.parametrize("shape,batch", [((128, 64, 3), 128), ((256, 256, 10), 256)])
+def test_every_row_alignment_gives_the_same_bits(shape, batch):
+    """The update's tiles are counted from the first 128-byte line of a worker's row: whatever the row's offset, and
+    with line 6 inside the last step or alone, the result is the same."""
+    W, theta = 3, theta_of(shape)
+    d = synth_inputs.mlp_param_count(*shape)
+    want = None
+    for extra in (0, 4, 12, 20, 28, 32):
+        stride = (d + 31) // 32 * 32 + extra
+        dev = torch.device("cuda:0")
+        xA = torch.zeros((W, stride), device=dev)
+        xA[:, :d] = torch.from_numpy(theta).to(dev) * torch.tensor([[1.0], [0.5], [2.0]], device=dev)
+        xB, v, mean = torch.zeros_like(xA), torch.zeros_like(xA), torch.zeros(stride, device=dev)
+        s = torch.cuda.Stream(device=dev)
+        torch.cuda.synchronize()
+        ctx = P.Context(W=W, d=d, stride=stride, xA=xA, xB=xB, v=v, mean=mean, grad=P.GRAD_MLP, mlp=(*shape, batch),
+                        compute_stream=s, avg_stream=s, **HYPER)
+        ctx.round(2)
+        ctx.round_fused_tail(2)
+        ctx.sync()
+        live = xA if ctx.live_model() == xA.data_ptr() else xB
+        got = [t[..., :d].cpu() for t in (live, v, mean)]
+        ctx.close()
+        if want is None:
+            want = got
+        assert all(torch.equal(p, q) for p, q in zip(got, want)), extra
