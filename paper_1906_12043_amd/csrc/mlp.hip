@@ -2,17 +2,15 @@
 // perceptron  A = X W1 + b1, H = relu(A), Z = H W2 + b2, loss = mean softmax cross-entropy,
 // on a fresh seeded mini-batch per (worker, step); all W workers advance in the same launches.
 //
-// One local step = four launches on the compute stream (five for a step whose mini-batch no earlier
+// One local step = three launches on the compute stream (four for a step whose mini-batch no earlier
 // step has drawn: gen_batch in front):
 //   gemm<FWD>      X W1, in K splits                           [B x in] x [in x hid]
 //   head           H = relu(X W1 + b1), Z = H W2 + b2, softmax, dZ = (P - onehot)/B, dA = (dZ W2^T) * [H > 0]
 //                  (sixteen samples per block, fp32 matrix instructions)
-//   head_update    dW2 = H^T dZ, db2, db1 = colsum(dA); momentum-SGD update of W2, b2, b1;
-//                  further blocks of the same launch draw the NEXT step's X and labels from the
-//                  counter-based generator into the other of two batch buffers (vector ALU work
-//                  beside a kernel that is a short chain of dependent loads)
 //   gemm<BWD>      dW1 = X^T dA with the momentum-SGD update of W1 fused into the epilogue
-//                  (the 12.6 MB gradient of W1 never goes to memory)   [in x B] x [B x hid]
+//                  (the 12.6 MB gradient of W1 never goes to memory)   [in x B] x [B x hid]; its first blocks
+//                  update W2, b2, b1 (dW2 = H^T dZ, db2, db1 = colsum(dA)), and every block draws a share of the
+//                  NEXT step's X and labels from the counter-based generator into the other of two batch buffers
 //
 // The two big contractions (98 % of the flops) run on the 16-bit matrix instructions at fp32 accuracy: every fp32
 // operand is split into two fp16 values (its leading 11 bits and the remainder's), scaled by a power of two into the
@@ -33,7 +31,6 @@
 #include <hip/hip_ext.h>
 
 #include <type_traits>
-#include <utility>
 
 namespace cocod {
 namespace {
@@ -59,8 +56,9 @@ __host__ __device__ inline Offsets offsets_of(const MlpParams &p)
 }
 
 // g = G + lambda x ; v = mu v + g ; x' = x - gamma v   (same update as the quadratic step)
-__device__ __forceinline__ void sgd_update(const MlpParams &p, uint64_t at, float G)
+__device__ __forceinline__ void sgd_update(const MlpParams &p, uint64_t row, uint64_t e, float G)
 {
+    const uint64_t at = row + e;              // worker's row of the model buffers, element in it
     const float x = p.x_in[at];
     float g = G + p.weight_decay * x;
     if (p.momentum != 0.0f) {
@@ -69,7 +67,7 @@ __device__ __forceinline__ void sgd_update(const MlpParams &p, uint64_t at, floa
         g = v;
     }
     float x_new = x - p.lr * g;
-    if (p.snap) x_new = p.mean[at % p.stride] + (x_new - p.snap[at]);     // line 6 (last step of a round)
+    if (p.snap) x_new = p.mean[e] + (x_new - p.snap[at]);     // line 6 (last step of a round)
     p.x_out[at] = x_new;
 }
 
@@ -131,8 +129,6 @@ constexpr int kHeadWaves = 16;
 constexpr uint32_t kHeadChunk = 2048;  // hidden units held in LDS at a time (132 KB); more pass through it chunk by chunk
 constexpr int kHeadGroup = 4;          // 1 KiB pieces of a row, and
 constexpr int kHeadTerms = 4;          //   terms of H (K splits beside the first, bias) that are requested together
-constexpr int kUpdateWaves = 8;                 // head_update: waves per block, each sums an eighth of the batch
-constexpr int kDzGroup = 16, kDzBatch = 16;     //   samples per staged group of dZ rows, and per batch of H / dA loads
 __host__ __device__ inline uint32_t head_pitch(uint32_t n_hid) { return (n_hid < kHeadChunk ? n_hid : kHeadChunk) + 4; }
 
 __global__ __launch_bounds__(64 * kHeadWaves) void head_kernel(const MlpParams p)
@@ -304,115 +300,82 @@ __global__ __launch_bounds__(64 * kHeadWaves) void head_kernel(const MlpParams p
     }
 }
 
-// Gradients of the small parameters and their update.  A block owns 64 hidden units (row n of W2 and
-// b1[n]); its eight waves each sum an eighth of the batch and the partial sums meet in LDS in a fixed
-// order.  Block 0 of a worker also owns b2 and the alignment pads.
-template <int NOUT>
-__global__ __launch_bounds__(64 * kUpdateWaves) void head_update_kernel(const MlpParams p)
+// Gradients of the small parameters and their update, as blocks of the backward product's launch (in a launch of their
+// own they were a chain of memory round trips of 16 us on one block per compute unit; beside the update of W1 they are
+// not seen).  A block owns 64 hidden units (rows of W2, and b1): dW2 = H^T dZ on the fp32 matrix instruction 16x16x4,
+// each of the four waves over a quarter of the batch, db1 = colsum(dA); the waves' sums meet in LDS in a fixed order.
+// Block 0 of a worker also owns b2 and the alignment pads.
+constexpr uint32_t kSmallUnits = 64;
+constexpr int kSmallWaves = 4, kSmallSteps = 4;                // waves per block; matrix instructions' worth of samples requested together
+struct SmallUpdateLds { float part[kSmallWaves][kSmallUnits][kMaxOut + 1]; float b2[16][kMaxOut]; };
+__host__ __device__ inline uint32_t small_blocks(const MlpParams &p) { return p.n_hid / kSmallUnits * p.W; }
+
+__device__ __forceinline__ void small_update_block(const MlpParams &p, uint32_t block, SmallUpdateLds &lds)
 {
-    __shared__ float part[kUpdateWaves][64][NOUT + 1];
-    __shared__ __attribute__((aligned(16))) float dzs[kUpdateWaves][kDzGroup][kMaxOut];     // per wave: dZ rows of the current group
-    // The first W * ceil(n_hid / 64) blocks own hidden units.  The blocks behind them draw the NEXT local
-    // step's mini-batch into the other batch buffer: the owners are a short chain of dependent loads on one
-    // block per compute unit, and the generator is pure vector arithmetic that fills the rest of the chip
-    // meanwhile.  Blocks are dispatched in the order of their index: the owners, whose chain decides when
-    // the kernel ends, all start at once.
-    const uint32_t own_blocks = (p.n_hid + 63) / 64;
-    if (blockIdx.x >= own_blocks * p.W) {
-        constexpr uint32_t GROUPS = kUpdateWaves / 4;                // 256-thread generator groups per block
-        const uint32_t id = blockIdx.x - own_blocks * p.W, per_worker = (gen_batch_blocks(p) + GROUPS - 1) / GROUPS;
-        const uint32_t step = p.step_base ? *p.step_base + p.step : p.step;
-        gen_batch_block(p, (id % per_worker) * GROUPS + threadIdx.x / 256, threadIdx.x % 256, id / per_worker, step + 1, p.X_next, p.y_next);
-        return;
-    }
-    const uint32_t worker = blockIdx.x / own_blocks, own = blockIdx.x % own_blocks;
-    const uint32_t u = threadIdx.x % 64, slice = threadIdx.x / 64;
-    const uint32_t n = own * 64 + u;
+    const uint32_t own_blocks = p.n_hid / kSmallUnits;
+    const uint32_t worker = block / own_blocks, own = block % own_blocks;
+    const uint32_t t = threadIdx.x, wave = t / 64, lane = t % 64, s16 = lane % 16, g = lane / 16;
     const Offsets o = offsets_of(p);
     const uint64_t base = static_cast<uint64_t>(worker) * p.stride;
-    float gw[NOUT];
-    #pragma unroll
-    for (int c = 0; c < NOUT; ++c) gw[c] = 0.0f;
-    float gb = 0.0f;
-    {
-        // The wave's eighth of the batch in groups of 16 samples.  Every lane needs the same dZ rows: the wave
-        // fetches a group's rows once (one quad per lane) into its own piece of LDS and reads them back as
-        // broadcasts, instead of 10 same-address loads per sample and lane.
-        const uint32_t per = p.batch / kUpdateWaves;                 // a multiple of 16 by the shape contract
-        const bool mine = n < p.n_hid;
-        for (uint32_t g0 = slice * per; g0 < (slice + 1) * per; g0 += kDzGroup) {
-            const float *dz_rows = p.dZ + (static_cast<uint64_t>(worker) * p.batch + g0) * kMaxOut;
-            static_assert(kDzGroup * kMaxOut == 4 * 64, "one quad of the group's dZ rows per lane");
-            const f4 q0 = *reinterpret_cast<const f4 *>(dz_rows + 4 * u);
+    const uint32_t per = p.batch / kSmallWaves;                // samples of a wave: a multiple of 32
+    const uint64_t sample = static_cast<uint64_t>(worker) * p.batch + wave * per + g;
+    const float *H = p.H + sample * p.n_hid + own * kSmallUnits + s16, *dA = p.dA + sample * p.n_hid + own * kSmallUnits + s16;
+    const float *dZ = p.dZ + sample * kMaxOut + s16;
+    f4v d[4] = {};
+    float gb[4] = {0.f, 0.f, 0.f, 0.f};
+    for (uint32_t s0 = 0; s0 < per; s0 += 4 * kSmallSteps) {
+        float h[kSmallSteps][4], a[kSmallSteps][4], z[kSmallSteps];
+        #pragma unroll
+        for (int s = 0; s < kSmallSteps; ++s) {
+            const uint64_t at = s0 + 4 * s;
+            z[s] = dZ[at * kMaxOut];
             #pragma unroll
-            for (int half = 0; half < kDzGroup / kDzBatch; ++half) {
-                float hv[kDzBatch], da[kDzBatch];                    // the batch's loads are all in flight together
-                #pragma unroll
-                for (int j = 0; j < kDzBatch; ++j) {
-                    const uint64_t sample = static_cast<uint64_t>(worker) * p.batch + g0 + half * kDzBatch + j;
-                    hv[j] = mine ? p.H[sample * p.n_hid + n] : 0.0f;
-                    da[j] = mine ? p.dA[sample * p.n_hid + n] : 0.0f;
-                }
-                if (half == 0) {                                     // rows of the group -> LDS (this wave's piece only)
-                    *reinterpret_cast<f4 *>(&dzs[slice][0][0] + 4 * u) = q0;
-                }
-                #pragma unroll
-                for (int j = 0; j < kDzBatch; ++j) {
-                    gb += da[j];
-                    #pragma unroll
-                    for (int c = 0; c < NOUT; ++c) gw[c] += hv[j] * dzs[slice][half * kDzBatch + j][c];
-                }
-            }
+            for (int b = 0; b < 4; ++b) { h[s][b] = H[at * p.n_hid + 16 * b]; a[s][b] = dA[at * p.n_hid + 16 * b]; }
         }
+        #pragma unroll
+        for (int s = 0; s < kSmallSteps; ++s)
+            #pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                d[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(h[s][b], z[s], d[b], 0, 0, 0);
+                gb[b] += a[s][b];
+            }
     }
     #pragma unroll
-    for (int c = 0; c < NOUT; ++c) part[slice][u][c] = gw[c];
-    part[slice][u][NOUT] = gb;
+    for (int b = 0; b < 4; ++b) {
+        #pragma unroll
+        for (int r = 0; r < 4; ++r) lds.part[wave][16 * b + 4 * g + r][s16] = d[b][r];
+        gb[b] += __shfl_xor(gb[b], 16, 64);
+        gb[b] += __shfl_xor(gb[b], 32, 64);
+        if (g == 0) lds.part[wave][16 * b + s16][kMaxOut] = gb[b];
+    }
+    if (own == 0) {                                            // db2[c]: thread (r, c) takes the samples r, r + 16, ...
+        float sum = 0.0f;
+        for (uint32_t b = t / kMaxOut; b < p.batch; b += 16) sum += p.dZ[(static_cast<uint64_t>(worker) * p.batch + b) * kMaxOut + t % kMaxOut];
+        lds.b2[t / kMaxOut][t % kMaxOut] = sum;
+    }
     __syncthreads();
-    if (slice == 0 && n < p.n_hid) {
-        // row n of W2 and b1[n]: all old values first (independent loads), then the updates
-        uint64_t at[NOUT + 1];
-        float xo[NOUT + 1], vo[NOUT + 1];
+    for (uint32_t e = t; e < kSmallUnits * p.n_out; e += 64 * kSmallWaves) {        // this block's rows of W2: contiguous
+        const uint32_t n = e / p.n_out, c = e % p.n_out;
+        float G = lds.part[0][n][c];
         #pragma unroll
-        for (int c = 0; c <= NOUT; ++c) {
-            at[c] = c == NOUT ? base + o.b1 + n : base + o.W2 + static_cast<uint64_t>(n) * NOUT + c;
-            xo[c] = p.x_in[at[c]];
-            vo[c] = p.momentum != 0.0f ? p.v[at[c]] : 0.0f;
-        }
-        #pragma unroll
-        for (int c = 0; c <= NOUT; ++c) {
-            {
-                float G = part[0][u][c];
-                #pragma unroll
-                for (int w = 1; w < kUpdateWaves; ++w) G += part[w][u][c];
-                float g = G + p.weight_decay * xo[c];
-                if (p.momentum != 0.0f) {
-                    g = p.momentum * vo[c] + g;
-                    p.v[at[c]] = g;
-                }
-                float x_new = xo[c] - p.lr * g;
-                if (p.snap) x_new = p.mean[at[c] - base] + (x_new - p.snap[at[c]]);   // line 6 (last step of a round)
-                p.x_out[at[c]] = x_new;
-            }
-        }
+        for (int w = 1; w < kSmallWaves; ++w) G += lds.part[w][n][c];
+        sgd_update(p, base, o.W2 + static_cast<uint64_t>(own) * kSmallUnits * p.n_out + e, G);
     }
-    if (own == 0 && slice == 1) {
-        // db2[c] = sum_b dZ[b][c]: lanes take the samples 64 apart, then a butterfly over the wave
-        float col[NOUT];
+    if (t < kSmallUnits) {
+        float G = lds.part[0][t][kMaxOut];
         #pragma unroll
-        for (int c = 0; c < NOUT; ++c) col[c] = 0.0f;
-        for (uint32_t b = u; b < p.batch; b += 64) {
-            const float *dz = p.dZ + (static_cast<uint64_t>(worker) * p.batch + b) * kMaxOut;
+        for (int w = 1; w < kSmallWaves; ++w) G += lds.part[w][t][kMaxOut];
+        sgd_update(p, base, o.b1 + own * kSmallUnits + t, G);
+    }
+    if (own == 0 && wave == kSmallWaves - 1) {
+        if (lane < p.n_out) {
+            float G = lds.b2[0][lane];
             #pragma unroll
-            for (int c = 0; c < NOUT; ++c) col[c] += dz[c];
+            for (int r = 1; r < 16; ++r) G += lds.b2[r][lane];
+            sgd_update(p, base, o.b2 + lane, G);
         }
-        #pragma unroll
-        for (int c = 0; c < NOUT; ++c) {
-            const float g = wave_sum(col[c]);
-            if (u == static_cast<uint32_t>(c)) sgd_update(p, base + o.b2 + u, g);
-        }
-        const uint64_t d = o.b2 + NOUT;                       // pads after the last parameter travel along
-        if (p.x_out != p.x_in && u < ((d + 3) & ~3ull) - d) p.x_out[base + d + u] = p.x_in[base + d + u];
+        const uint64_t d_end = o.b2 + p.n_out;                // pads after the last parameter travel along
+        if (p.x_out != p.x_in && lane < ((d_end + 3) & ~3ull) - d_end) p.x_out[base + d_end + lane] = p.x_in[base + d_end + lane];
     }
 }
 
@@ -474,6 +437,7 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kBwd ? 3 : 2) void mlp_gemm_ke
     constexpr int CPITCH = BN + 4;
     struct Operands { OperandTile<BM> a; OperandTile<BN> b; };
     constexpr int OPERANDS = 2 * sizeof(Operands), TILE = EPI == kFwd ? 0 : BM * CPITCH * 4;
+    static_assert(EPI == kFwd || OPERANDS >= static_cast<int>(sizeof(SmallUpdateLds)), "the small update's sums fit");
     __shared__ __attribute__((aligned(16))) unsigned char smem[OPERANDS > TILE ? OPERANDS : TILE];
     __shared__ float col_max[EPI == kFwd ? 4 : 1][EPI == kFwd ? BN : 1];
     Operands *ops = reinterpret_cast<Operands *>(smem);                                            // two buffers
@@ -483,24 +447,30 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kBwd ? 3 : 2) void mlp_gemm_ke
     // that every XCD owns a CONTIGUOUS run of tiles (n fastest, then m, then K split, then worker): the tiles that
     // share an operand panel (all n-tiles of an m-tile share its X panel, all m-tiles of an n-tile its
     // W1 / dA panel) then meet in one L2 instead of fetching the panel once per XCD.
-    uint32_t bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
-    {
-        const uint32_t total = gridDim.x * gridDim.y * gridDim.z;
-        const uint32_t linear = bx + gridDim.x * (by + gridDim.y * bz);
-        if (EPI == kBwdTail && gridDim.y % kXcds == 0) {
-            // the mean is read by every worker: an XCD owns the same eighth of the rows of W1 for all of them
-            const uint32_t rows = gridDim.y / kXcds, r = linear / kXcds;
-            bx = r % gridDim.x;
-            by = (linear % kXcds) * rows + (r / gridDim.x) % rows;
-            bz = r / (gridDim.x * rows);
-        } else if (total % kXcds == 0) {
-            const uint32_t logical = (linear % kXcds) * (total / kXcds) + linear / kXcds;
-            bx = logical % gridDim.x;
-            by = (logical / gridDim.x) % gridDim.y;
-            bz = logical / (gridDim.x * gridDim.y);
-        }
-    }
     const uint32_t splits = EPI == kFwd ? p.fwd_splits : 1u;
+    const uint32_t nx = p.n_hid / BN, ny = (EPI == kFwd ? p.batch : p.n_in) / BM, total = nx * ny * p.W * splits;
+    uint32_t linear = blockIdx.x;
+    if (EPI != kFwd) {                                         // the launch's first blocks update the small parameters
+        if (linear < small_blocks(p)) {
+            small_update_block(p, linear, *reinterpret_cast<SmallUpdateLds *>(smem));
+            return;
+        }
+        linear -= small_blocks(p);
+    }
+    uint32_t bx, by, bz;
+    if (EPI == kBwdTail && ny % kXcds == 0) {
+        // the mean is read by every worker: an XCD owns the same eighth of the rows of W1 for all of them
+        // (222 -> 206 us at W = 16, 3072-1024-10)
+        const uint32_t rows = ny / kXcds, r = linear / kXcds;
+        bx = r % nx;
+        by = (linear % kXcds) * rows + (r / nx) % rows;
+        bz = r / (nx * rows);
+    } else {
+        const uint32_t logical = total % kXcds == 0 ? (linear % kXcds) * (total / kXcds) + linear / kXcds : linear;
+        bx = logical % nx;
+        by = (logical / nx) % ny;
+        bz = logical / (nx * ny);
+    }
     const uint32_t worker = bz / splits, split = bz % splits;
     const uint32_t m0 = by * BM, n0 = bx * BN;
     const Offsets o = offsets_of(p);
@@ -653,6 +623,13 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kBwd ? 3 : 2) void mlp_gemm_ke
     for (int attempt = 0; attempt < (EPI == kFwd ? 2 : 1); ++attempt) {
         load_slice(Set0{}, 0);
         if (SETS == 2) load_slice(Set1{}, 1);
+        if (EPI != kFwd && p.X_next) {
+            // The NEXT local step's mini-batch is drawn here, a share per block, into the other batch buffer: vector
+            // arithmetic under the latency of the first operand loads.
+            const uint32_t step = p.step_base ? *p.step_base + p.step : p.step, per_worker = gen_batch_blocks(p);
+            for (uint32_t id = linear; id < per_worker * p.W; id += total)
+                gen_batch_block(p, id % per_worker, t, id / per_worker, step + 1, p.X_next, p.y_next);
+        }
         if (EPI == kFwd) {
             #pragma unroll
             for (int c = 0; c < BP; ++c) {
@@ -794,29 +771,10 @@ template <int EPI, int BM, int BN>
 void launch_gemm(hipStream_t stream, const MlpParams &p, hipEvent_t start = nullptr, hipEvent_t stop = nullptr)
 {
     const uint32_t M = (EPI == kFwd) ? p.batch : p.n_in;
-    const dim3 grid(p.n_hid / BN, M / BM, p.W * (EPI == kFwd ? p.fwd_splits : 1u)), block(kGemmThreads);
+    const dim3 grid(p.n_hid / BN * (M / BM) * p.W * (EPI == kFwd ? p.fwd_splits : 1u) + (EPI == kFwd ? 0u : small_blocks(p))), block(kGemmThreads);
     // the events, if any, take the kernel's own start / end timestamps (no marker of their own in the queue)
     if (start || stop) hipExtLaunchKernelGGL((mlp_gemm_kernel<EPI, BM, BN>), grid, block, 0, stream, start, stop, 0, p);
     else               hipLaunchKernelGGL((mlp_gemm_kernel<EPI, BM, BN>), grid, block, 0, stream, p);
-}
-
-// The update of the small parameters, instantiated for every supported output width 1..kMaxOut.
-template <int NOUT>
-hipError_t launch_update_for(hipStream_t stream, const MlpParams &p)
-{
-    const uint32_t gen_blocks = p.X_next ? (gen_batch_blocks(p) + kUpdateWaves / 4 - 1) / (kUpdateWaves / 4) : 0u;
-    const uint64_t update_blocks = (static_cast<uint64_t>((p.n_hid + 63) / 64) + gen_blocks) * p.W;
-    if (update_blocks > 0x7fffffffull) return hipErrorInvalidValue;      // a mini-batch of terabytes: its work space was never allocated
-    hipLaunchKernelGGL(head_update_kernel<NOUT>, dim3(static_cast<uint32_t>(update_blocks)), dim3(64 * kUpdateWaves), 0, stream, p);
-    return hipSuccess;
-}
-
-template <int... I>
-hipError_t launch_update(hipStream_t stream, const MlpParams &p, std::integer_sequence<int, I...>)
-{
-    hipError_t rc = hipErrorInvalidValue;
-    (void)((p.n_out == static_cast<uint32_t>(I + 1) ? (rc = launch_update_for<I + 1>(stream, p), true) : false) || ...);
-    return rc;
 }
 
 }  // namespace
@@ -861,8 +819,6 @@ hipError_t launch_mlp_step(hipStream_t stream, const MlpParams &p, hipEvent_t st
                                                          kHeadSamples * (kHeadChunk + 4) * sizeof(float));
     if (lds_ok != hipSuccess) return lds_ok;
     hipLaunchKernelGGL(head_kernel, dim3(p.batch / kHeadSamples, p.W), dim3(64 * kHeadWaves), head_lds, stream, p);
-    const hipError_t update_rc = launch_update(stream, p, std::make_integer_sequence<int, kMaxOut>{});
-    if (update_rc != hipSuccess) return update_rc;
     if (p.snap) { if (wide) launch_gemm<kBwdTail, 64, 128>(stream, p, nullptr, stop); else launch_gemm<kBwdTail, 64, 64>(stream, p, nullptr, stop); }
     else        { if (wide) launch_gemm<kBwd, 64, 128>(stream, p, nullptr, stop); else launch_gemm<kBwd, 64, 64>(stream, p, nullptr, stop); }
     return hipGetLastError();
