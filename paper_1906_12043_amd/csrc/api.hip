@@ -351,7 +351,9 @@ int cocod_create(const cocod_config *cfg, cocod_ctx **out)
             Chunk ck{};
             ck.mem_quad = static_cast<uint32_t>((ctx->tensor_offset[t] + off) / 4);
             ck.glob_off = global + off;
-            ck.n = static_cast<uint32_t>(left < span ? left : span);
+            ck.n = static_cast<uint16_t>(left < span ? left : span);
+            ck.after = static_cast<uint8_t>(left - ck.n < cocod::kLineElems ? left - ck.n : cocod::kLineElems);
+            ck.first = off == 0;
             ctx->chunks.push_back(ck);
         }
         global += ctx->tensor_numel[t];

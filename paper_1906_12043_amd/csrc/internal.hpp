@@ -9,6 +9,7 @@ namespace cocod {
 // consecutive elements of ONE tensor of one worker, one 16-byte quad per thread.
 constexpr uint32_t kStepThreads = 256;
 constexpr uint32_t kChunkElems = kStepThreads * 4;
+constexpr uint32_t kLineElems = 32;      // fp32 elements of a 128-byte line
 
 // Stream tags: fourth counter word of the generator, keeps random streams disjoint.
 enum : uint32_t { kTagNoise = 0, kTagH = 1, kTagC = 2, kTagMlpX = 4, kTagMlpY = 5 };
@@ -16,7 +17,9 @@ enum : uint32_t { kTagNoise = 0, kTagH = 1, kTagC = 2, kTagMlpX = 4, kTagMlpY = 
 struct Chunk {
     uint64_t glob_off;  // unpadded global parameter index of the chunk's first element
     uint32_t mem_quad;  // 16-byte quad offset inside a worker's padded row (element offset / 4)
-    uint32_t n;         // real elements in the chunk (1 .. kChunkElems)
+    uint16_t n;         // real elements in the chunk (1 .. kChunkElems)
+    uint8_t after;      // elements of the same tensor behind the chunk, at most kLineElems
+    uint8_t first;      // 1: the tensor's first chunk
 };
 static_assert(sizeof(Chunk) == 16, "one 16-byte scalar load per block");
 

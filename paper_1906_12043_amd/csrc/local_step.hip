@@ -106,14 +106,34 @@ __global__ __launch_bounds__(64 * NWMAX) void local_step_kernel(const StepParams
     const Chunk ck = p.table[chunk_id];
     const uint32_t first = part * TILE_ELEMS;                 // first element of the tile inside its chunk
     if (first >= ck.n) return;                                // block-uniform: the tensor ends before this tile
-    const uint32_t n = ck.n - first < TILE_ELEMS ? ck.n - first : TILE_ELEMS;     // real elements in the tile
-    const uint32_t n4 = (n + 3u) & ~3u;                       // whole quads: a tensor's tail quad ends in pads
-    const uint32_t bytes = n4 * 4u;
-    const uint64_t col = static_cast<uint64_t>(ck.mem_quad) * 4 + first;
-    const uint32_t shift = static_cast<uint32_t>(ck.glob_off & 3u);
-    const uint64_t q0 = ((ck.glob_off + first) >> 2);         // generator block of lane 0's first quad
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const uint32_t step = p.step_base ? *p.step_base + p.step : p.step;      // wave-uniform
+
+    // The tile: elements [begin, begin + n) counted from its chunk.
+    // Rows off the 128-byte lines: a worker's row starts on any 16-byte boundary (the stride is the caller's), and a
+    // wave that streams 1 KiB off the lines leaves half a line at both ends (plain step, W = 21, d = 4.0 M, rows 48 bytes
+    // off: 390 us = 5.2 TB/s, with this rule 312 us = 6.45 TB/s, rows on lines 308 us).  Where every wave has a row of its own its tiles are therefore moved up to the next line of that row,
+    // `lead` elements; the tensor's first tile also serves the elements before it, in a second pass.
+    uint32_t begin = first, n = ck.n - first < TILE_ELEMS ? ck.n - first : TILE_ELEMS, lead = 0;
+    if (!FORMS_MEAN) {
+        const uint32_t row_worker = group * nw + wave;
+        const uint64_t at = reinterpret_cast<uintptr_t>(p.x_out) / 4 + static_cast<uint64_t>(row_worker) * p.stride;
+        lead = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(-at) & (kLineElems - 1u));
+        begin = first + lead;
+        const uint32_t end = ck.n + ck.after, left = end > begin ? end - begin : 0u;
+        n = left < TILE_ELEMS ? left : TILE_ELEMS;
+        if (n == 0 && !(ck.first && first == 0)) return;      // wave-uniform, no barrier in these modes
+    }
+    uint32_t n4, bytes, shift;
+    uint64_t col, q0;
+    auto set_tile = [&]() {
+        n4 = (n + 3u) & ~3u;                                  // whole quads: a tensor's tail quad ends in pads
+        bytes = n4 * 4u;
+        col = static_cast<uint64_t>(ck.mem_quad) * 4 + begin;
+        shift = static_cast<uint32_t>(ck.glob_off & 3u);
+        q0 = ((ck.glob_off + begin) >> 2);                    // generator block of lane 0's first quad
+    };
+    set_tile();
 
     struct Row { f4 v[Q], h[Q], c[Q]; };                      // what a step needs beside the model itself
     auto load_row = [&](uint32_t w) {
@@ -175,47 +195,60 @@ __global__ __launch_bounds__(64 * NWMAX) void local_step_kernel(const StepParams
     if (!FORMS_MEAN) {
         const uint32_t w = group * nw + wave;
         if (w >= p.W) return;                              // no barrier in these modes
-        f4 x0[Q], snap[Q], m[Q];
-        load_x(x0, w);
-        if constexpr (MODE == kModeLine6) {                // line 6 alone, in place: x = mean + (x - stored model)
-            const uint64_t row = static_cast<uint64_t>(w) * p.stride + col;
-            const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.snap + row, bytes), rm = make_rsrc(p.mean + col, bytes);
-            const __amdgpu_buffer_rsrc_t rx_out = make_rsrc(p.x_out + row, bytes);
-            #pragma unroll
-            for (int u = 0; u < Q; ++u) {
-                const uint32_t e = (64u * u + lane) * 4u, off = e * 4u;
-                snap[u] = load_quad(rs, off);
-                m[u] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rm, static_cast<int>(off), 0, 0));
-            }
-            #pragma unroll
-            for (int u = 0; u < Q; ++u) {
-                const uint32_t e = (64u * u + lane) * 4u;
-                f4 x = line6_quad(m[u], x0[u], snap[u]);
-                if (e + 4 > n && e < n) {                  // tensor tail: alignment pads keep their old values
-                    const uint32_t keep = n - e;
-                    if (keep < 2) x.y = x0[u].y;
-                    if (keep < 3) x.z = x0[u].z;
-                    x.w = x0[u].w;
+        auto serve = [&]() {
+            f4 x0[Q], snap[Q], m[Q];
+            load_x(x0, w);
+            if constexpr (MODE == kModeLine6) {                // line 6 alone, in place: x = mean + (x - stored model)
+                const uint64_t row = static_cast<uint64_t>(w) * p.stride + col;
+                const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.snap + row, bytes), rm = make_rsrc(p.mean + col, bytes);
+                const __amdgpu_buffer_rsrc_t rx_out = make_rsrc(p.x_out + row, bytes);
+                #pragma unroll
+                for (int u = 0; u < Q; ++u) {
+                    const uint32_t e = (64u * u + lane) * 4u, off = e * 4u;
+                    snap[u] = load_quad(rs, off);
+                    m[u] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rm, static_cast<int>(off), 0, 0));
                 }
-                store_quad(rx_out, e * 4u, x);
+                #pragma unroll
+                for (int u = 0; u < Q; ++u) {
+                    const uint32_t e = (64u * u + lane) * 4u;
+                    f4 x = line6_quad(m[u], x0[u], snap[u]);
+                    if (e + 4 > n && e < n) {                  // tensor tail: alignment pads keep their old values
+                        const uint32_t keep = n - e;
+                        if (keep < 2) x.y = x0[u].y;
+                        if (keep < 3) x.z = x0[u].z;
+                        x.w = x0[u].w;
+                    }
+                    store_quad(rx_out, e * 4u, x);
+                }
+            } else {
+                const Row r = load_row(w);
+                #pragma unroll
+                for (int u = 0; u < Q; ++u) { snap[u] = x0[u]; m[u] = f4{0.f, 0.f, 0.f, 0.f}; }
+                if (MODE == kModeTail) {
+                    const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.snap + static_cast<uint64_t>(w) * p.stride + col, bytes);
+                    #pragma unroll
+                    for (int u = 0; u < Q; ++u) snap[u] = load_quad(rs, (64u * u + lane) * 16u);
+                }
+                if (LINE6) {                                   // shared by the block's waves: ordinary cached load
+                    const __amdgpu_buffer_rsrc_t rm = make_rsrc(p.mean + col, bytes);
+                    #pragma unroll
+                    for (int u = 0; u < Q; ++u)
+                        m[u] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rm, static_cast<int>((64u * u + lane) * 16u), 0, 0));
+                }
+                step_row(w, x0, r, snap, m);
             }
-            return;
+        };
+        if (ck.first && first == 0 && lead != 0) {         // the elements before the tensor's first line
+            const uint32_t whole = n;
+            begin = 0;
+            n = ck.n < lead ? ck.n : lead;
+            set_tile();
+            serve();
+            begin = lead;
+            n = whole;
+            set_tile();
         }
-        const Row r = load_row(w);
-        #pragma unroll
-        for (int u = 0; u < Q; ++u) { snap[u] = x0[u]; m[u] = f4{0.f, 0.f, 0.f, 0.f}; }
-        if (MODE == kModeTail) {
-            const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.snap + static_cast<uint64_t>(w) * p.stride + col, bytes);
-            #pragma unroll
-            for (int u = 0; u < Q; ++u) snap[u] = load_quad(rs, (64u * u + lane) * 16u);
-        }
-        if (LINE6) {                                       // shared by the block's waves: ordinary cached load
-            const __amdgpu_buffer_rsrc_t rm = make_rsrc(p.mean + col, bytes);
-            #pragma unroll
-            for (int u = 0; u < Q; ++u)
-                m[u] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rm, static_cast<int>((64u * u + lane) * 16u), 0, 0));
-        }
-        step_row(w, x0, r, snap, m);
+        if (n != 0) serve();
         return;
     }
 

@@ -1,0 +1,66 @@
+"""The step kernel moves a worker's tiles to the 128-byte lines of its row: for every distance of the rows from a line,
+every kind of step and every gradient the bits are those of rows that lie on lines, and pads stay untouched."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1906_12043_amd as P
+from tests.gpu_harness import packed_positions
+
+pytestmark = pytest.mark.gpu
+W = 3
+HYPER = dict(lr=0.05, weight_decay=5e-4, noise_sigma=0.01, seed=77)
+
+
+def rounds(sizes, extra, momentum, kind):
+    """(x, v, mean) of the real parameters after rounds of every kind; models, h, c drawn by parameter index."""
+    d = sum(sizes)
+    packed = sizes if len(sizes) > 1 else None
+    padded, _, _ = P.plan_layout(d, packed)
+    stride = (padded + 31) // 32 * 32 + extra
+    dev = torch.device("cuda:0")
+    pos = torch.from_numpy(packed_positions(packed, d)).to(dev)
+    rng = np.random.default_rng(d)
+
+    def buf(scale, fill=7.0):
+        t = torch.full((W, stride), fill, device=dev)
+        t[:, pos] = torch.from_numpy((scale * rng.standard_normal((W, d))).astype(np.float32)).to(dev)
+        return t
+    xA, v, h, c = buf(0.5), buf(0.1), buf(1.0), buf(1.0)
+    xB, mean = torch.full_like(xA, 7.0), torch.zeros(stride, device=dev)
+    g16 = h.to(torch.bfloat16)
+    s = torch.cuda.Stream(device=dev)
+    torch.cuda.synchronize()
+    ctx = P.Context(W=W, d=d, stride=stride, xA=xA, xB=xB, v=v if momentum else None, mean=mean, h=h, c=c, momentum=momentum,
+                    tensor_numel=packed, compute_stream=s, avg_stream=s, **HYPER)
+    if kind == "round":
+        ctx.round(2)                                 # plain steps, line 6 alone
+        ctx.round_fused_tail(2)                      # line 6 inside the last step
+        ctx.round_fused_tail(1)                      # line 6 inside the only step
+    else:
+        step, g = (ctx.external_step, h) if kind == "fp32" else (ctx.external_step_bf16, g16)
+        for k in (2, 1):
+            ctx.average_begin()
+            for i in range(k):
+                step(g, close_round=(i == k - 1))
+    ctx.sync()
+    live = xA if ctx.live_model() == xA.data_ptr() else xB
+    real = torch.zeros(stride, dtype=torch.bool, device=dev)
+    real[pos] = True
+    tail_quad = torch.zeros(stride, dtype=torch.bool, device=dev)       # pads that share a tensor's last quad travel along
+    tail_quad[pos // 4 * 4 + 3] = tail_quad[pos // 4 * 4 + 2] = tail_quad[pos // 4 * 4 + 1] = True
+    for t in (xA, xB, v):
+        assert bool((t[:, ~real & ~tail_quad] == 7.0).all())
+    out = [live[:, pos].cpu(), v[:, pos].cpu(), mean[pos].cpu()]
+    ctx.close()
+    return out
+
+
+@pytest.mark.parametrize("sizes", [[1], [27], [30], [255], [257], [283], [1024], [1025], [1051], [2077], [5000],
+                                   [3, 29, 1024, 1055, 33, 2048], [1, 1, 6, 5000, 1020]])
+@pytest.mark.parametrize("kind,momentum", [("round", 0.9), ("round", 0.0), ("fp32", 0.9), ("bf16", 0.9)])
+def test_rows_off_the_lines_give_the_same_bits(sizes, kind, momentum):
+    want = rounds(sizes, 0, momentum, kind)
+    for extra in (4, 8, 16, 28):                     # three workers: leads of 0, -extra and -2 extra modulo 32
+        got = rounds(sizes, extra, momentum, kind)
+        assert all(torch.equal(a, b) for a, b in zip(got, want)), extra
