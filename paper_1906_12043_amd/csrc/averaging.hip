@@ -15,6 +15,8 @@
 #include "internal.hpp"
 #include "mean_sum.hpp"
 
+#include <type_traits>
+
 namespace cocod {
 namespace {
 
@@ -23,6 +25,7 @@ namespace {
 // step with 64-thread blocks, 0.33 ms with 128 and 0.79 ms (the whole step) with 256 or 1024.  Alone the
 // averaging kernels run at the same rate for every block size.
 constexpr uint32_t kAvgThreads = 64;
+constexpr uint32_t kXcds = 8;  // accelerator complex dies of the MI355X, each with its own L2
 constexpr int kRowBatch = 8;   // independent row loads in flight per thread
 
 typedef float f4v __attribute__((ext_vector_type(4)));
@@ -106,47 +109,77 @@ __device__ __forceinline__ void correct_column(float *xcol, const float *scol, c
     }
 }
 
-// WREG > 0: W <= WREG and the column's stored models stay in registers between the two passes, so
-// each is read from memory once (12 + 4/W bytes per parameter).  WREG == 0: any W, the stored models
-// are read a second time for line 6.
-template <bool WEIGHTED, int WREG>
-__global__ __launch_bounds__(kAvgThreads) void mean_correct_kernel(float *x, const float *snap, uint64_t stride,
-                                                                   uint32_t W, uint64_t begin, uint64_t n_quads,
+// R > 0: W <= R and the column's stored models stay in registers between the two passes, so each is read from
+// memory once (12 + 4/W bytes per parameter).  R == 0: any W, the stored models are read a second time for line 6.
+// V: elements per thread, a column quad or (above 32 workers, to keep the rows in 128 registers) a column pair.
+// SAME: the models ARE the stored models (the blocking average of Local SGD): x is not read again, 8 + 4/W bytes.
+// LINES: every row starts on a 128-byte line.  Off the lines a wave's kilobyte of a row leaves half a line at both ends;
+// there the stores are ordinary ones and an XCD owns a contiguous run of columns, so that neighbouring waves'
+// halves meet in its L2.
+// Memory bounds all of it.  Blocking average, before (rows read up to three times) and now: W = 16, d = 11.2 M 380 -> 255 us
+// (5.6 TB/s of 8 bytes), W = 21, d = 4.0 M 183 -> 128, W = 64, d = 5.6 M 784 -> 546; the same off the lines 457 -> 315,
+// 220 -> 132, 967 -> 636 (with streaming stores in plain block order 320, 151, 785).  Open round, W = 21: 245 -> 180 us, W = 64:
+// 1076 -> 829.  On the lines the plain order with streaming stores is the faster one (W = 16: 247 us against 290).
+constexpr int mean_correct_waves(int R) { return R == 0 || R <= 8 ? 8 : R <= 16 ? 4 : 3; }    // per SIMD: the rows of a thread and a batch of x fit
+template <bool WEIGHTED, int R, int V, bool SAME, bool LINES>
+__global__ __launch_bounds__(kAvgThreads, mean_correct_waves(R)) void mean_correct_kernel(float *x, const float *snap, uint64_t stride,
+                                                                   uint32_t W, uint64_t begin, uint64_t n_groups,
                                                                    const float *weights, float *mean)
 {
-    const uint64_t quad = static_cast<uint64_t>(blockIdx.x) * kAvgThreads + threadIdx.x;
-    if (quad >= n_quads) return;
-    const uint64_t e = begin + quad * 4;
-    if (WREG == 0) {
+    #pragma clang fp contract(off)
+    uint32_t block = blockIdx.x;
+    if (!LINES) {
+        const uint32_t run = gridDim.x / kXcds;                // what does not divide stays in place at the end
+        if (block < run * kXcds) block = (block % kXcds) * run + block / kXcds;
+    }
+    const uint64_t group = static_cast<uint64_t>(block) * kAvgThreads + threadIdx.x;
+    if (group >= n_groups) return;
+    const uint64_t e = begin + group * V;
+    if constexpr (R == 0) {
         const float4 m = column_mean<WEIGHTED>(snap + e, stride, W, weights);
         st4(mean + e, m);
         correct_column(x + e, snap + e, m, stride, W);
-        return;
-    }
-    constexpr int R = WREG > 0 ? WREG : 1;
-    float4 s[R];
-    #pragma unroll
-    for (int i = 0; i < R; ++i)
-        if (static_cast<uint32_t>(i) < W) s[i] = ld4_stream(snap + e + static_cast<uint64_t>(i) * stride);
-    MeanSum acc;
-    acc.clear();
-    #pragma unroll
-    for (int i = 0; i < R; ++i) {                          // same order and operations as column_mean
-        if (static_cast<uint32_t>(i) < W)                  // guard, not break: the loop must unroll fully or s[] goes to scratch
-            acc.add<WEIGHTED>(WEIGHTED ? weights[i] : 1.0f, s[i].x, s[i].y, s[i].z, s[i].w);
-    }
-    acc.finish<WEIGHTED>(W);
-    const float4 m = make_float4(acc.s[0], acc.s[1], acc.s[2], acc.s[3]);
-    st4(mean + e, m);
-    #pragma unroll
-    for (int i = 0; i < R; ++i) {
-        if (static_cast<uint32_t>(i) < W) {
-            float *xp = x + e + static_cast<uint64_t>(i) * stride;
-            const float4 xr = ld4_stream(xp);
-            float4 o;
-            o.x = m.x + (xr.x - s[i].x); o.y = m.y + (xr.y - s[i].y);
-            o.z = m.z + (xr.z - s[i].z); o.w = m.w + (xr.w - s[i].w);
-            st4_stream(xp, o);
+    } else {
+        typedef float fv __attribute__((ext_vector_type(V)));
+        fv s[R];
+        #pragma unroll
+        for (int i = 0; i < R; ++i)                            // guards, not breaks: the loops must unroll fully or s[] goes to scratch
+            if (static_cast<uint32_t>(i) < W)
+                s[i] = __builtin_nontemporal_load(reinterpret_cast<const fv *>(snap + e + static_cast<uint64_t>(i) * stride));
+        MeanSumN<V> acc;
+        acc.clear();
+        #pragma unroll
+        for (int i = 0; i < R; ++i)                            // same order and operations as column_mean
+            if (static_cast<uint32_t>(i) < W) {
+                #pragma unroll
+                for (int c = 0; c < V; ++c) acc.template add_one<WEIGHTED>(c, WEIGHTED ? weights[i] : 1.0f, s[i][c]);
+            }
+        acc.template finish<WEIGHTED>(W);
+        fv m;
+        #pragma unroll
+        for (int c = 0; c < V; ++c) m[c] = acc.s[c];
+        *reinterpret_cast<fv *>(mean + e) = m;
+        auto put = [&](int i, const fv xr) {
+            fv *to = reinterpret_cast<fv *>(x + e + static_cast<uint64_t>(i) * stride);
+            if (LINES) __builtin_nontemporal_store(m + (xr - s[i]), to);
+            else       *to = m + (xr - s[i]);
+        };
+        auto get = [&](int i) { return __builtin_nontemporal_load(reinterpret_cast<const fv *>(x + e + static_cast<uint64_t>(i) * stride)); };
+        constexpr int B = 4;                                   // rows of x in flight
+        #pragma unroll
+        for (int i0 = 0; i0 < R; i0 += B) {
+            if (SAME || static_cast<uint32_t>(i0 + B) > W) {
+                #pragma unroll
+                for (int i = i0; i < i0 + B; ++i)
+                    if (static_cast<uint32_t>(i) < W) put(i, SAME ? s[i] : get(i));
+            } else {
+                fv xr[B];
+                #pragma unroll
+                for (int b = 0; b < B; ++b) xr[b] = get(i0 + b);
+                #pragma unroll
+                for (int b = 0; b < B; ++b) put(i0 + b, xr[b]);
+                __builtin_amdgcn_sched_barrier(0);             // or the loads of all batches are hoisted into registers
+            }
         }
     }
 }
@@ -343,20 +376,25 @@ hipError_t launch_mean_correct(hipStream_t stream, float *x, const float *snap, 
 {
     const uint64_t n_quads = (end - begin) / 4;
     if (n_quads == 0) return hipSuccess;
-    const dim3 grid(blocks_for(n_quads)), block(kAvgThreads);
-    if (W <= 8) {
-        if (weights) hipLaunchKernelGGL((mean_correct_kernel<true, 8>), grid, block, 0, stream, x, snap, stride, W, begin, n_quads, weights, mean);
-        else         hipLaunchKernelGGL((mean_correct_kernel<false, 8>), grid, block, 0, stream, x, snap, stride, W, begin, n_quads, weights, mean);
+    auto launch = [&](auto kernel, uint32_t v) {
+        hipLaunchKernelGGL(kernel, dim3(blocks_for((end - begin) / v)), dim3(kAvgThreads), 0, stream, x, snap, stride, W, begin,
+                           (end - begin) / v, weights, mean);
         return hipGetLastError();
-    }
-    if (W <= 16) {
-        if (weights) hipLaunchKernelGGL((mean_correct_kernel<true, 16>), grid, block, 0, stream, x, snap, stride, W, begin, n_quads, weights, mean);
-        else         hipLaunchKernelGGL((mean_correct_kernel<false, 16>), grid, block, 0, stream, x, snap, stride, W, begin, n_quads, weights, mean);
-        return hipGetLastError();
-    }
-    if (weights) hipLaunchKernelGGL((mean_correct_kernel<true, 0>), grid, block, 0, stream, x, snap, stride, W, begin, n_quads, weights, mean);
-    else         hipLaunchKernelGGL((mean_correct_kernel<false, 0>), grid, block, 0, stream, x, snap, stride, W, begin, n_quads, weights, mean);
-    return hipGetLastError();
+    };
+    auto rows = [&](auto weighted, auto same, auto lines) {
+        constexpr bool WT = decltype(weighted)::value, SAME = decltype(same)::value, LINES = decltype(lines)::value;
+        if (W <= 8) return launch(mean_correct_kernel<WT, 8, 4, SAME, LINES>, 4);
+        if (W <= 16) return launch(mean_correct_kernel<WT, 16, 4, SAME, LINES>, 4);
+        if (W <= 32) return launch(mean_correct_kernel<WT, 32, 4, SAME, LINES>, 4);
+        if (W <= 64) return launch(mean_correct_kernel<WT, 64, 2, SAME, LINES>, 2);
+        return launch(mean_correct_kernel<WT, 0, 4, false, true>, 4);
+    };
+    using T = std::true_type;
+    using F = std::false_type;
+    const bool lines = W == 1 || ((reinterpret_cast<uintptr_t>(x + begin) | stride * sizeof(float)) & 127u) == 0;
+    auto with_rows = [&](auto weighted, auto same) { return lines ? rows(weighted, same, T{}) : rows(weighted, same, F{}); };
+    if (x == snap) return weights ? with_rows(T{}, T{}) : with_rows(F{}, T{});
+    return weights ? with_rows(T{}, F{}) : with_rows(F{}, F{});
 }
 
 hipError_t launch_consensus_distance(hipStream_t stream, const Chunk *table, uint32_t n_chunks, const float *x,
