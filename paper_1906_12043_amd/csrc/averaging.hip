@@ -186,9 +186,8 @@ __global__ __launch_bounds__(kAvgThreads, mean_correct_waves(R)) void mean_corre
 
 // ---- consensus distance: sum_i p_i || xbar - x_i ||^2 with xbar = sum_i p_i x_i ---------------------
 // (the quantity bounded by Lemma 2 of the paper).  A scalar, so this is where wave and LDS reductions
-// belong: per thread a column quad (its W rows held in registers up to 16 workers; above, two passes
-// over the rows, the second one from cache), then a butterfly over the wave, the four wave sums through LDS, one double per block; a second one-block
-// kernel adds the block partials in a fixed order, so the result is deterministic.
+// belong: per thread a column quad or pair, then a butterfly over the wave, the four wave sums through LDS, one double
+// per block; a second one-block kernel adds the block partials in a fixed order, so the result is deterministic.
 // the same mean with ordinary (cached) loads, for the kernels that read the models a second time
 template <bool WEIGHTED>
 __device__ __forceinline__ float4 column_mean_cached(const float *col, uint64_t stride, uint32_t W, const float *weights)
@@ -212,8 +211,6 @@ __device__ __forceinline__ float4 column_mean_cached(const float *col, uint64_t 
     return make_float4(acc.s[0], acc.s[1], acc.s[2], acc.s[3]);
 }
 
-constexpr uint32_t kRowsInRegisters = 16;   // up to this many workers a thread keeps its whole column quad in registers
-
 __device__ __forceinline__ double wave_sum_f64(double v)
 {
     #pragma unroll
@@ -221,59 +218,69 @@ __device__ __forceinline__ double wave_sum_f64(double v)
     return v;
 }
 
-template <bool WEIGHTED>
-__global__ __launch_bounds__(kStepThreads) void consensus_partial_kernel(const Chunk *table, const float *x, uint64_t stride,
-                                                                         uint32_t W, const float *weights, double *partial)
+// R > 0: up to R workers a thread holds V columns of every row in registers and reads each model once; R == 0: any W,
+// two passes over the rows.  (W = 64, d = 2.8 M: two passes 207 us, the second one mostly from memory again, as the rows of
+// the blocks in flight are far more than L2 holds; column pairs in registers 121 us = 5.9 TB/s.  W = 21, d = 4.0 M:
+// 104 -> 59 us; W = 1, where registers for 16 rows cost occupancy: 27 -> 23.)
+template <bool WEIGHTED, int R, int V>
+__global__ __launch_bounds__(kStepThreads, R > 16 ? 3 : 4) void consensus_partial_kernel(const Chunk *table, const float *x, uint64_t stride,
+                                                                                                 uint32_t W, const float *weights, double *partial)
 {
     __shared__ double wave_part[kStepThreads / 64];
     const Chunk ck = table[blockIdx.x];
-    const uint32_t e = threadIdx.x * 4;
+    const float uniform = 1.0f / static_cast<float>(W);
     double local = 0.0;
-    if (e < ck.n) {
+    auto columns = [&](uint32_t e) {
         const float *col = x + static_cast<uint64_t>(ck.mem_quad) * 4 + e;
-        const float uniform = 1.0f / static_cast<float>(W);
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        auto add_row = [&](uint32_t i, const float4 &r, const float4 &m) {
+        float acc[V], m[V];
+        #pragma unroll
+        for (int c = 0; c < V; ++c) acc[c] = 0.0f;
+        auto add_row = [&](uint32_t i, const auto &r) {
             const float pw = WEIGHTED ? weights[i] : uniform;
-            acc.x += pw * (r.x - m.x) * (r.x - m.x); acc.y += pw * (r.y - m.y) * (r.y - m.y);
-            acc.z += pw * (r.z - m.z) * (r.z - m.z); acc.w += pw * (r.w - m.w) * (r.w - m.w);
-        };
-        if (W <= kRowsInRegisters) {
-            // one pass: every row of the column quad is requested at once and stays in registers for the
-            // squared distances (the guards are uniform over the grid)
-            float4 r[kRowsInRegisters];
             #pragma unroll
-            for (uint32_t i = 0; i < kRowsInRegisters; ++i)
-                if (i < W) r[i] = ld4_stream(col + static_cast<uint64_t>(i) * stride);
-            MeanSum ms;
+            for (int c = 0; c < V; ++c) acc[c] += pw * (r[c] - m[c]) * (r[c] - m[c]);
+        };
+        typedef float fv __attribute__((ext_vector_type(V)));
+        if constexpr (R > 0) {
+            fv r[R];                                          // every row is requested at once (the guards are uniform over the grid)
+            #pragma unroll
+            for (int i = 0; i < R; ++i)
+                if (static_cast<uint32_t>(i) < W) r[i] = __builtin_nontemporal_load(reinterpret_cast<const fv *>(col + static_cast<uint64_t>(i) * stride));
+            MeanSumN<V> ms;
             ms.clear();
             #pragma unroll
-            for (uint32_t i = 0; i < kRowsInRegisters; ++i)
-                if (i < W) ms.add<WEIGHTED>(WEIGHTED ? weights[i] : 1.0f, r[i].x, r[i].y, r[i].z, r[i].w);
-            ms.finish<WEIGHTED>(W);
-            const float4 m = make_float4(ms.s[0], ms.s[1], ms.s[2], ms.s[3]);
+            for (int i = 0; i < R; ++i)
+                if (static_cast<uint32_t>(i) < W) {
+                    #pragma unroll
+                    for (int c = 0; c < V; ++c) ms.template add_one<WEIGHTED>(c, WEIGHTED ? weights[i] : 1.0f, r[i][c]);
+                }
+            ms.template finish<WEIGHTED>(W);
             #pragma unroll
-            for (uint32_t i = 0; i < kRowsInRegisters; ++i)
-                if (i < W) add_row(i, r[i], m);
+            for (int c = 0; c < V; ++c) m[c] = ms.s[c];
+            #pragma unroll
+            for (int i = 0; i < R; ++i)
+                if (static_cast<uint32_t>(i) < W) add_row(i, r[i]);
         } else {
-            // two passes over the W rows, the second one from cache
-            const float4 m = column_mean_cached<WEIGHTED>(col, stride, W, weights);
+            static_assert(V == 4, "column quads");
+            const float4 mean = column_mean_cached<WEIGHTED>(col, stride, W, weights);
+            m[0] = mean.x; m[1] = mean.y; m[2] = mean.z; m[3] = mean.w;
             uint32_t i = 0;
             for (; i + kRowBatch <= W; i += kRowBatch) {
-                float4 r[kRowBatch];
+                fv r[kRowBatch];
                 #pragma unroll
-                for (int b = 0; b < kRowBatch; ++b) r[b] = ld4(col + static_cast<uint64_t>(i + b) * stride);
+                for (int b = 0; b < kRowBatch; ++b) r[b] = *reinterpret_cast<const fv *>(col + static_cast<uint64_t>(i + b) * stride);
                 #pragma unroll
-                for (int b = 0; b < kRowBatch; ++b) add_row(i + b, r[b], m);
+                for (int b = 0; b < kRowBatch; ++b) add_row(i + b, r[b]);
             }
-            for (; i < W; ++i) add_row(i, ld4(col + static_cast<uint64_t>(i) * stride), m);
+            for (; i < W; ++i) add_row(i, *reinterpret_cast<const fv *>(col + static_cast<uint64_t>(i) * stride));
         }
-        const uint32_t keep = ck.n - e;                   // alignment pads of a tensor's tail quad do not count
-        local = static_cast<double>(acc.x);
-        if (keep > 1) local += static_cast<double>(acc.y);
-        if (keep > 2) local += static_cast<double>(acc.z);
-        if (keep > 3) local += static_cast<double>(acc.w);
-    }
+        #pragma unroll
+        for (int c = 0; c < V; ++c)                           // alignment pads of a tensor's tail quad do not count
+            if (e + c < ck.n) local += static_cast<double>(acc[c]);
+    };
+    if (threadIdx.x * V < ck.n) columns(threadIdx.x * V);
+    if (V * kStepThreads < kChunkElems)
+        for (uint32_t e = (kStepThreads + threadIdx.x) * V; e < ck.n; e += kStepThreads * V) columns(e);
     local = wave_sum_f64(local);
     if (threadIdx.x % 64 == 0) wave_part[threadIdx.x / 64] = local;
     __syncthreads();
@@ -284,17 +291,28 @@ __global__ __launch_bounds__(kStepThreads) void consensus_partial_kernel(const C
     }
 }
 
-// block b adds the b-th run of n block partials into out[b]
-__global__ __launch_bounds__(256) void consensus_final_kernel(const double *partial, uint32_t n, double *out)
+// block b adds the b-th run of n block partials into out[b] (one block is a chain of load latencies: sixteen waves, four
+// loads in flight each: n = 2735 6.3 -> 5.8 us, n = 9766 about 16 -> 8 us)
+constexpr uint32_t kFinalThreads = 1024;
+__global__ __launch_bounds__(kFinalThreads) void consensus_final_kernel(const double *partial, uint32_t n, double *out)
 {
-    __shared__ double wave_part[4];
+    __shared__ double wave_part[kFinalThreads / 64];
     partial += static_cast<uint64_t>(blockIdx.x) * n;
-    double local = 0.0;
-    for (uint32_t i = threadIdx.x; i < n; i += 256) local += partial[i];
-    local = wave_sum_f64(local);
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+    for (uint32_t i = threadIdx.x; i < n; i += 4 * kFinalThreads) {
+        #pragma unroll
+        for (uint32_t u = 0; u < 4; ++u)
+            if (i + u * kFinalThreads < n) sum[u] += partial[i + u * kFinalThreads];
+    }
+    const double local = wave_sum_f64((sum[0] + sum[1]) + (sum[2] + sum[3]));
     if (threadIdx.x % 64 == 0) wave_part[threadIdx.x / 64] = local;
     __syncthreads();
-    if (threadIdx.x == 0) out[blockIdx.x] = (wave_part[0] + wave_part[1]) + (wave_part[2] + wave_part[3]);
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        #pragma unroll
+        for (uint32_t w = 0; w < kFinalThreads / 64; ++w) s += wave_part[w];
+        out[blockIdx.x] = s;
+    }
 }
 
 // ---- the objective of the paper's problem definition at the averaged model ------------------------
@@ -400,9 +418,17 @@ hipError_t launch_mean_correct(hipStream_t stream, float *x, const float *snap, 
 hipError_t launch_consensus_distance(hipStream_t stream, const Chunk *table, uint32_t n_chunks, const float *x,
                                      uint64_t stride, uint32_t W, const float *weights, double *partial, double *out)
 {
-    if (weights) hipLaunchKernelGGL((consensus_partial_kernel<true>), dim3(n_chunks), dim3(kStepThreads), 0, stream, table, x, stride, W, weights, partial);
-    else         hipLaunchKernelGGL((consensus_partial_kernel<false>), dim3(n_chunks), dim3(kStepThreads), 0, stream, table, x, stride, W, weights, partial);
-    hipLaunchKernelGGL(consensus_final_kernel, dim3(1), dim3(256), 0, stream, partial, n_chunks, out);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(n_chunks), dim3(kStepThreads), 0, stream, table, x, stride, W, weights, partial); };
+    auto rows = [&](auto weighted) {
+        constexpr bool WT = decltype(weighted)::value;
+        if (W <= 8) launch(consensus_partial_kernel<WT, 8, 4>);
+        else if (W <= 16) launch(consensus_partial_kernel<WT, 16, 4>);
+        else if (W <= 32) launch(consensus_partial_kernel<WT, 32, 4>);
+        else if (W <= 64) launch(consensus_partial_kernel<WT, 64, 2>);
+        else launch(consensus_partial_kernel<WT, 0, 4>);
+    };
+    if (weights) rows(std::true_type{}); else rows(std::false_type{});
+    hipLaunchKernelGGL(consensus_final_kernel, dim3(1), dim3(kFinalThreads), 0, stream, partial, n_chunks, out);
     return hipGetLastError();
 }
 
@@ -412,7 +438,7 @@ hipError_t launch_quadratic_objective(hipStream_t stream, const Chunk *table, ui
 {
     if (weights) hipLaunchKernelGGL((objective_partial_kernel<true>), dim3(n_chunks), dim3(kStepThreads), 0, stream, table, x, h, c, stride, W, weights, partial);
     else         hipLaunchKernelGGL((objective_partial_kernel<false>), dim3(n_chunks), dim3(kStepThreads), 0, stream, table, x, h, c, stride, W, weights, partial);
-    hipLaunchKernelGGL(consensus_final_kernel, dim3(2), dim3(256), 0, stream, partial, n_chunks, out);
+    hipLaunchKernelGGL(consensus_final_kernel, dim3(2), dim3(kFinalThreads), 0, stream, partial, n_chunks, out);
     return hipGetLastError();
 }
 

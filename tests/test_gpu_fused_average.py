@@ -46,3 +46,37 @@ def test_one_kernel_gives_the_bits_of_two(W, extra, weighted, d):
     nan = [torch.isnan(t.view(torch.float32)) for t in out[0]]               # a NaN's payload is not part of the result
     for a, b, n in zip(out[0], out[1], nan):
         assert torch.equal(torch.isnan(b.view(torch.float32)), n) and torch.equal(a[~n], b[~n])
+
+
+@pytest.mark.parametrize("W", [1, 8, 9, 16, 17, 32, 33, 64, 65])
+@pytest.mark.parametrize("sizes,weighted", [([1], False), ([2050], True), ([3, 1023, 1026, 5, 700_001], False)])
+def test_consensus_distance_of_every_worker_class(W, sizes, weighted):
+    """Against 64 bits: a column's sum of W squares is formed in fp32 (each a few roundings), the rest in fp64."""
+    from tests.gpu_harness import packed_positions
+    d = sum(sizes)
+    packed = sizes if len(sizes) > 1 else None
+    stride = (P.plan_layout(d, packed)[0] + 3) // 4 * 4 + 4
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(W)
+    x = rng.standard_normal((W, d)).astype(np.float32)
+    pos = torch.from_numpy(packed_positions(packed, d)).to(dev)
+    xA = torch.full((W, stride), 1e3, device=dev)                       # pads must not count
+    xA[:, pos] = torch.from_numpy(x).to(dev)
+    xB, mean, out = torch.zeros_like(xA), torch.zeros(stride, device=dev), torch.zeros(1, dtype=torch.float64, device=dev)
+    p = np.full(W, 1.0 / W)
+    if weighted:
+        p = rng.uniform(0.1, 1.0, W).astype(np.float32)
+        p = (p / p.sum()).astype(np.float32).astype(np.float64)
+    s = torch.cuda.Stream(device=dev)
+    torch.cuda.synchronize()
+    ctx = P.Context(W=W, d=d, stride=stride, xA=xA, xB=xB, mean=mean, lr=0.1, grad=P.GRAD_EXTERNAL, tensor_numel=packed,
+                    weights=[float(v) for v in p] if weighted else None, compute_stream=s, avg_stream=s)
+    got = ctx.consensus_distance()
+    ctx.consensus_distance_noalloc(out)
+    ctx.sync()
+    x64 = x.astype(np.float64)
+    want = float((p[:, None] * (x64 - p @ x64) ** 2).sum())
+    ctx.close()
+    # W squares of a column in one fp32 chain, each with a difference that the rounded mean moves by 2^-23 of |x|
+    assert abs(got - want) <= (W + 8) * 2.0**-24 * want + 2.0**-22 * float((p[:, None] * np.abs(x64) * np.abs(x64 - p @ x64)).sum()) + 1e-30
+    assert got == float(out.item())
