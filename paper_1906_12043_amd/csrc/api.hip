@@ -24,7 +24,8 @@ struct cocod_ctx {
     Chunk *d_chunks = nullptr;          // device copy of the chunk table (owned)
     float *d_weights = nullptr;         // device copy of p_i (owned), nullptr = uniform
     float *d_sigma_w = nullptr;         // device copy of the per-worker noise scale (owned), nullptr = cfg.noise_sigma
-    double *d_reduce = nullptr;         // scratch of the consensus-distance reduction (owned, allocated on first use)
+    double *d_reduce = nullptr;         // scratch of the diagnostics' reductions (owned, allocated on first use)
+    double *host_result = nullptr;      // their two results, pinned host memory that the last kernel writes (owned, with d_reduce)
     double *static_scratch = nullptr;   // this GPU's copy of the library's static scratch array (not owned)
     float *mlp_ws = nullptr;            // MLP kind: work space (owned); mlp holds the pointers carved from it
     cocod::MlpParams mlp{};
@@ -258,6 +259,7 @@ void release(cocod_ctx *ctx)
         if (ctx->d_sigma_w) (void)hipFree(ctx->d_sigma_w);
         if (ctx->mlp_ws) (void)hipFree(ctx->mlp_ws);
         if (ctx->d_reduce) (void)hipFree(ctx->d_reduce);
+        if (ctx->host_result) (void)hipHostFree(ctx->host_result);
         if (ctx->d_step) (void)hipFree(ctx->d_step);
         for (auto &g : ctx->graphs) (void)hipGraphExecDestroy(g.exec);
         if (ctx->ev_snap) (void)hipEventDestroy(ctx->ev_snap);
@@ -922,18 +924,29 @@ int cocod_step_timing_read(cocod_ctx *ctx, double total_ms[3], uint32_t launches
     return COCOD_OK;
 }
 
+// Scratch of the diagnostics, on first use: block partials of two reductions, and the pinned words that receive the
+// results (a copy of 8 bytes to ordinary host memory costs 10 us on the way to the caller).
+static int diagnostics_scratch(cocod_ctx *ctx)
+{
+    if (!ctx->d_reduce)
+        COCOD_HIP(ctx, hipMalloc(reinterpret_cast<void **>(&ctx->d_reduce), ctx->chunks.size() * 2 * sizeof(double)));
+    if (!ctx->host_result)
+        COCOD_HIP(ctx, hipHostMalloc(reinterpret_cast<void **>(&ctx->host_result), 2 * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent));
+    return COCOD_OK;
+}
+
 int cocod_consensus_distance(cocod_ctx *ctx, double *result)
 {
     if (!ctx || !result) return fail(nullptr, COCOD_ERR_INVALID, "ctx and result must not be NULL");
     *result = 0.0;
     if (ctx->dry) return COCOD_OK;
     const uint32_t n_chunks = static_cast<uint32_t>(ctx->chunks.size());
-    if (!ctx->d_reduce)     // two results, then two runs of block partials
-        COCOD_HIP(ctx, hipMalloc(reinterpret_cast<void **>(&ctx->d_reduce), (static_cast<size_t>(n_chunks) + 1) * 2 * sizeof(double)));
+    const int rc = diagnostics_scratch(ctx);
+    if (rc != COCOD_OK) return rc;
     COCOD_HIP(ctx, cocod::launch_consensus_distance(ctx->s_compute, ctx->d_chunks, n_chunks, ctx->live, ctx->cfg.stride,
-                                                    ctx->cfg.W, ctx->d_weights, ctx->d_reduce + 2, ctx->d_reduce));
-    COCOD_HIP(ctx, hipMemcpyAsync(result, ctx->d_reduce, sizeof(double), hipMemcpyDeviceToHost, ctx->s_compute));
+                                                    ctx->cfg.W, ctx->d_weights, ctx->d_reduce, ctx->host_result));
     COCOD_HIP(ctx, hipStreamSynchronize(ctx->s_compute));
+    *result = ctx->host_result[0];
     return COCOD_OK;
 }
 
@@ -963,16 +976,14 @@ int cocod_quadratic_objective(cocod_ctx *ctx, double *f_at_mean, double *grad_no
     if (ctx->cfg.grad != COCOD_GRAD_QUADRATIC) return fail(ctx, COCOD_ERR_INVALID, "not a quadratic-gradient context");
     if (ctx->dry) return COCOD_OK;
     const uint32_t n_chunks = static_cast<uint32_t>(ctx->chunks.size());
-    if (!ctx->d_reduce)
-        COCOD_HIP(ctx, hipMalloc(reinterpret_cast<void **>(&ctx->d_reduce), (static_cast<size_t>(n_chunks) + 1) * 2 * sizeof(double)));
+    const int rc = diagnostics_scratch(ctx);
+    if (rc != COCOD_OK) return rc;
     COCOD_HIP(ctx, cocod::launch_quadratic_objective(ctx->s_compute, ctx->d_chunks, n_chunks, ctx->live, ctx->cfg.h, ctx->cfg.c,
-                                                     ctx->cfg.stride, ctx->cfg.W, ctx->d_weights, ctx->d_reduce + 2,
-                                                     ctx->d_reduce));
-    double both[2] = {0.0, 0.0};
-    COCOD_HIP(ctx, hipMemcpyAsync(both, ctx->d_reduce, sizeof both, hipMemcpyDeviceToHost, ctx->s_compute));
+                                                     ctx->cfg.stride, ctx->cfg.W, ctx->d_weights, ctx->d_reduce,
+                                                     ctx->host_result));
     COCOD_HIP(ctx, hipStreamSynchronize(ctx->s_compute));
-    *f_at_mean = both[0];
-    *grad_norm_sq_at_mean = both[1];
+    *f_at_mean = ctx->host_result[0];
+    *grad_norm_sq_at_mean = ctx->host_result[1];
     return COCOD_OK;
 }
 
