@@ -127,6 +127,11 @@ constexpr uint32_t kPanelTiles = 16384;
 // A mean vector up to this size is expected to stay in the 256 MB last-level cache while the W
 // workers of a line-6 step read it one after the other.
 constexpr uint64_t kMeanCacheBytes = 128ull << 20;
+// Steps access a state (both model buffers, v, h, c: 20 bytes per worker-parameter) up to this size without the
+// streaming hint: the next step finds it in the last-level cache.  k = 8 rounds, hint / no hint: W = 8, d = 250 k
+// (40 MB) 83.7 / 66.5 us, W = 16, d = 400 k (128 MB) 220 / 206, d = 700 k (224 MB) 367 / 337 (with three such contexts in
+// turn 355 / 348), d = 1 M (320 MB) 514 / 479 but in turn 518 / 570, d = 2 M (640 MB) 992 / 1125.
+constexpr uint64_t kCachedStateBytes = 224ull << 20;
 // one grid dimension holds fewer than 2^32 threads
 constexpr uint64_t kMaxThreadsPerGridDim = 1ull << 32;
 // the mean-forming steps launch up to four 1024-thread blocks per chunk in one grid dimension
@@ -464,6 +469,11 @@ static uint32_t panel_tiles_for(const cocod_ctx *ctx)
                ? kPanelTiles : 0u;
 }
 
+static uint32_t step_state_is_cached(const cocod_ctx *ctx)
+{
+    return 20 * ctx->cfg.stride * static_cast<uint64_t>(ctx->cfg.W) <= kCachedStateBytes ? 1u : 0u;
+}
+
 // The next step, if it carries line 6, can also form the round's mean itself (k = 1 under the schedule
 // that folds Step I into Step II: the step reads exactly the stored models).
 static bool one_pass_applies(const cocod_ctx *ctx)
@@ -540,6 +550,7 @@ static int enqueue_step(cocod_ctx *ctx, bool with_line6, const void *g_ext = nul
         p.step = static_cast<uint32_t>(ctx->capturing ? ctx->step - ctx->capture_base : ctx->step);
         p.step_base = ctx->capturing ? ctx->d_step : nullptr;
         p.panel_tiles = panel_tiles_for(ctx);
+        p.cached = step_state_is_cached(ctx);
         // Step I inside the round's first step: that step reads exactly the stored models (when there are
         // too many workers for its LDS tile, the mean stays pending and is formed just before line 6)
         const bool head = ctx->schedule == COCOD_SCHED_HEAD && ctx->mean_pending && ctx->store_pending && !g_ext &&
@@ -696,6 +707,7 @@ int cocod_average_end_apply(cocod_ctx *ctx)
                 p.snap = ctx->snap;
                 p.mean = ctx->cfg.mean;
                 p.panel_tiles = panel_tiles_for(ctx);
+                p.cached = step_state_is_cached(ctx);
                 COCOD_HIP(ctx, cocod::launch_line6(ctx->s_compute, p));
             }
         }

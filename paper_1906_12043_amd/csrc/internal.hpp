@@ -44,6 +44,7 @@ struct StepParams {
     const uint32_t *step_base;   // non-null inside a replayable graph: device word holding t at the start of the replay
     uint32_t panel_tiles;      // line-6 step only, non-zero: blocks run in panels of this many tiles, worker by worker
                                // inside a panel (for a mean larger than the cache); 0 = grid (tiles, workers)
+    uint32_t cached;           // the state stays in the last-level cache from step to step: no streaming hint (not for mean-forming steps)
     float *mean_out;           // non-null: first step of a round that also forms the mean of the models it reads
     const float *weights;      //           (Step I inside Step II's first pass); p_i, nullptr = 1/W
 };

@@ -23,10 +23,10 @@
 //   ONE_PASS  k = 1: Step I, the local step and line 6 in a single sweep (24 + 4/W bytes per
 //             parameter): as HEAD, and line 6 is applied with the tile's mean before anything is stored.
 //
-// Memory path: every model array is streamed exactly once per step and is far larger than the caches,
-// so all accesses carry the non-temporal hint and go through buffer instructions whose descriptor
-// covers exactly the tile (step_common.hpp).  The mean is shared by the W workers of a column and is
-// read with an ordinary cached load.
+// Memory path: every model array is streamed exactly once per step, through buffer instructions whose descriptor
+// covers exactly the tile (step_common.hpp).  Where the state is larger than the 256 MB last-level cache the accesses
+// carry the non-temporal hint; a smaller one is found there again by the next step and is accessed without it
+// (step_state_is_cached).  The mean is shared by the W workers of a column and is read with an ordinary cached load.
 #include "internal.hpp"
 #include "step_common.hpp"
 #include "philox.hpp"
@@ -77,7 +77,7 @@ __device__ __forceinline__ void noise_for_lane(f4 (&z)[Q], uint64_t q0, uint32_t
 // Grid: x = tiles (chunks * 4 / Q); y = groups of workers (modes without a mean: ceil(W / waves);
 // mean-forming modes: 1, the block loops over its worker groups itself).
 // Dynamic LDS (mean-forming modes only): W rows of the tile, then (ONE_PASS) the tile of the mean.
-template <bool HAS_V, int GRAD, int MODE, bool WEIGHTED, int NWMAX, int Q>
+template <bool HAS_V, int GRAD, int MODE, bool WEIGHTED, int NWMAX, int Q, int AUX>
 __global__ __launch_bounds__(64 * NWMAX) void local_step_kernel(const StepParams p)
 {
     constexpr bool FORMS_MEAN = MODE == kModeHead || MODE == kModeOnePass;
@@ -142,18 +142,18 @@ __global__ __launch_bounds__(64 * NWMAX) void local_step_kernel(const StepParams
         #pragma unroll
         for (int u = 0; u < Q; ++u) {
             const uint32_t off = (64u * u + lane) * 16u;
-            r.v[u] = HAS_V ? load_quad(make_rsrc(p.v + row, bytes), off) : f4{0.f, 0.f, 0.f, 0.f};
+            r.v[u] = HAS_V ? load_quad<AUX>(make_rsrc(p.v + row, bytes), off) : f4{0.f, 0.f, 0.f, 0.f};
             r.c[u] = f4{0.f, 0.f, 0.f, 0.f};
             if (GRAD == kGradQuadNoisy || GRAD == kGradQuadExact) {
-                r.h[u] = load_quad(make_rsrc(p.h + row, bytes), off);
-                r.c[u] = load_quad(make_rsrc(p.c + row, bytes), off);
+                r.h[u] = load_quad<AUX>(make_rsrc(p.h + row, bytes), off);
+                r.c[u] = load_quad<AUX>(make_rsrc(p.c + row, bytes), off);
             } else if (GRAD == kGradExternal) {
-                r.h[u] = load_quad(make_rsrc(p.g + row, bytes), off);         // the caller's gradient
+                r.h[u] = load_quad<AUX>(make_rsrc(p.g + row, bytes), off);         // the caller's gradient
             } else {                                                          // 16-bit gradients: the upper halves of fp32
                 const uint16_t *gb = reinterpret_cast<const uint16_t *>(p.g) + row;
                 const __amdgpu_buffer_rsrc_t rg =
                     __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(gb), 0, static_cast<int>(bytes / 2), 0x00020000);
-                const u2 t = __builtin_amdgcn_raw_buffer_load_b64(rg, static_cast<int>(off / 2), 0, kAuxNonTemporal);
+                const u2 t = __builtin_amdgcn_raw_buffer_load_b64(rg, static_cast<int>(off / 2), 0, AUX);
                 r.h[u] = f4{__uint_as_float(t.x << 16), __uint_as_float(t.x & 0xffff0000u),
                             __uint_as_float(t.y << 16), __uint_as_float(t.y & 0xffff0000u)};
             }
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(64 * NWMAX) void local_step_kernel(const StepParams
     auto load_x = [&](f4 (&x)[Q], uint32_t w) {
         const __amdgpu_buffer_rsrc_t rx = make_rsrc(p.x_in + static_cast<uint64_t>(w) * p.stride + col, bytes);
         #pragma unroll
-        for (int u = 0; u < Q; ++u) x[u] = load_quad(rx, (64u * u + lane) * 16u);
+        for (int u = 0; u < Q; ++u) x[u] = load_quad<AUX>(rx, (64u * u + lane) * 16u);
     };
     // the step itself for worker w: x0 = model read, r = its other streams, m = mean quads (line 6)
     auto step_row = [&](uint32_t w, const f4 (&x0)[Q], const Row &r, const f4 (&snap)[Q], const f4 (&m)[Q]) {
@@ -187,8 +187,8 @@ __global__ __launch_bounds__(64 * NWMAX) void local_step_kernel(const StepParams
                 if (keep < 3) { x.z = x0[u].z; v.z = r.v[u].z; }
                 x.w = x0[u].w; v.w = r.v[u].w;
             }
-            store_quad(rx_out, off, x);
-            if (HAS_V) store_quad(rv, off, v);
+            store_quad<AUX>(rx_out, off, x);
+            if (HAS_V) store_quad<AUX>(rv, off, v);
         }
     };
 
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(64 * NWMAX) void local_step_kernel(const StepParams
                 #pragma unroll
                 for (int u = 0; u < Q; ++u) {
                     const uint32_t e = (64u * u + lane) * 4u, off = e * 4u;
-                    snap[u] = load_quad(rs, off);
+                    snap[u] = load_quad<AUX>(rs, off);
                     m[u] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rm, static_cast<int>(off), 0, 0));
                 }
                 #pragma unroll
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(64 * NWMAX) void local_step_kernel(const StepParams
                         if (keep < 3) x.z = x0[u].z;
                         x.w = x0[u].w;
                     }
-                    store_quad(rx_out, e * 4u, x);
+                    store_quad<AUX>(rx_out, e * 4u, x);
                 }
             } else {
                 const Row r = load_row(w);
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(64 * NWMAX) void local_step_kernel(const StepParams
                 if (MODE == kModeTail) {
                     const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.snap + static_cast<uint64_t>(w) * p.stride + col, bytes);
                     #pragma unroll
-                    for (int u = 0; u < Q; ++u) snap[u] = load_quad(rs, (64u * u + lane) * 16u);
+                    for (int u = 0; u < Q; ++u) snap[u] = load_quad<AUX>(rs, (64u * u + lane) * 16u);
                 }
                 if (LINE6) {                                   // shared by the block's waves: ordinary cached load
                     const __amdgpu_buffer_rsrc_t rm = make_rsrc(p.mean + col, bytes);
@@ -317,11 +317,11 @@ hipError_t allow_big_lds(K kernel, size_t bytes)
 
 constexpr size_t kTileLdsMax = 132u << 10;      // of the 160 KB per compute unit
 
-template <bool HAS_V, int GRAD, int MODE, bool WEIGHTED, int NWMAX, int Q>
+template <bool HAS_V, int GRAD, int MODE, bool WEIGHTED, int NWMAX, int Q, int AUX>
 hipError_t launch_one(hipStream_t stream, const StepParams &p, uint32_t waves, hipEvent_t start, hipEvent_t stop)
 {
     constexpr bool FORMS_MEAN = MODE == kModeHead || MODE == kModeOnePass;
-    auto kernel = local_step_kernel<HAS_V, GRAD, MODE, WEIGHTED, NWMAX, Q>;
+    auto kernel = local_step_kernel<HAS_V, GRAD, MODE, WEIGHTED, NWMAX, Q, AUX>;
     size_t lds = 0;
     if (FORMS_MEAN) {
         lds = (static_cast<size_t>(p.W) + (MODE == kModeOnePass ? 1 : 0)) * Q * 256 * sizeof(float);
@@ -339,7 +339,7 @@ hipError_t launch_one(hipStream_t stream, const StepParams &p, uint32_t waves, h
     return hipGetLastError();
 }
 
-template <int MODE, bool WEIGHTED, int NWMAX, int Q>
+template <int MODE, bool WEIGHTED, int NWMAX, int Q, int AUX = kAuxNonTemporal>
 hipError_t launch_grad(hipStream_t stream, const StepParams &p, uint32_t waves, hipEvent_t start, hipEvent_t stop)
 {
     const bool has_v = p.momentum != 0.0f;
@@ -347,19 +347,19 @@ hipError_t launch_grad(hipStream_t stream, const StepParams &p, uint32_t waves, 
     constexpr bool FORMS_MEAN = MODE == kModeHead || MODE == kModeOnePass;
     if (!FORMS_MEAN) {                      // the caller's gradient: plain steps and steps that carry line 6
         if (grad == kGradExternal)
-            return has_v ? launch_one<true, kGradExternal, MODE, false, NWMAX, Q>(stream, p, waves, start, stop)
-                         : launch_one<false, kGradExternal, MODE, false, NWMAX, Q>(stream, p, waves, start, stop);
+            return has_v ? launch_one<true, kGradExternal, MODE, false, NWMAX, Q, AUX>(stream, p, waves, start, stop)
+                         : launch_one<false, kGradExternal, MODE, false, NWMAX, Q, AUX>(stream, p, waves, start, stop);
         if (grad == kGradExternalBf16)
-            return has_v ? launch_one<true, kGradExternalBf16, MODE, false, NWMAX, Q>(stream, p, waves, start, stop)
-                         : launch_one<false, kGradExternalBf16, MODE, false, NWMAX, Q>(stream, p, waves, start, stop);
+            return has_v ? launch_one<true, kGradExternalBf16, MODE, false, NWMAX, Q, AUX>(stream, p, waves, start, stop)
+                         : launch_one<false, kGradExternalBf16, MODE, false, NWMAX, Q, AUX>(stream, p, waves, start, stop);
     } else if (grad != kGradQuadNoisy && grad != kGradQuadExact) {
         return hipErrorInvalidValue;
     }
     if (grad == kGradQuadNoisy)
-        return has_v ? launch_one<true, kGradQuadNoisy, MODE, WEIGHTED, NWMAX, Q>(stream, p, waves, start, stop)
-                     : launch_one<false, kGradQuadNoisy, MODE, WEIGHTED, NWMAX, Q>(stream, p, waves, start, stop);
-    return has_v ? launch_one<true, kGradQuadExact, MODE, WEIGHTED, NWMAX, Q>(stream, p, waves, start, stop)
-                 : launch_one<false, kGradQuadExact, MODE, WEIGHTED, NWMAX, Q>(stream, p, waves, start, stop);
+        return has_v ? launch_one<true, kGradQuadNoisy, MODE, WEIGHTED, NWMAX, Q, AUX>(stream, p, waves, start, stop)
+                     : launch_one<false, kGradQuadNoisy, MODE, WEIGHTED, NWMAX, Q, AUX>(stream, p, waves, start, stop);
+    return has_v ? launch_one<true, kGradQuadExact, MODE, WEIGHTED, NWMAX, Q, AUX>(stream, p, waves, start, stop)
+                 : launch_one<false, kGradQuadExact, MODE, WEIGHTED, NWMAX, Q, AUX>(stream, p, waves, start, stop);
 }
 
 // Launch shapes (measured on MI355X, see the file header): single-wave blocks with one quad per lane
@@ -370,7 +370,8 @@ hipError_t launch_mode(hipStream_t stream, const StepParams &p, hipEvent_t start
 {
     constexpr bool FORMS_MEAN = MODE == kModeHead || MODE == kModeOnePass;
     if constexpr (!FORMS_MEAN) {
-        return launch_grad<MODE, false, 1, 1>(stream, p, 1, start, stop);
+        return p.cached ? launch_grad<MODE, false, 1, 1, kAuxCached>(stream, p, 1, start, stop)
+                        : launch_grad<MODE, false, 1, 1>(stream, p, 1, start, stop);
     } else {
         const uint32_t waves = p.W < 16u ? p.W : 16u;
         const int q = local_step_mean_quads_per_lane(p.W, MODE == kModeOnePass);
@@ -394,7 +395,8 @@ int local_step_mean_quads_per_lane(uint32_t W, bool one_pass)
 
 hipError_t launch_line6(hipStream_t stream, const StepParams &p)
 {
-    return launch_one<false, kGradQuadExact, kModeLine6, false, 1, 1>(stream, p, 1, nullptr, nullptr);
+    return p.cached ? launch_one<false, kGradQuadExact, kModeLine6, false, 1, 1, kAuxCached>(stream, p, 1, nullptr, nullptr)
+                    : launch_one<false, kGradQuadExact, kModeLine6, false, 1, 1, kAuxNonTemporal>(stream, p, 1, nullptr, nullptr);
 }
 
 hipError_t launch_local_step(hipStream_t stream, const StepParams &p, hipEvent_t start, hipEvent_t stop)

@@ -1,6 +1,6 @@
 // Device helpers shared by the local-step kernels: 16-byte vector types and streaming accesses
-// through raw buffer instructions.  Every model array is streamed once per step and is far larger
-// than the caches, so the accesses carry the non-temporal hint; the buffer descriptor covers exactly
+// through raw buffer instructions.  Every model array is streamed once per step; where the arrays are larger
+// than the caches the accesses carry the non-temporal hint.  The buffer descriptor covers exactly
 // the piece of the row a block (or wave) works on, so lanes past its end read zeros and their stores
 // are dropped by the hardware range check: no divergent tail code.
 #pragma once
@@ -12,20 +12,22 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u2 __attribute__((ext_vector_type(2)));
 
-constexpr int kAuxNonTemporal = 2;   // cache-policy bits of the buffer instructions: nt
+constexpr int kAuxNonTemporal = 2, kAuxCached = 0;   // cache-policy bits of the buffer instructions: nt, none
 
 // Raw buffer descriptor over `bytes` bytes starting at p (stride 0, 32-bit data format).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const float *p, uint32_t bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, static_cast<int>(bytes), 0x00020000);
 }
+template <int AUX>
 __device__ __forceinline__ f4 load_quad(__amdgpu_buffer_rsrc_t r, uint32_t byte_off)
 {
-    return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, static_cast<int>(byte_off), 0, kAuxNonTemporal));
+    return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, static_cast<int>(byte_off), 0, AUX));
 }
+template <int AUX>
 __device__ __forceinline__ void store_quad(__amdgpu_buffer_rsrc_t r, uint32_t byte_off, f4 a)
 {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, a), r, static_cast<int>(byte_off), 0, kAuxNonTemporal);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, a), r, static_cast<int>(byte_off), 0, AUX);
 }
 
 // Where the stochastic gradient G of a step comes from.
