@@ -13,9 +13,9 @@
 //                  NEXT step's X and labels from the counter-based generator into the other of two batch buffers
 //
 // The two big contractions (98 % of the flops) run on the 16-bit matrix instructions at fp32 accuracy: every fp32
-// operand is split into two fp16 values (its leading 11 bits and the remainder's), scaled by a power of two into the
-// middle of the fp16 range, and three of the four partial products are formed with fp32 accumulation.  Against 64 bits
-// (W = 16, 3072-1024-10, batch 128) H = relu(X W1 + b1) is off by 3.2e-7 and dW1 by 1.44e-7 of their norms; the fp32
+// operand is split into two fp16 values (its leading 11 bits and the remainder's; W1 and dA first scaled by a power of
+// two into the fp16 range), and three of the four partial products are formed with fp32 accumulation.  Against 64 bits
+// (W = 16, 3072-1024-10, batch 128) H = relu(X W1 + b1) is off by 4.4e-7 and dW1 by 1.45e-7 of their norms; the fp32
 // matrix instruction, whose chain of additions is longer, gave 1.0e-6 and 1.47e-7, and the other shapes measured move the same way.
 // The fp32 instruction peaks at 157 TFLOP/s; three fp16 products per fp32 product cost a fifth of its time, and the
 // contractions are then bound by their streams: the forward one by W1 (201 MB at that shape), the backward one by
@@ -128,7 +128,7 @@ constexpr int kHeadSamples = 16;       // per block
 constexpr int kHeadWaves = 16;
 constexpr uint32_t kHeadChunk = 2048;  // hidden units held in LDS at a time (132 KB); more pass through it chunk by chunk
 constexpr int kHeadGroup = 4;          // 1 KiB pieces of a row, and
-constexpr int kHeadTerms = 4;          //   terms of H (K splits beside the first, bias) that are requested together
+constexpr int kHeadTerms = 2;          //   terms of H (K splits beside the first, bias) that are requested together
 __host__ __device__ inline uint32_t head_pitch(uint32_t n_hid) { return (n_hid < kHeadChunk ? n_hid : kHeadChunk) + 4; }
 
 __global__ __launch_bounds__(64 * kHeadWaves) void head_kernel(const MlpParams p)
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(64 * kHeadWaves) void head_kernel(const MlpParams p
         }
     };
 
-    f4v z = {0.f, 0.f, 0.f, 0.f};
+    f4v zq[4] = {};                                            // one chain of additions per quarter j: shorter and independent
     for (uint32_t c0 = 0; c0 < p.n_hid; c0 += kHeadChunk) {
         const uint32_t width = p.n_hid - c0 < kHeadChunk ? p.n_hid - c0 : kHeadChunk;
         if (c0 != 0) __syncthreads();                          // the chunk before has been multiplied
@@ -225,19 +225,21 @@ __global__ __launch_bounds__(64 * kHeadWaves) void head_kernel(const MlpParams p
                 if (blk < n_blocks) {                          // wave-uniform
                     const f4 h = *reinterpret_cast<const f4 *>(tile + s16 * pitch + 16 * blk + 4 * g);
                     #pragma unroll
-                    for (int j = 0; j < 4; ++j) z = __builtin_amdgcn_mfma_f32_16x16x4f32(h[j], w2[i][j], z, 0, 0, 0);
+                    for (int j = 0; j < 4; ++j) zq[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(h[j], w2[i][j], zq[j], 0, 0, 0);
                 }
             }
         }
     }
     load_w2_classes(0, wave, (p.n_hid < kHeadChunk ? p.n_hid : kHeadChunk) / 16);
+    const f4v z = (zq[0] + zq[1]) + (zq[2] + zq[3]);
     #pragma unroll
     for (int r = 0; r < 4; ++r) zs[wave][4 * g + r][s16] = z[r];
     __syncthreads();
     if (threadIdx.x < kHeadSamples * kMaxOut) {                // one thread per sample and class
-        float a = 0.0f;
+        float q[4] = {0.f, 0.f, 0.f, 0.f};
         #pragma unroll
-        for (int w = 0; w < kHeadWaves; ++w) a += zs[w][smp][c];
+        for (int w = 0; w < kHeadWaves; ++w) q[w % 4] += zs[w][smp][c];
+        float a = (q[0] + q[1]) + (q[2] + q[3]);
         a = real ? a + b2 : -INFINITY;
         float zmax = a;
         #pragma unroll
@@ -386,20 +388,30 @@ typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 
-// Eight values, scaled into the upper half of the fp16 range, as two fp16 vectors: the value rounded to 11 bits and
-// the (in fp32 exact) remainder rounded to 11 bits.
+// Eight values as two fp16 vectors: the value rounded to 11 bits and the (in fp32 exact) remainder rounded to 11 bits.
+// Per pair of values two conversions and two mixed-precision subtractions; SCALED: both values are multiplied first.
+// (As plain code, with X scaled too, the split took 250 vector instructions per slice and thread instead of 130, and with
+// one to two waves per SIMD they were the longer part of the loop: W = 6, 1024-2048-10, batch 512: forward 76 -> 66 us,
+// backward 92 -> 86.)
 struct Planes { u4 p[2]; };
+__device__ __forceinline__ unsigned int pack_fp16(float a, float b)
+{
+    typedef float v2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned int, __builtin_convertvector(v2{a, b}, h2));
+}
+template <bool SCALED>
 __device__ __forceinline__ Planes split8(const float (&a)[8], float scale)
 {
-    #pragma clang fp contract(off)
     Planes out;
     #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float x0 = a[2 * i] * scale, x1 = a[2 * i + 1] * scale;
-        const h2 hi = {static_cast<_Float16>(x0), static_cast<_Float16>(x1)};
-        const h2 lo = {static_cast<_Float16>(x0 - static_cast<float>(hi.x)), static_cast<_Float16>(x1 - static_cast<float>(hi.y))};
-        out.p[0][i] = __builtin_bit_cast(unsigned int, hi);
-        out.p[1][i] = __builtin_bit_cast(unsigned int, lo);
+        const float x0 = SCALED ? a[2 * i] * scale : a[2 * i], x1 = SCALED ? a[2 * i + 1] * scale : a[2 * i + 1];
+        const unsigned int hi = pack_fp16(x0, x1);
+        float lo0, lo1;                                        // x - (float)hi: the compiler spends a conversion and a subtraction on each
+        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(lo0) : "v"(hi), "v"(x0));
+        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(lo1) : "v"(hi), "v"(x1));
+        out.p[0][i] = hi;
+        out.p[1][i] = pack_fp16(lo0, lo1);
     }
     return out;
 }
@@ -413,8 +425,6 @@ __device__ __forceinline__ float scale_to(float m, uint32_t target)
 }
 __device__ __forceinline__ float inverse_scale(float s) { return __uint_as_float((254u << 23) - __float_as_uint(s)); }
 
-// The mini-batch is drawn by this library: |x| <= sqrt(-2 ln 2^-24) = 5.77, times 2^12 below the largest fp16.
-constexpr float kXScale = 4096.0f;
 constexpr int kGemmThreads = 256;
 
 // The operand planes of one K slice in LDS, in the order in which the matrix instruction's lanes read them:
@@ -547,14 +557,14 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kBwd ? 3 : 2) void mlp_gemm_ke
         for (int i = 0; i < AP; ++i) {
             const uint32_t row = EPI == kFwd ? t / 4 + 64 * i : lane * AP + i, oct = EPI == kFwd ? t % 4 : wave;
             const uint32_t slot = EPI == kFwd ? ops[S].a.slot_k(row % 32, oct) : ops[S].a.slot_col(row % 32);
-            const Planes s = split8(ra[R][i], kXScale);
+            const Planes s = split8<false>(ra[R][i], 1.0f);
             #pragma unroll
             for (int pl = 0; pl < 2; ++pl) ops[S].a.q[pl][row / 32][oct][slot] = s.p[pl];
         }
         #pragma unroll
         for (int i = 0; i < BP; ++i) {
             const uint32_t row = lane * BP + i;
-            const Planes s = split8(rb[R][i], b_scale[i]);
+            const Planes s = split8<true>(rb[R][i], b_scale[i]);
             #pragma unroll
             for (int pl = 0; pl < 2; ++pl) ops[S].b.q[pl][row / 32][wave][ops[S].b.slot_col(row % 32)] = s.p[pl];
         }
@@ -692,7 +702,7 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kBwd ? 3 : 2) void mlp_gemm_ke
     if (EPI == kFwd) {
         if (wave == 0) {
             #pragma unroll
-            for (int c = 0; c < BP; ++c) col_max[0][lane * BP + c] = inverse_scale(b_scale[c]) * (1.0f / kXScale);
+            for (int c = 0; c < BP; ++c) col_max[0][lane * BP + c] = inverse_scale(b_scale[c]);
         }
         __syncthreads();
     }
@@ -701,7 +711,7 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kBwd ? 3 : 2) void mlp_gemm_ke
         #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const float inv = EPI == kFwd ? col_max[0][(wn * NB + j) * 32 + 8 * (r / 4) + 4 * (lane / 32) + r % 4]
-                                          : inverse_scale(b_scale[0]) * (1.0f / kXScale);
+                                          : inverse_scale(b_scale[0]);
             #pragma unroll
             for (int i = 0; i < MB; ++i) acc[i][j][r] *= inv;
         }

@@ -49,7 +49,8 @@ def test_contractions_and_small_gradients_against_64_bits(W, shape, batch):
         X, H, dA, dZ = ws["X"][i], ws["H"][i], ws["dA"][i], ws["dZ"][i]
         H64 = np.maximum(X @ W1 + b1, 0)
         assert np.all(np.abs(H - H64) <= bound(n_in, X, W1) + 2.0**-22 * (np.abs(b1) + np.abs(H64)))
-        assert np.all(np.abs(dA - np.where(H > 0, dZ @ W2.T, 0)) <= 2.0**-21 * (np.abs(dZ) @ np.abs(W2.T)))
+        # n_out products, each added with a rounding of at most 2^-24 of the partial sum (largest seen 8 x 2^-24 at 16)
+        assert np.all(np.abs(dA - np.where(H > 0, dZ @ W2.T, 0)) <= (n_out + 4) * 2.0**-24 * (np.abs(dZ) @ np.abs(W2.T)))
         assert np.all(np.abs(v[i, :a].reshape(n_in, n_hidden) - X.T @ dA) <= bound(batch, X.T, dA))
         small = (batch + 8) * 2.0**-24                       # a chain of fp32 additions over the batch
         assert np.all(np.abs(v[i, a:b] - dA.sum(0)) <= small * np.abs(dA).sum(0))
