@@ -34,9 +34,12 @@
 
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 namespace cocod {
 namespace {
 
+constexpr uint32_t kXcds = 8;      // accelerator complex dies of the MI355X, each with its own L2
 enum { kModePlain = 0, kModeTail = 1, kModeTailIn = 2, kModeHead = 3, kModeOnePass = 4, kModeLine6 = 5 };
 
 // Normals for the Q memory quads of one lane.  Quad u of lane l covers global indices
@@ -101,6 +104,13 @@ __global__ __launch_bounds__(64 * NWMAX) void local_step_kernel(const StepParams
         group = r / here;
         tile_id = first_tile + r % here;
         if (group >= n_groups) return;                       // block-uniform: padding of the short last panel
+    }
+    if (FORMS_MEAN && AUX == kAuxCached) {
+        // Rows off the 128-byte lines: a tile is the same columns of every worker, so it cannot move to the lines of
+        // each row.  An XCD owns a contiguous run of tiles instead, and with ordinary stores the halves of a line that
+        // neighbouring tiles write meet in its L2.
+        const uint32_t run = gridDim.x / kXcds;              // what does not divide stays in place at the end
+        if (tile_id < run * kXcds) tile_id = (tile_id % kXcds) * run + tile_id / kXcds;
     }
     const uint32_t chunk_id = tile_id / PARTS, part = tile_id % PARTS;
     const Chunk ck = p.table[chunk_id];
@@ -376,10 +386,21 @@ hipError_t launch_mode(hipStream_t stream, const StepParams &p, hipEvent_t start
         const uint32_t waves = p.W < 16u ? p.W : 16u;
         const int q = local_step_mean_quads_per_lane(p.W, MODE == kModeOnePass);
         if (q == 0) return hipErrorInvalidValue;
-        if (p.weights) return q == 2 ? launch_grad<MODE, true, 16, 2>(stream, p, waves, start, stop)
-                                     : launch_grad<MODE, true, 16, 1>(stream, p, waves, start, stop);
-        return q == 2 ? launch_grad<MODE, false, 16, 2>(stream, p, waves, start, stop)
-                      : launch_grad<MODE, false, 16, 1>(stream, p, waves, start, stop);
+        auto shape = [&](auto weighted, auto aux) {
+            constexpr bool WT = decltype(weighted)::value;
+            constexpr int AUX = decltype(aux)::value;
+            return q == 2 ? launch_grad<MODE, WT, 16, 2, AUX>(stream, p, waves, start, stop)
+                          : launch_grad<MODE, WT, 16, 1, AUX>(stream, p, waves, start, stop);
+        };
+        using Streaming = std::integral_constant<int, kAuxNonTemporal>;
+        using Cached = std::integral_constant<int, kAuxCached>;
+        // Rows off the 128-byte lines (see the kernel), streaming stores in plain order / ordinary ones XCD by XCD: mean-forming
+        // first step W = 4, d = 8 M 150 / 138 us, W = 16, d = 11.2 M 923 / 836, W = 64, d = 2 M 642 / 609; one pass W = 16
+        // 923 / 854, W = 8, d = 8 M 319 / 312, but W = 4 151 / 158.
+        const bool lines = p.W == 1 || (MODE == kModeOnePass && p.W < 8) ||
+                           ((reinterpret_cast<uintptr_t>(p.x_out) | p.stride * sizeof(float)) & 127u) == 0;
+        if (p.weights) return lines ? shape(std::true_type{}, Streaming{}) : shape(std::true_type{}, Cached{});
+        return lines ? shape(std::false_type{}, Streaming{}) : shape(std::false_type{}, Cached{});
     }
 }
 

@@ -64,3 +64,34 @@ def test_rows_off_the_lines_give_the_same_bits(sizes, kind, momentum):
     for extra in (4, 8, 16, 28):                     # three workers: leads of 0, -extra and -2 extra modulo 32
         got = rounds(sizes, extra, momentum, kind)
         assert all(torch.equal(a, b) for a, b in zip(got, want)), extra
+
+
+@pytest.mark.parametrize("workers", [3, 8, 17])
+@pytest.mark.parametrize("d", [5, 1025, 9000, 70_001])
+def test_mean_forming_steps_off_the_lines_give_the_same_bits(workers, d):
+    """Off the lines these steps take their tiles XCD by XCD, with another store policy; tiles in numbers that do and do
+    not divide by the eight dies, k = 1 (one pass) and k = 2 (mean in the first step)."""
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(d)
+    base = [torch.from_numpy(rng.standard_normal((workers, d)).astype(np.float32)).to(dev) for _ in range(4)]
+    want = None
+    for extra in (0, 4, 20):
+        stride = (d + 31) // 32 * 32 + extra
+        xA, v, h, c = [torch.zeros((workers, stride), device=dev) for _ in range(4)]
+        for t, src in zip((xA, v, h, c), base):
+            t[:, :d] = src
+        xB, mean = torch.zeros_like(xA), torch.zeros(stride, device=dev)
+        s = torch.cuda.Stream(device=dev)
+        torch.cuda.synchronize()
+        ctx = P.Context(W=workers, d=d, stride=stride, xA=xA, xB=xB, v=v, mean=mean, h=h, c=c, momentum=0.9, compute_stream=s,
+                        avg_stream=s, **HYPER)
+        ctx.set_schedule(P.SCHED_HEAD)
+        ctx.round_fused_tail(1)
+        ctx.round_fused_tail(2)
+        ctx.sync()
+        live = xA if ctx.live_model() == xA.data_ptr() else xB
+        got = [live[:, :d].cpu(), v[:, :d].cpu(), mean[:d].cpu()]
+        ctx.close()
+        if want is None:
+            want = got
+        assert all(torch.equal(a, b) for a, b in zip(got, want)), extra
