@@ -441,7 +441,7 @@ struct OperandTile {
 
 // BM x BN block tile, four waves of (BM/2) x (BN/2).
 template <int EPI, int BM, int BN>
-__global__ __launch_bounds__(kGemmThreads, EPI == kBwd ? 3 : 2) void mlp_gemm_kernel(const MlpParams p)
+__global__ __launch_bounds__(kGemmThreads, EPI == kFwd ? 2 : 3) void mlp_gemm_kernel(const MlpParams p)
 {
     constexpr int MB = BM / 64, NB = BN / 64;                  // 32-blocks per wave and direction
     constexpr int CPITCH = BN + 4;
@@ -608,7 +608,7 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kBwd ? 3 : 2) void mlp_gemm_ke
     const uint32_t tile_row = t / (BN / 4), tile_col = (t % (BN / 4)) * 4;
     const uint64_t row_at = o.W1 + static_cast<uint64_t>(m0 + tile_row) * p.n_hid + column(tile_col);
     const uint64_t tile_at = static_cast<uint64_t>(worker) * p.stride + row_at;
-    f4 x_old[EPI_ITERS], v_old[EPI_ITERS], snap_old[EPI_ITERS];
+    f4 x_old[EPI_ITERS], v_old[EPI_ITERS];
     auto prefetch_x = [&]() {
         #pragma unroll
         for (int it = 0; it < EPI_ITERS; ++it)
@@ -619,7 +619,6 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kBwd ? 3 : 2) void mlp_gemm_ke
         for (int it = 0; it < EPI_ITERS; ++it) {
             const uint64_t at = tile_at + static_cast<uint64_t>(it * ROWS_PER_PASS) * p.n_hid;
             v_old[it] = p.momentum != 0.0f ? __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p.v + at)) : f4{0.f, 0.f, 0.f, 0.f};
-            if (EPI == kBwdTail) snap_old[it] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p.snap + at));
         }
     };
 
@@ -758,6 +757,17 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kBwd ? 3 : 2) void mlp_gemm_ke
             for (int g = 0; g < 4; ++g)
                 *reinterpret_cast<f4 *>(&Ct[(wm * MB + i) * 32 + lane % 32][(wn * NB + j) * 32 + 8 * g + 4 * (lane / 32)]) =
                     f4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+    // line 6: the stored model and the mean, into the registers that the accumulators have just left (stored model requested
+    // with v, mean one quad at a time below: 203 us, like this 191, W = 16, 3072-1024-10)
+    f4 snap_old[EPI_ITERS], mean[EPI_ITERS];
+    if (EPI == kBwdTail) {
+        #pragma unroll
+        for (int it = 0; it < EPI_ITERS; ++it) {
+            const uint64_t down = static_cast<uint64_t>(it * ROWS_PER_PASS) * p.n_hid;
+            snap_old[it] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p.snap + tile_at + down));
+            mean[it] = *reinterpret_cast<const f4 *>(p.mean + row_at + down);
+        }
+    }
     __syncthreads();
     #pragma unroll
     for (int it = 0; it < EPI_ITERS; ++it) {
@@ -769,10 +779,7 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kBwd ? 3 : 2) void mlp_gemm_ke
             __builtin_nontemporal_store(g, reinterpret_cast<f4 *>(p.v + at));
         }
         f4 x_new = x_old[it] - p.lr * g;
-        if (EPI == kBwdTail) {       // line 6 of Algorithm 1 on the fresh model, same operation order as the separate kernel
-            const f4 mean = *reinterpret_cast<const f4 *>(p.mean + row_at + static_cast<uint64_t>(it * ROWS_PER_PASS) * p.n_hid);
-            x_new = mean + (x_new - snap_old[it]);
-        }
+        if (EPI == kBwdTail) x_new = mean[it] + (x_new - snap_old[it]);      // line 6 on the fresh model, same operation order as the separate kernel
         __builtin_nontemporal_store(x_new, reinterpret_cast<f4 *>(p.x_out + at));
     }
 }
