@@ -30,7 +30,6 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0           # MI355X published HBM3E bandwidth
-MFMA_F32_PEAK_TFLOPS = 157.3    # MI355X published dense fp32 matrix rate
 STEP_BYTES = 24                 # plain local step: read x, v, h, c; write x, v (fp32); 16 without momentum
 # HBM bytes per launch at C2 from two rocprofv3 --pmc runs (FETCH_SIZE x 2.000 + WRITE_SIZE x 0.999,
 # factors from the known-size copy kernel): profiles/kernels_C2_W16_d11.2M_hbm_counters.md, checked
@@ -464,8 +463,9 @@ def bench_quadratic(workload, k, variant, steps, warmup, full):
 
 
 def bench_mlp(k, variant, steps, warmup, full):
-    """C4: W=16 perceptron workers 3072-1024-10, batch 128: rounds/s, and the MFMA roofline of a
-    local step (the two big contractions are 2 * 2*B*in*hid flops per worker-step)."""
+    """C4: W=16 perceptron workers 3072-1024-10, batch 128: rounds/s, and the HBM roofline of a local step (the
+    contractions, 2 * 2*B*in*hid flops per worker-step, run on the 16-bit matrix instructions at fp32 accuracy and
+    are bound by their weight and update streams)."""
     import torch
     import paper_1906_12043_amd as P
     import synth_inputs
@@ -490,7 +490,6 @@ def bench_mlp(k, variant, steps, warmup, full):
     n_in, n_hid, n_out = shape
     gemm_flops = W * 2 * (2 * batch * n_in * n_hid)
     all_flops = gemm_flops + W * 3 * (2 * batch * n_hid * n_out)
-    achieved = gemm_flops / step_s / 1e12
     # HBM bytes a local step must move: the parameters and their momentum in and out (the update of every
     # parameter), the mini-batch written once and read by both contractions' first touch, H and dA once each way
     step_hbm_bytes = W * (16 * d + 4 * batch * (2 * n_in + 4 * n_hid))
@@ -506,10 +505,9 @@ def bench_mlp(k, variant, steps, warmup, full):
         "line6_step_ms": tail_s * 1e3 if tail_s else None,
         "local_step_TFLOPs_all": all_flops / step_s / 1e12,
         "local_step_hbm_GBps": step_hbm_bytes / step_s / 1e9,
-        "roofline": {"bound": "mfma", "kernel": "one local step (4 launches; mlp_gemm_kernel<fwd>, <bwd> carry the flops)",
-                     "achieved": achieved, "peak": MFMA_F32_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved / MFMA_F32_PEAK_TFLOPS, "traffic": None, "avg_launch_ms": step_s * 1e3,
-                     "launches_timed": steps * k, "algorithmic_flops_per_launch": gemm_flops},
+        "local_step_TFLOPs_contractions": gemm_flops / step_s / 1e12,
+        "roofline": roofline("one local step (3 launches: forward product, output layer, backward product with the update)",
+                             step_hbm_bytes, step_s, steps * k, None),
     }
     if full:
         other = "separate" if fused else "fused_tail"

@@ -21,8 +21,8 @@
  *     (cocod_create copies its small tables synchronously).
  *   - the caller owns all large device buffers and both streams; they must
  *     outlive the context.  The context owns its small tables (chunk table, weight and
- *     noise-scale vectors), two events, the MLP work space, the scratch of the
- *     diagnostics, and the recorded graphs with their step-counter word.
+ *     noise-scale vectors), two events, the MLP work space, the scratch and the pinned
+ *     result words of the diagnostics, and the recorded graphs with their step-counter word.
  *   - argument errors are detected before any GPU call is made.
  *   - a context is not thread safe; use it from one host thread at a time.
  */
@@ -86,9 +86,11 @@ enum {
  * of 1024 elements) and the end of the list rounded up to 4; see
  * cocod_plan_layout.  The elements in the gaps are pads: the local step and line 6
  * never touch them, the mean kernels may carry them along, and they never
- * influence real elements (their contents are unspecified).  For full memory
- * bandwidth choose stride as a multiple of 1024 elements, so that every
- * worker's row starts on a 4 KiB boundary as well (any multiple of 4 is legal).
+ * influence real elements (their contents are unspecified).  Any stride that is a
+ * multiple of 4 is legal.  For full memory bandwidth choose a multiple of 32
+ * elements (every worker's row then starts on a 128-byte line): the plain and line-6
+ * steps follow the lines of each row by themselves, the kernels that work on the
+ * same columns of all workers (mean, mean + line 6, mean-forming steps) cannot.
  */
 typedef struct cocod_config {
     uint32_t struct_size;          /* sizeof(cocod_config); checked */
@@ -341,7 +343,7 @@ int cocod_fill_quadratic(cocod_ctx *ctx);
  *   dZ [W][batch][*dz_pitch] gradient at the logits (first mlp_out entries of each row),
  *   y [W][batch] labels.
  * X and y are those of the most recent local step: the context keeps two mini-batch buffers (a step
- * draws the next step's batch into the other one while its output layer runs), so the two pointers
+ * draws the next step's batch into the other one beside its backward product), so the two pointers
  * change from step to step - ask again after each.
  */
 int cocod_mlp_workspace(const cocod_ctx *ctx, float **X, float **H, float **dA, float **dZ, int32_t **y,
