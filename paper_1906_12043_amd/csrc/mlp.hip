@@ -628,7 +628,7 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kFwd ? 2 : 3) void mlp_gemm_ke
     // leaves the range gives an infinity, and the block starts again with the true maximum of its columns at 2^14.
     using Set0 = std::integral_constant<int, 0>;
     using Set1 = std::integral_constant<int, 1>;
-    bool finite = true;
+    bool finite = true, infinite_operand = false;
     for (int attempt = 0; attempt < (EPI == kFwd ? 2 : 1); ++attempt) {
         load_slice(Set0{}, 0);
         if (SETS == 2) load_slice(Set1{}, 1);
@@ -654,7 +654,9 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kFwd ? 2 : 3) void mlp_gemm_ke
             #pragma unroll
             for (int c = 0; c < BP; ++c) {
                 const uint32_t n = lane * BP + c;
-                b_scale[c] = scale_to(fmaxf(fmaxf(col_max[0][n], col_max[1][n]), fmaxf(col_max[2][n], col_max[3][n])), attempt == 0 ? 6 : 14);
+                const float m = fmaxf(fmaxf(col_max[0][n], col_max[1][n]), fmaxf(col_max[2][n], col_max[3][n]));
+                infinite_operand |= m == INFINITY;
+                b_scale[c] = scale_to(m, attempt == 0 ? 6 : 14);
             }
         } else {
             float m = lane < p.batch / kHeadSamples ? p.dA_max[worker * (p.batch / kHeadSamples) + lane] : 0.0f;
@@ -662,6 +664,7 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kFwd ? 2 : 3) void mlp_gemm_ke
             for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
             #pragma unroll
             for (int c = 0; c < BP; ++c) b_scale[c] = scale_to(m, 14);
+            infinite_operand = m == INFINITY;
         }
         #pragma unroll
         for (int i = 0; i < MB; ++i)
@@ -714,9 +717,10 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kFwd ? 2 : 3) void mlp_gemm_ke
             #pragma unroll
             for (int i = 0; i < MB; ++i) acc[i][j][r] *= inv;
         }
-    if (!finite) {
-        // Infinities or NaN among the operands (or a product beyond fp32): with fp32 products throughout, which give
-        // inf, NaN or neither just as the fp32 arithmetic of the rest of the step.  Not a path that a run stays on.
+    if (!finite && __syncthreads_or(infinite_operand)) {
+        // Infinities among the operands (they split into inf and NaN): with fp32 products throughout, which give inf, NaN
+        // or neither just as the fp32 arithmetic of the rest of the step.  (A NaN operand alone needs nothing: its sums
+        // are NaN either way.)
         const uint32_t K0 = slice0 * kBK, K1 = K0 + n_slices * kBK;
         #pragma unroll
         for (int i = 0; i < MB; ++i)
