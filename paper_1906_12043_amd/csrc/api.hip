@@ -278,16 +278,9 @@ void release(cocod_ctx *ctx)
 // Step I arithmetic on `stream`, one launch per bucket.
 int enqueue_mean(cocod_ctx *ctx, hipStream_t stream)
 {
-    // Perceptron workers, mean on the averaging stream: the kernel beside it is the forward contraction, which
-    // needs a steady trickle of its weight stream and little bandwidth.  At full width the mean takes the memory
-    // system for its 43 us and the contraction loses 36 of them; in four single-wave blocks per compute unit it
-    // takes longer and the round is 15 us shorter (W = 16, 3072-1024-10, k = 2: 0.705 -> 0.690 ms; two blocks per
-    // unit: 0.700, one or eight: 0.709; k = 1, where the step waits for the mean: unchanged, 0.392 ms).
-    const uint32_t cap = ctx->cfg.grad == COCOD_GRAD_MLP && stream == ctx->s_avg && ctx->s_avg != ctx->s_compute
-                             ? 4u * ctx->compute_units : 0u;
     for (size_t b = 0; b + 1 < ctx->bucket_begin.size(); ++b)
         COCOD_HIP(ctx, cocod::launch_wmean(stream, ctx->snap, ctx->cfg.stride, ctx->cfg.W, ctx->bucket_begin[b],
-                                           ctx->bucket_begin[b + 1], ctx->d_weights, ctx->cfg.mean, cap));
+                                           ctx->bucket_begin[b + 1], ctx->d_weights, ctx->cfg.mean));
     return COCOD_OK;
 }
 
