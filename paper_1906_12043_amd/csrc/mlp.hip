@@ -717,7 +717,9 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kFwd ? 2 : 3) void mlp_gemm_ke
             #pragma unroll
             for (int i = 0; i < MB; ++i) acc[i][j][r] *= inv;
         }
-    if (!finite && __syncthreads_or(infinite_operand)) {
+    // Backward: an infinite dA anywhere in the worker takes the scale of all its tiles with it (2^-114, where the finite
+    // dA are zeros and their sums finite), so they are all formed again; the flag is the same in the whole block.
+    if (EPI == kFwd ? !finite && __syncthreads_or(infinite_operand) : infinite_operand) {
         // Infinities among the operands (they split into inf and NaN): with fp32 products throughout, which give inf, NaN
         // or neither just as the fp32 arithmetic of the rest of the step.  (A NaN operand alone needs nothing: its sums
         // are NaN either way.)

@@ -108,6 +108,26 @@ def test_infinities_and_nan_in_the_weights_go_where_fp32_takes_them():
     assert np.all(np.abs(H[:, rest] - np.maximum(X @ C1 + b1, 0)) <= bound(shape[0], X, C1) + 2.0**-21 * (1 + np.abs(b1)))
 
 
+def test_an_infinity_in_dA_leaves_the_other_columns_their_gradient():
+    """W2 = -inf at a unit that is active on every sample: its class never occurs (probability 0), the unit's column of
+    dA is inf where the class is the label and NaN elsewhere, every other dA is an ordinary number and so is its column
+    of the gradient of W1, in the tile of the infinite column and in the others."""
+    W, shape, batch = 1, (256, 384, 3), 128
+    n_in, n_hidden, n_out = shape
+    theta = theta_of(shape)
+    a, b = n_in * n_hidden, n_in * n_hidden + n_hidden
+    theta[a + 200] = 1e3                                         # active on every sample
+    theta[b + 200 * n_out + 1] = -np.inf
+    ws, v, _ = one_step(W, shape, batch, theta)
+    X, dA = ws["X"][0], ws["dA"][0]
+    assert np.isinf(dA[:, 200]).any() and np.isnan(dA[:, 200]).any()
+    rest = np.arange(n_hidden) != 200
+    assert np.isfinite(dA[:, rest]).all() and np.abs(dA[:, rest]).max() > 0
+    dW1 = v[0, :a].reshape(n_in, n_hidden)
+    assert np.isnan(dW1[:, 200]).all()
+    assert np.all(np.abs(dW1[:, rest] - X.T @ dA[:, rest]) <= bound(batch, X.T, dA[:, rest]))
+
+
 @pytest.mark.parametrize("shape,batch", [((128, 64, 3), 128), ((256, 256, 10), 256)])
 def test_every_row_alignment_gives_the_same_bits(shape, batch):
     """The update's tiles are counted from the first 128-byte line of a worker's row: whatever the row's offset, and
