@@ -398,9 +398,8 @@ int cocod_create(const cocod_config *cfg, cocod_ctx **out)
         if (e == hipSuccess && cfg->grad == COCOD_GRAD_MLP) {      // one work-space block, carved below
             const size_t wb = static_cast<size_t>(cfg->W) * cfg->mlp_batch;
             const size_t n_x = wb * cfg->mlp_in, n_h = wb * cfg->mlp_hidden, n_z = wb * cocod::mlp_dz_pitch();
-            const size_t n_m = cfg->W * cocod::mlp_max_groups(cfg->mlp_batch);
             const uint32_t splits = cocod::mlp_forward_splits(cfg->W, cfg->mlp_in, cfg->mlp_hidden, cfg->mlp_batch, ctx->compute_units);
-            e = hipMalloc(reinterpret_cast<void **>(&ctx->mlp_ws), (2 * n_x + (1 + splits) * n_h + n_z + 2 * wb + n_m) * sizeof(float));
+            e = hipMalloc(reinterpret_cast<void **>(&ctx->mlp_ws), (2 * n_x + (1 + splits) * n_h + n_z + 2 * wb) * sizeof(float));
             if (e == hipSuccess) {
                 float *at = ctx->mlp_ws;
                 ctx->mlp_X[0] = at; at += n_x;
@@ -411,8 +410,7 @@ int cocod_create(const cocod_config *cfg, cocod_ctx **out)
                 ctx->mlp.dA = at; at += n_h;
                 ctx->mlp.dZ = at; at += n_z;
                 ctx->mlp_y[0] = reinterpret_cast<int32_t *>(at); at += wb;
-                ctx->mlp_y[1] = reinterpret_cast<int32_t *>(at); at += wb;
-                ctx->mlp.dA_max = at;
+                ctx->mlp_y[1] = reinterpret_cast<int32_t *>(at);
                 ctx->mlp.X = ctx->mlp_X[0];
                 ctx->mlp.y = ctx->mlp_y[0];
             }

@@ -109,14 +109,12 @@ struct MlpParams {
     float *H_part;            // [fwd_splits - 1][W][batch][n_hid]  the other K splits
     uint32_t fwd_splits;      // mlp_forward_splits of the shape
     float *dA;                // [W][batch][n_hid]  gradient at the hidden pre-activation
-    float *dA_max;            // [W][mlp_max_groups(batch)]  largest |dA| of each group of samples
     float *dZ;                // [W][batch][mlp_dz_pitch()]  gradient at the logits
     int32_t *y;               // [W][batch] labels
 };
 
 bool mlp_shape_supported(uint32_t n_in, uint32_t n_hid, uint32_t n_out, uint32_t batch);
 size_t mlp_dz_pitch();
-size_t mlp_max_groups(uint32_t batch);
 // K splits of the forward product (chosen once per context: their sums need work space)
 uint32_t mlp_forward_splits(uint32_t W, uint32_t n_in, uint32_t n_hid, uint32_t batch, uint32_t compute_units);
 // start / stop (may be null) receive the start timestamp of the step's first kernel and the end timestamp of its last

@@ -13,18 +13,22 @@
 //                  NEXT step's X and labels from the counter-based generator into the other of two batch buffers
 //
 // The two big contractions (98 % of the flops) run on the 16-bit matrix instructions at fp32 accuracy: every fp32
-// operand is split into two fp16 values (its leading 11 bits and the remainder's; W1 and dA first scaled by a power of
-// two into the fp16 range), and three of the four partial products are formed with fp32 accumulation.  Against 64 bits
-// (W = 16, 3072-1024-10, batch 128) H = relu(X W1 + b1) is off by 4.4e-7 and dW1 by 1.45e-7 of their norms; the fp32
-// matrix instruction, whose chain of additions is longer, gave 1.0e-6 and 1.47e-7, and the other shapes measured move the same way.
-// The fp32 instruction peaks at 157 TFLOP/s; three fp16 products per fp32 product cost a fifth of its time, and the
-// contractions are then bound by their streams: the forward one by W1 (201 MB at that shape), the backward one by
-// its fused update (805 MB).
+// operand is split exactly into three bf16 values (8 + 8 + 8 bits), and six of the nine partial products are formed with
+// fp32 accumulation; the three left out are below 2^-24 of the product together.  The leading products and the small ones
+// have accumulators of their own, so the long chain of additions has one rounding per 16 products.  Against 64 bits
+// (W = 16, 3072-1024-10, batch 128) H = relu(X W1 + b1) is off by 2.4e-7 and dW1 by 5.9e-8 of their norms; the fp32 matrix
+// instruction gave 1.0e-6 and 1.46e-7.  Columns far below the others, sums of one term and operands down to the
+// smallest fp32 numbers are as exact.  (fp16 pairs with three products are half the matrix work, forward 61 us against 93,
+// backward 143 against 160 at that shape, but hold 22 bits and need scales: a sum of one term was off by up to 2^-11, a
+// column of dA 2^-45 of the largest was lost.)
+// The fp32 instruction peaks at 157 TFLOP/s; six bf16 products per fp32 product cost two fifths of its time.
 //
-// GEMM kernel: 256 threads, four waves of 64 x 64 (forward, 128 x 128 block tile) or 32 x 64 (backward, 64 x 128).
-// K goes through LDS in slices of 32, two buffers and one barrier per slice: a slice is loaded as fp32, split
-// in registers on its way into LDS and read back as 16-byte operand pieces.  Neither operand needs to be K-contiguous
-// in memory: a thread stages 8 consecutive k of its row or column, so no transposed copy is ever written.
+// GEMM kernel: 256 threads, four waves, each with 32 columns of the block's tile and all of its rows (128 forward,
+// 64 backward).  A (the mini-batch) goes through LDS in slices of K = 32, two buffers and one barrier per slice: loaded as
+// fp32, split in registers on its way into LDS, read back as 16-byte operand pieces by every wave.  B (W1 or dA) belongs to
+// one wave alone: eight consecutive k of a column per lane, straight from memory into the operand registers.  (With both
+// operands in LDS the backward product's reads took longer than its multiplies: W = 6, 1024-2048-10, batch 512, 115 us
+// against 108, the forward one 102 against 88.)  No transposed copy is ever written.
 #include "internal.hpp"
 #include "philox.hpp"
 
@@ -116,7 +120,7 @@ __device__ __forceinline__ float wave_sum(float v)
 
 // Output layer, forward and backward, for sixteen samples of one worker per block:
 //   H = relu(sum of the forward product's K splits + b1), Z = H W2 + b2, softmax (row maximum subtracted),
-//   dZ = (P - onehot(y)) / batch, dA = (dZ W2^T) * [H > 0], and the largest |dA| of the block.
+//   dZ = (P - onehot(y)) / batch, dA = (dZ W2^T) * [H > 0].
 // Memory is touched a row at a time: a wave takes one sample's row in 1 KiB pieces and puts it into LDS, and dA leaves
 // the same way (reading the rows straight into the products' operand layout, 64 bytes from each of 16 rows 4 KiB
 // apart, took 25 us instead of 17 us at W = 16, 3072-1024-10, batch 128, four K splits).  Both products run on the fp32 matrix
@@ -137,7 +141,6 @@ __global__ __launch_bounds__(64 * kHeadWaves) void head_kernel(const MlpParams p
     extern __shared__ __attribute__((aligned(16))) float tile[];                // [kHeadSamples][head_pitch]: a chunk of H, then of dA
     __shared__ float zs[kHeadWaves][kHeadSamples][kMaxOut];
     __shared__ float dzs[kHeadSamples][kMaxOut + 1];
-    __shared__ float wave_max[kHeadWaves];
     const uint32_t worker = blockIdx.y, group = blockIdx.x, pitch = head_pitch(p.n_hid);
     const uint32_t lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     const uint32_t s16 = lane % 16, g = lane / 16;
@@ -257,7 +260,6 @@ __global__ __launch_bounds__(64 * kHeadWaves) void head_kernel(const MlpParams p
     #pragma unroll
     for (int q = 0; q < kMaxOut / 4; ++q) dz[q] = dzs[s16][4 * q + g];
     const uint32_t steps = (p.n_out + 3) / 4;
-    float most = 0.0f;
     float *dArow = p.dA + sample * p.n_hid;
     for (uint32_t c0 = 0; c0 < p.n_hid; c0 += kHeadChunk) {
         const uint32_t width = p.n_hid - c0 < kHeadChunk ? p.n_hid - c0 : kHeadChunk;
@@ -287,18 +289,8 @@ __global__ __launch_bounds__(64 * kHeadWaves) void head_kernel(const MlpParams p
         for (uint32_t n = 4 * lane; n < width; n += 256) {
             const f4 a = *reinterpret_cast<const f4 *>(tile + wave * pitch + n);
             *reinterpret_cast<f4 *>(dArow + c0 + n) = a;
-            most = fmaxf(most, fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))));
         }
         if (c0 + kHeadChunk < p.n_hid) __syncthreads();
-    }
-    #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) most = fmaxf(most, __shfl_xor(most, off, 64));
-    if (lane == 0) wave_max[wave] = most;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        #pragma unroll
-        for (int w = 1; w < kHeadWaves; ++w) most = fmaxf(most, wave_max[w]);
-        p.dA_max[worker * gridDim.x + group] = most;
     }
 }
 
@@ -385,72 +377,63 @@ __device__ __forceinline__ void small_update_block(const MlpParams &p, uint32_t 
 enum { kFwd = 0, kBwd = 1, kBwdTail = 2 };   // kBwdTail: the backward product of a round's last step (line 6 in its epilogue)
 
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef __bf16 h2 __attribute__((ext_vector_type(2)));
+typedef __bf16 h8 __attribute__((ext_vector_type(8)));
 
-// Eight values as two fp16 vectors: the value rounded to 11 bits and the (in fp32 exact) remainder rounded to 11 bits.
-// Per pair of values two conversions and two mixed-precision subtractions; SCALED: both values are multiplied first.
-// (As plain code, with X scaled too, the split took 250 vector instructions per slice and thread instead of 130, and with
-// one to two waves per SIMD they were the longer part of the loop: W = 6, 1024-2048-10, batch 512: forward 76 -> 66 us,
-// backward 92 -> 86.)
-struct Planes { u4 p[2]; };
-__device__ __forceinline__ unsigned int pack_fp16(float a, float b)
+// Eight values as three bf16 vectors: the value rounded to 8 bits, the remainder rounded to 8 bits, and what is left, at
+// most 8 bits.  Exact where the last bit of the value is a normal bf16, 2^-126: B is scaled so that this holds for the
+// smallest fp32 number, and values below 2^104 still have room above.  (X needs no scale: normals of 24-bit uniforms, zero
+// or above 1e-12.)
+constexpr float kScale = 0x1p24f, kUnscale = 0x1p-24f;
+struct Planes { u4 p[3]; };
+__device__ __forceinline__ unsigned int pack_bf16(float a, float b)
 {
     typedef float v2 __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(unsigned int, __builtin_convertvector(v2{a, b}, h2));
 }
 template <bool SCALED>
-__device__ __forceinline__ Planes split8(const float (&a)[8], float scale)
+__device__ __forceinline__ Planes split8(const float (&a)[8])
 {
     Planes out;
     #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float x0 = SCALED ? a[2 * i] * scale : a[2 * i], x1 = SCALED ? a[2 * i + 1] * scale : a[2 * i + 1];
-        const unsigned int hi = pack_fp16(x0, x1);
-        float lo0, lo1;                                        // x - (float)hi: the compiler spends a conversion and a subtraction on each
-        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(lo0) : "v"(hi), "v"(x0));
-        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(lo1) : "v"(hi), "v"(x1));
-        out.p[0][i] = hi;
-        out.p[1][i] = pack_fp16(lo0, lo1);
+        float x0 = SCALED ? a[2 * i] * kScale : a[2 * i], x1 = SCALED ? a[2 * i + 1] * kScale : a[2 * i + 1];
+        #pragma unroll
+        for (int pl = 0; pl < 3; ++pl) {
+            const unsigned int pair = pack_bf16(x0, x1);
+            out.p[pl][i] = pair;
+            x0 -= __uint_as_float(pair << 16);
+            x1 -= __uint_as_float(pair & 0xffff0000u);
+        }
     }
     return out;
 }
 
-// The power of two that takes a value of magnitude m to [2^target, 2^(target+1)); kept where it and its inverse
-// are normal numbers.
-__device__ __forceinline__ float scale_to(float m, uint32_t target)
-{
-    const uint32_t f = 254u + target - (__float_as_uint(m) >> 23);
-    return __uint_as_float((f < 240u ? f : 240u) << 23);
-}
-__device__ __forceinline__ float inverse_scale(float s) { return __uint_as_float((254u << 23) - __float_as_uint(s)); }
-
 constexpr int kGemmThreads = 256;
 
-// The operand planes of one K slice in LDS, in the order in which the matrix instruction's lanes read them:
-// [plane][32-row block][k octet][slot] pieces of 16 bytes (8 consecutive k of one row or column).  A fragment read is
-// then 1 KiB contiguous per wave.  The slot of a row is chosen so that the eight lanes that write together also hit
-// eight different 16-byte bank groups: rows staged column-wise (two adjacent rows per thread) swap neighbours in
-// every other group of eight, rows staged k-wise (four octets of one row in four lanes) rotate by the octet.
+// The planes of A's K slice in LDS, in the order in which the matrix instruction's lanes read them:
+// [plane][32-row block][k octet][slot] pieces of 16 bytes (8 consecutive k of one row).  A fragment read is then 1 KiB
+// contiguous per wave.  The slot of a row is chosen so that the eight lanes that write together also hit eight different
+// 16-byte bank groups: a wave that stages one octet of 64 rows does so as it is, rows staged k-wise (four octets of one
+// row in four lanes) rotate by the octet.
 template <int ROWS>
 struct OperandTile {
-    u4 q[2][ROWS / 32][4][32];
-    static __device__ __forceinline__ uint32_t slot_col(uint32_t r) { return r ^ ((r >> 3) & 1u); }
-    static __device__ __forceinline__ uint32_t slot_k(uint32_t r, uint32_t o) { return (r + 2 * o) & 31u; }
+    u4 q[3][ROWS / 32][4][32];
 };
+template <int EPI>
+__device__ __forceinline__ uint32_t slot_of(uint32_t r, uint32_t octet) { return EPI == kFwd ? (r + 2 * octet) & 31u : r; }
 
-// BM x BN block tile, four waves of (BM/2) x (BN/2).
+// BM x BN block tile, four waves, each 32 columns of BN and all of BM (half of it where BN is 64).
 template <int EPI, int BM, int BN>
-__global__ __launch_bounds__(kGemmThreads, EPI == kFwd ? 2 : 3) void mlp_gemm_kernel(const MlpParams p)
+__global__ __launch_bounds__(kGemmThreads, 2) void mlp_gemm_kernel(const MlpParams p)
 {
-    constexpr int MB = BM / 64, NB = BN / 64;                  // 32-blocks per wave and direction
+    constexpr int NWN = BN / 32, NWM = 4 / NWN, MB = BM / 32 / NWM;      // waves per direction, 32-row blocks per wave
     constexpr int CPITCH = BN + 4;
-    struct Operands { OperandTile<BM> a; OperandTile<BN> b; };
-    constexpr int OPERANDS = 2 * sizeof(Operands), TILE = EPI == kFwd ? 0 : BM * CPITCH * 4;
+    constexpr int OPERANDS = 2 * sizeof(OperandTile<BM>), TILE = EPI == kFwd ? 0 : BM * CPITCH * 4;
+    static_assert(EPI == kFwd || BM == 64, "a lane stages one row");
     static_assert(EPI == kFwd || OPERANDS >= static_cast<int>(sizeof(SmallUpdateLds)), "the small update's sums fit");
     __shared__ __attribute__((aligned(16))) unsigned char smem[OPERANDS > TILE ? OPERANDS : TILE];
-    __shared__ float col_max[EPI == kFwd ? 4 : 1][EPI == kFwd ? BN : 1];
-    Operands *ops = reinterpret_cast<Operands *>(smem);                                            // two buffers
+    OperandTile<BM> *ops = reinterpret_cast<OperandTile<BM> *>(smem);                              // two buffers
     float (*Ct)[CPITCH] = reinterpret_cast<float (*)[CPITCH]>(smem);                               // epilogue tile
 
     // Workgroups go to the 8 XCDs (each with its own L2) round-robin by linear id.  Renumber them so
@@ -470,7 +453,7 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kFwd ? 2 : 3) void mlp_gemm_ke
     uint32_t bx, by, bz;
     if (EPI == kBwdTail && ny % kXcds == 0) {
         // the mean is read by every worker: an XCD owns the same eighth of the rows of W1 for all of them
-        // (222 -> 206 us at W = 16, 3072-1024-10)
+        // (222 -> 206 us at W = 16, 3072-1024-10; measured, like the two figures at the epilogue, with half the products)
         const uint32_t rows = ny / kXcds, r = linear / kXcds;
         bx = r % nx;
         by = (linear % kXcds) * rows + (r / nx) % rows;
@@ -488,11 +471,13 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kFwd ? 2 : 3) void mlp_gemm_ke
     const uint32_t ldb = p.n_hid;
     const float *Xw = p.X + static_cast<uint64_t>(worker) * p.batch * p.n_in;
 
-    // Global -> register staging of one K slice: 8 consecutive k of one row or column per piece.
+    // Global -> registers, one K slice: 8 consecutive k of one row or column per piece.
     //   forward : A = X [batch][n_in], K-contiguous: lane t takes octet t % 4 of row t / 4 (+ 64)
-    //   backward: A = X^T, read from X M-contiguous: wave w takes octet w, lane l its BM/64 columns
-    //   B       : K-major (W1 rows, or dA rows): wave w takes octet w, lane l its BN/64 columns
-    constexpr int AP = BM / 64, BP = BN / 64;                  // pieces per thread
+    //   backward: A = X^T, read from X M-contiguous: wave w takes octet w, lane l row l of the tile
+    //   B       : K-major (W1 rows, or dA rows), as the matrix instruction wants it: lane l has column l % 32 of its
+    //             wave, octets l / 32 and 2 + l / 32
+    constexpr int AP = BM / 64;                                // pieces of A per thread
+    const uint32_t wm = wave / NWN, wn = wave % NWN;           // wave owns rows 32 MB wm .., columns 32 wn ..
     const float *a_src, *b_base, *b_src;
     uint32_t slice0 = 0, n_slices;                             // this block's K slices: an even number, at least two
     if (EPI == kFwd) {
@@ -503,7 +488,7 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kFwd ? 2 : 3) void mlp_gemm_ke
         b_base = p.x_in + static_cast<uint64_t>(worker) * p.stride + o.W1;                // W1 [n_in][n_hid]
     } else {
         n_slices = p.batch / kBK;
-        a_src = Xw + static_cast<uint64_t>(wave) * 8 * p.n_in + m0 + lane * AP;
+        a_src = Xw + static_cast<uint64_t>(wave) * 8 * p.n_in + m0 + lane;
         b_base = p.dA + static_cast<uint64_t>(worker) * p.batch * p.n_hid;                // dA [batch][n_hid]
     }
     // Columns of this block's tile.  The update streams x, v (and the stored model) in rows of BN floats, and rows that
@@ -516,26 +501,10 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kFwd ? 2 : 3) void mlp_gemm_ke
         first_col += static_cast<uint32_t>(-at & 31u);
     }
     auto column = [&](uint32_t c) { const uint32_t n = first_col + c; return n < p.n_hid ? n : n - p.n_hid; };
-    b_src = b_base + static_cast<uint64_t>(wave) * 8 * ldb + column(lane * BP);
+    b_src = b_base + static_cast<uint64_t>(lane / 32) * 8 * ldb + column(wn * 32 + lane % 32);
 
-    // forward: two sets of staging registers, global loads run two K slices ahead of their use; backward: one, the
-    // registers belong to the update's loads
-    constexpr int SETS = EPI == kFwd ? 2 : 1;
-    float ra[SETS][AP][8], rb[SETS][BP][8];
-    auto load_cols = [&](auto &r, const float *src, uint64_t ld) {      // 8 rows x (1 or 2) columns
-        constexpr int C = sizeof(r) / sizeof(r[0]);
-        #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if constexpr (C == 2) {
-                const float2 q = *reinterpret_cast<const float2 *>(src + j * ld);
-                r[0][j] = q.x; r[1][j] = q.y;
-            } else {
-                r[0][j] = src[j * ld];
-            }
-        }
-    };
-    auto load_slice = [&](auto set, uint32_t slice) {
-        constexpr int S = decltype(set)::value % SETS;
+    float ra[AP][8], rb[2][8];
+    auto load_slice = [&](uint32_t slice) {
         const uint64_t s = slice0 + slice;
         if (EPI == kFwd) {
             #pragma unroll
@@ -543,60 +512,60 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kFwd ? 2 : 3) void mlp_gemm_ke
                 const float *src = a_src + s * kBK + static_cast<uint64_t>(i) * 64 * p.n_in;
                 const f4 lo = *reinterpret_cast<const f4 *>(src), hi = *reinterpret_cast<const f4 *>(src + 4);
                 #pragma unroll
-                for (int j = 0; j < 4; ++j) { ra[S][i][j] = lo[j]; ra[S][i][4 + j] = hi[j]; }
+                for (int j = 0; j < 4; ++j) { ra[i][j] = lo[j]; ra[i][4 + j] = hi[j]; }
             }
         } else {
-            load_cols(ra[S], a_src + s * kBK * p.n_in, p.n_in);
+            #pragma unroll
+            for (int j = 0; j < 8; ++j) ra[0][j] = a_src[(s * kBK + j) * p.n_in];
         }
-        load_cols(rb[S], b_src + s * kBK * ldb, ldb);
+        #pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+            #pragma unroll
+            for (int j = 0; j < 8; ++j) rb[kb][j] = b_src[(s * kBK + 16 * kb + j) * ldb];
     };
-    float b_scale[BP];
-    auto stage_slice = [&](auto set) {                          // register set s -> LDS buffer s
-        constexpr int S = decltype(set)::value, R = S % SETS;
+    float largest = 0.0f;                                       // |b|, a NaN not counted
+    Planes bp[2];
+    auto stage_slice = [&](auto buffer) {                       // A -> LDS buffer, B -> operand registers
+        constexpr int S = decltype(buffer)::value;
         #pragma unroll
         for (int i = 0; i < AP; ++i) {
-            const uint32_t row = EPI == kFwd ? t / 4 + 64 * i : lane * AP + i, oct = EPI == kFwd ? t % 4 : wave;
-            const uint32_t slot = EPI == kFwd ? ops[S].a.slot_k(row % 32, oct) : ops[S].a.slot_col(row % 32);
-            const Planes s = split8<false>(ra[R][i], 1.0f);
+            const uint32_t row = EPI == kFwd ? t / 4 + 64 * i : lane, oct = EPI == kFwd ? t % 4 : wave;
+            const uint32_t slot = slot_of<EPI>(row % 32, oct);
+            const Planes s = split8<false>(ra[i]);
             #pragma unroll
-            for (int pl = 0; pl < 2; ++pl) ops[S].a.q[pl][row / 32][oct][slot] = s.p[pl];
+            for (int pl = 0; pl < 3; ++pl) ops[S].q[pl][row / 32][oct][slot] = s.p[pl];
         }
         #pragma unroll
-        for (int i = 0; i < BP; ++i) {
-            const uint32_t row = lane * BP + i;
-            const Planes s = split8<true>(rb[R][i], b_scale[i]);
+        for (int kb = 0; kb < 2; ++kb) {
             #pragma unroll
-            for (int pl = 0; pl < 2; ++pl) ops[S].b.q[pl][row / 32][wave][ops[S].b.slot_col(row % 32)] = s.p[pl];
+            for (int j = 0; j < 8; j += 2) largest = fmaxf(fmaxf(largest, fabsf(rb[kb][j])), fabsf(rb[kb][j + 1]));
+            bp[kb] = split8<true>(rb[kb]);
         }
     };
 
     // The product is formed transposed (W1 columns as the instruction's rows): a lane then holds four consecutive
-    // columns of one row of the result.  The product of the two remainders (2^-22 of the whole at most) is left out;
-    // the small products are added first.
-    const uint32_t wm = wave % 2, wn = wave / 2;                // wave owns rows (BM/2) wm .., columns (BN/2) wn ..
-    f16v acc[MB][NB];
-    auto multiply_slice = [&](auto set) {
-        constexpr int S = decltype(set)::value;
+    // columns of one row of the result.
+    // (One accumulator for all six products: dW1 is off by 1.72e-7 instead of 5.9e-8 at W = 16, 3072-1024-10, batch 128.)
+    f16v acc[MB], low[MB];                                      // leading products, the others
+    auto multiply_slice = [&](auto buffer) {
+        constexpr int S = decltype(buffer)::value;
         #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
             const uint32_t oct = 2 * kb + lane / 32, r = lane % 32;
-            const uint32_t slot_a = EPI == kFwd ? ops[S].a.slot_k(r, oct) : ops[S].a.slot_col(r), slot_b = ops[S].b.slot_col(r);
-            h8 a[2][MB], b[2][NB];
+            const uint32_t slot = slot_of<EPI>(r, oct);
+            h8 a[3][MB];
             #pragma unroll
-            for (int pl = 0; pl < 2; ++pl) {
+            for (int i = 0; i < MB; ++i)
                 #pragma unroll
-                for (int i = 0; i < MB; ++i) a[pl][i] = __builtin_bit_cast(h8, ops[S].a.q[pl][wm * MB + i][oct][slot_a]);
-                #pragma unroll
-                for (int j = 0; j < NB; ++j) b[pl][j] = __builtin_bit_cast(h8, ops[S].b.q[pl][wn * NB + j][oct][slot_b]);
-            }
-            constexpr int PA[3] = {1, 0, 0}, PB[3] = {0, 1, 0};
+                for (int pl = 0; pl < 3; ++pl) a[pl][i] = __builtin_bit_cast(h8, ops[S].q[pl][wm * MB + i][oct][slot]);
+            constexpr int PA[6] = {0, 2, 1, 0, 1, 0}, PB[6] = {2, 0, 1, 1, 0, 0};
             #pragma unroll
-            for (int q = 0; q < 3; ++q)
+            for (int q = 0; q < 6; ++q)
                 #pragma unroll
-                for (int i = 0; i < MB; ++i)
-                    #pragma unroll
-                    for (int j = 0; j < NB; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(b[PB[q]][j], a[PA[q]][i], acc[i][j], 0, 0, 0);
+                for (int i = 0; i < MB; ++i) {
+                    f16v &to = q < 5 ? low[i] : acc[i];
+                    to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(h8, bp[kb].p[PB[q]]), a[PA[q]][i], to, 0, 0, 0);
+                }
         }
     };
 
@@ -622,121 +591,75 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kFwd ? 2 : 3) void mlp_gemm_ke
         }
     };
 
-    // The scale of the B operand.  Backward: the largest |dA| of the worker (found by the output-layer kernel) goes to
-    // 2^14.  Forward: W1 is the caller's and nothing is known of it, so every column takes its scale from the first 32
-    // of its elements that this block reads (the largest goes to 2^6, a thousandth of the range); a column that later
-    // leaves the range gives an infinity, and the block starts again with the true maximum of its columns at 2^14.
-    using Set0 = std::integral_constant<int, 0>;
-    using Set1 = std::integral_constant<int, 1>;
-    bool finite = true, infinite_operand = false;
-    for (int attempt = 0; attempt < (EPI == kFwd ? 2 : 1); ++attempt) {
-        load_slice(Set0{}, 0);
-        if (SETS == 2) load_slice(Set1{}, 1);
-        if (EPI != kFwd && p.X_next) {
-            // The NEXT local step's mini-batch is drawn here, a share per block, into the other batch buffer: vector
-            // arithmetic under the latency of the first operand loads.
-            const uint32_t step = p.step_base ? *p.step_base + p.step : p.step, per_worker = gen_batch_blocks(p);
-            for (uint32_t id = linear; id < per_worker * p.W; id += total)
-                gen_batch_block(p, id % per_worker, t, id / per_worker, step + 1, p.X_next, p.y_next);
-        }
-        if (EPI == kFwd) {
-            #pragma unroll
-            for (int c = 0; c < BP; ++c) {
-                float m = 0.0f;
-                #pragma unroll
-                for (int j = 0; j < 8; ++j) m = fmaxf(m, fabsf(rb[0][c][j]));
-                if (attempt != 0)
-                    for (uint32_t k = slice0 * kBK + wave; k < (slice0 + n_slices) * kBK; k += 4)
-                        m = fmaxf(m, fabsf(b_base[static_cast<uint64_t>(k) * ldb + n0 + lane * BP + c]));
-                col_max[wave][lane * BP + c] = m;
-            }
-            __syncthreads();
-            #pragma unroll
-            for (int c = 0; c < BP; ++c) {
-                const uint32_t n = lane * BP + c;
-                const float m = fmaxf(fmaxf(col_max[0][n], col_max[1][n]), fmaxf(col_max[2][n], col_max[3][n]));
-                infinite_operand |= m == INFINITY;
-                b_scale[c] = scale_to(m, attempt == 0 ? 6 : 14);
-            }
-        } else {
-            float m = lane < p.batch / kHeadSamples ? p.dA_max[worker * (p.batch / kHeadSamples) + lane] : 0.0f;
-            #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-            #pragma unroll
-            for (int c = 0; c < BP; ++c) b_scale[c] = scale_to(m, 14);
-            infinite_operand = m == INFINITY;
-        }
-        #pragma unroll
-        for (int i = 0; i < MB; ++i)
-            #pragma unroll
-            for (int j = 0; j < NB; ++j) acc[i][j] = f16v{0};
-        for (uint32_t s = 0; s + 2 < n_slices; s += 2) {      // one barrier per slice: waves stage one buffer while others multiply the other
-            stage_slice(Set0{});
-            load_slice(Set0{}, s + SETS);
-            __syncthreads();
-            multiply_slice(Set0{});
-            stage_slice(Set1{});
-            load_slice(Set1{}, s + SETS + 1);
-            __syncthreads();
-            multiply_slice(Set1{});
-        }
-        stage_slice(Set0{});
-        if (SETS == 1) load_slice(Set1{}, n_slices - 1);
-        if (EPI != kFwd) prefetch_x();
-        __syncthreads();
-        multiply_slice(Set0{});
-        stage_slice(Set1{});
-        if (EPI != kFwd) prefetch_v();
-        __syncthreads();
-        multiply_slice(Set1{});
-
-        bool mine = true;
-        #pragma unroll
-        for (int i = 0; i < MB; ++i)
-            #pragma unroll
-            for (int j = 0; j < NB; ++j)
-                #pragma unroll
-                for (int r = 0; r < 16; ++r) mine &= fabsf(acc[i][j][r]) < INFINITY;
-        finite = !__syncthreads_or(!mine);
-        if (finite) break;
-    }
-    // undo the scales: lane l, register r of a 32 x 32 block is row l % 32, column 8 (r / 4) + 4 (l / 32) + r % 4
-    if (EPI == kFwd) {
-        if (wave == 0) {
-            #pragma unroll
-            for (int c = 0; c < BP; ++c) col_max[0][lane * BP + c] = inverse_scale(b_scale[c]);
-        }
-        __syncthreads();
+    using Buffer0 = std::integral_constant<int, 0>;
+    using Buffer1 = std::integral_constant<int, 1>;
+    load_slice(0);
+    if (EPI != kFwd && p.X_next) {
+        // The NEXT local step's mini-batch is drawn here, a share per block, into the other batch buffer: vector
+        // arithmetic under the latency of the first operand loads.
+        const uint32_t step = p.step_base ? *p.step_base + p.step : p.step, per_worker = gen_batch_blocks(p);
+        for (uint32_t id = linear; id < per_worker * p.W; id += total)
+            gen_batch_block(p, id % per_worker, t, id / per_worker, step + 1, p.X_next, p.y_next);
     }
     #pragma unroll
-    for (int j = 0; j < NB; ++j)
+    for (int i = 0; i < MB; ++i) { acc[i] = f16v{0}; low[i] = f16v{0}; }
+    for (uint32_t s = 0; s + 2 < n_slices; s += 2) {          // one barrier per slice: waves stage one buffer while others multiply the other
+        stage_slice(Buffer0{});
+        load_slice(s + 1);
+        __syncthreads();
+        multiply_slice(Buffer0{});
+        stage_slice(Buffer1{});
+        load_slice(s + 2);
+        __syncthreads();
+        multiply_slice(Buffer1{});
+    }
+    stage_slice(Buffer0{});
+    load_slice(n_slices - 1);
+    if (EPI != kFwd) prefetch_x();
+    __syncthreads();
+    multiply_slice(Buffer0{});
+    stage_slice(Buffer1{});
+    if (EPI != kFwd) prefetch_v();
+    __syncthreads();
+    multiply_slice(Buffer1{});
+
+    // undo the scale: lane l, register r of a 32 x 32 block is row l % 32, column 8 (r / 4) + 4 (l / 32) + r % 4
+    bool mine = true;
+    #pragma unroll
+    for (int i = 0; i < MB; ++i)
         #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const float inv = EPI == kFwd ? col_max[0][(wn * NB + j) * 32 + 8 * (r / 4) + 4 * (lane / 32) + r % 4]
-                                          : inverse_scale(b_scale[0]);
-            #pragma unroll
-            for (int i = 0; i < MB; ++i) acc[i][j][r] *= inv;
+            const float sum = acc[i][r] + low[i][r];
+            mine &= fabsf(sum) < INFINITY;
+            acc[i][r] = sum * kUnscale;
         }
-    // Backward: an infinite dA anywhere in the worker takes the scale of all its tiles with it (2^-114, where the finite
-    // dA are zeros and their sums finite), so they are all formed again; the flag is the same in the whole block.
-    if (EPI == kFwd ? !finite && __syncthreads_or(infinite_operand) : infinite_operand) {
-        // Infinities among the operands (they split into inf and NaN): with fp32 products throughout, which give inf, NaN
-        // or neither just as the fp32 arithmetic of the rest of the step.  (A NaN operand alone needs nothing: its sums
-        // are NaN either way.)
-        const uint32_t K0 = slice0 * kBK, K1 = K0 + n_slices * kBK;
+    // A sum that is not finite comes from a NaN, and is NaN either way, or from an operand out of the planes' range: an
+    // infinity (it splits into inf and NaN) or one so large that products overflow with the scale (below 2^64 none can:
+    // |X| < 8, fewer than 2^37 terms).  Such a tile is formed with fp32 products throughout, which give inf, NaN or neither
+    // just as the fp32 arithmetic of the rest of the step.  (The first vote is also the barrier behind which the operand
+    // buffers are free.)
+    if (__syncthreads_or(!mine) && __syncthreads_or(largest >= 0x1p64f)) {
+        // (A pair of k and one block of rows at a time, such a step took 0.5 ms longer.)
+        constexpr int kPairs = 8;                               // pairs of k requested together; slices come in pairs, 64 k
+        const uint32_t k0 = slice0 * kBK + lane / 32, n = column(wn * 32 + lane % 32);
+        const uint64_t lda = EPI == kFwd ? 1 : p.n_in, ldm = EPI == kFwd ? p.n_in : 1;
+        const float *bk = b_base + static_cast<uint64_t>(k0) * ldb + n, *ak = Xw + (m0 + wm * MB * 32 + lane % 32) * ldm + k0 * lda;
         #pragma unroll
-        for (int i = 0; i < MB; ++i)
+        for (int i = 0; i < MB; ++i) acc[i] = f16v{0};
+        #pragma unroll 1
+        for (uint32_t k = 0; k < n_slices * kBK; k += 2 * kPairs, bk += 2 * kPairs * static_cast<uint64_t>(ldb), ak += 2 * kPairs * lda) {
+            float bq[kPairs], aq[MB][kPairs];
             #pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const uint32_t m = m0 + (wm * MB + i) * 32 + lane % 32, n = column((wn * NB + j) * 32 + lane % 32);
-                const float *am = EPI == kFwd ? Xw + static_cast<uint64_t>(m) * p.n_in : Xw + m;
-                const uint64_t lda = EPI == kFwd ? 1 : p.n_in;
-                f16v sum = {0};
-                #pragma unroll 1
-                for (uint32_t k = K0 + lane / 32; k < K1; k += 2)
-                    sum = __builtin_amdgcn_mfma_f32_32x32x2f32(b_base[static_cast<uint64_t>(k) * ldb + n], am[k * lda], sum, 0, 0, 0);
-                acc[i][j] = sum;
+            for (int q = 0; q < kPairs; ++q) {
+                bq[q] = bk[2 * q * static_cast<uint64_t>(ldb)];
+                #pragma unroll
+                for (int i = 0; i < MB; ++i) aq[i][q] = ak[2 * q * lda + 32 * i * ldm];
             }
+            #pragma unroll
+            for (int q = 0; q < kPairs; ++q)
+                #pragma unroll
+                for (int i = 0; i < MB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(bq[q], aq[i][q], acc[i], 0, 0, 0);
+        }
     }
 
     if (EPI == kFwd) {
@@ -746,11 +669,9 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kFwd ? 2 : 3) void mlp_gemm_ke
         #pragma unroll
         for (int i = 0; i < MB; ++i)
             #pragma unroll
-            for (int j = 0; j < NB; ++j)
-                #pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    *reinterpret_cast<f4 *>(out + static_cast<uint64_t>((wm * MB + i) * 32 + lane % 32) * p.n_hid + (wn * NB + j) * 32 + 8 * g + 4 * (lane / 32)) =
-                        f4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+            for (int g = 0; g < 4; ++g)
+                *reinterpret_cast<f4 *>(out + static_cast<uint64_t>((wm * MB + i) * 32 + lane % 32) * p.n_hid + wn * 32 + 8 * g + 4 * (lane / 32)) =
+                    f4{acc[i][4 * g], acc[i][4 * g + 1], acc[i][4 * g + 2], acc[i][4 * g + 3]};
         return;
     }
     // accumulators -> LDS tile (the operand buffers are dead: the vote above was a barrier), then the update over
@@ -758,11 +679,9 @@ __global__ __launch_bounds__(kGemmThreads, EPI == kFwd ? 2 : 3) void mlp_gemm_ke
     #pragma unroll
     for (int i = 0; i < MB; ++i)
         #pragma unroll
-        for (int j = 0; j < NB; ++j)
-            #pragma unroll
-            for (int g = 0; g < 4; ++g)
-                *reinterpret_cast<f4 *>(&Ct[(wm * MB + i) * 32 + lane % 32][(wn * NB + j) * 32 + 8 * g + 4 * (lane / 32)]) =
-                    f4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+        for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<f4 *>(&Ct[(wm * MB + i) * 32 + lane % 32][wn * 32 + 8 * g + 4 * (lane / 32)]) =
+                f4{acc[i][4 * g], acc[i][4 * g + 1], acc[i][4 * g + 2], acc[i][4 * g + 3]};
     // line 6: the stored model and the mean, into the registers that the accumulators have just left (stored model requested
     // with v, mean one quad at a time below: 203 us, like this 191, W = 16, 3072-1024-10)
     f4 snap_old[EPI_ITERS], mean[EPI_ITERS];
@@ -811,13 +730,11 @@ bool mlp_shape_supported(uint32_t n_in, uint32_t n_hid, uint32_t n_out, uint32_t
 }
 
 size_t mlp_dz_pitch() { return kMaxOut; }
-size_t mlp_max_groups(uint32_t batch) { return batch / kHeadSamples; }
 
 // K splits of the forward product: the fewest that give every compute unit a block, at least four K slices each.
-// More of them feed the chip better (W = 16, 3072-1024-10, batch 128, 128 tiles: the product takes 109 us at one
-// split, 67 at two, 62 at four) but every split writes and reads H once more and the round does not gain: 539 us at one
-// split, 537 at two, 548 at four, 559 at six.  W = 6, 1024-2048-10, batch 512, 384 tiles: round 207 us at one split, 216
-// at two, 240 at four.
+// More of them feed the chip better (W = 16, 3072-1024-10, batch 128, 128 tiles: the product alone takes 93 us at two
+// splits, 74 at four) but every split writes and reads H once more and the kernels behind it slow down: round 595 us at
+// two splits, 584 at four; W = 6, 1024-2048-10, batch 512, 384 tiles: 260 us at one split, 265 at two.
 uint32_t mlp_forward_splits(uint32_t W, uint32_t n_in, uint32_t n_hid, uint32_t batch, uint32_t compute_units)
 {
     const uint64_t tiles = static_cast<uint64_t>(W) * (batch / 128) * (n_hid / (n_hid % 128 == 0 ? 128 : 64));

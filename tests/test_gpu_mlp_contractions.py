@@ -1,6 +1,6 @@
-"""The perceptron workers' two big contractions (fp16 pairs on the matrix cores at fp32 accuracy) at the sizes and
-values where their splitting, scaling, K splits, tiles and chunks can go wrong, against 64 bits on the device's own
-operands."""
+"""The perceptron workers' two big contractions (three bf16 planes per operand on the matrix cores, at fp32 accuracy) at
+the sizes and values where their splitting, range, K splits, tiles and chunks can go wrong, against 64 bits on the device's
+own operands."""
 import numpy as np
 import pytest
 import torch
@@ -29,9 +29,10 @@ def one_step(W, shape, batch, theta):
 
 
 def bound(K, a, b):
-    """Largest error of an element of a @ b: every operand carries 22 bits (2^-23 each), one of four partial products
-    (2^-22) is left out, and 3 K / 16 sums of 16 products are rounded to fp32, each a few times inside."""
-    return (2.0**-21 + 3 * K / 16 * 4 * 2.0**-24) * (np.abs(a) @ np.abs(b))
+    """Largest error of an element of a @ b.  Every operand is split exactly (8 + 8 + 8 bits); the partial products left out
+    are at most 2^-24 of the product; K / 16 sums of 16 leading products are rounded to fp32, each a few times inside, 5 K / 16
+    sums of small ones (2^-7 of the leading ones) likewise; the two are added once."""
+    return 2.0**-24 * (2 + 4 * K / 16 * (1 + 5 * 2.0**-7)) * (np.abs(a) @ np.abs(b))
 
 
 # one and several K splits; 64- and 128-column tiles; one and several m-tiles; a hidden layer that passes through the
@@ -60,7 +61,7 @@ def test_contractions_and_small_gradients_against_64_bits(W, shape, batch):
 
 @pytest.mark.parametrize("scale", [1e-30, 1e-12, 1e12])
 def test_weights_of_any_magnitude(scale):
-    """A worker's W1 far from 1: the columns' scales follow it (bias 0, so that H shows the product itself)."""
+    """A worker's W1 far from 1 (bias 0, so that H shows the product itself)."""
     W, shape, batch = 1, (512, 128, 3), 128
     theta = theta_of(shape)
     a = shape[0] * shape[1]
@@ -73,9 +74,8 @@ def test_weights_of_any_magnitude(scale):
 
 
 def test_columns_that_outgrow_their_first_rows():
-    """The scale of a column comes from its first 32 rows; one that then grows a millionfold, one whose first rows are
-    zero and one that is zero throughout must still be exact to the bound (their block starts again with the true
-    maximum)."""
+    """A column that grows a millionfold after its first rows, one whose first rows are zero and one that is zero throughout
+    are exact to the bound."""
     W, shape, batch = 1, (512, 256, 3), 128
     theta = theta_of(shape)
     a = shape[0] * shape[1]
@@ -106,6 +106,73 @@ def test_infinities_and_nan_in_the_weights_go_where_fp32_takes_them():
     C1 = clean[:a].astype(np.float64).reshape(shape[0], shape[1])[:, rest]
     b1 = clean[a:a + shape[1]].astype(np.float64)[rest]
     assert np.all(np.abs(H[:, rest] - np.maximum(X @ C1 + b1, 0)) <= bound(shape[0], X, C1) + 2.0**-21 * (1 + np.abs(b1)))
+
+
+def scale_rows(factors):
+    def change(W1, W2):
+        W2 *= factors(len(W2))[:, None].astype(np.float32)
+    return change
+
+
+@pytest.mark.parametrize("change", [scale_rows(lambda n: 2.0 ** (-45 * np.arange(n) / (n - 1))),      # rows of W2 over 2^-45 .. 1
+                                    scale_rows(lambda n: np.where(np.arange(n) == 7, 1e8, 1.0)),       # one row above the others
+                                    scale_rows(lambda n: np.full(n, 1e-34))])                          # near the smallest numbers
+def test_every_column_of_the_gradient_has_its_own_accuracy(change):
+    """W2 is the caller's and sets the columns of dA: the gradient of a column must not lose bits to a larger one."""
+    W, shape, batch = 1, (256, 128, 10), 128
+    theta = theta_of(shape)
+    a, b, c = 256 * 128, 256 * 128 + 128, 256 * 128 + 128 + 128 * 10
+    change(theta[:a].reshape(256, 128), theta[b:c].reshape(128, 10))
+    ws, v, _ = one_step(W, shape, batch, theta)
+    X, dA = ws["X"][0], ws["dA"][0]
+    assert (np.abs(dA).max(0) > 0).sum() > 100
+    assert np.all(np.abs(v[0, :a].reshape(256, 128) - X.T @ dA) <= bound(batch, X.T, dA))
+
+
+def test_sums_of_one_term_are_products_of_whole_operands():
+    """A column of W1 with one entry that is not zero, and units that are active on a few samples: no sum hides what an
+    operand has lost.  One term: 2^-24 left out, 2^-24 for adding the small products, the last place of the fp32 result."""
+    W, shape, batch = 2, (512, 256, 10), 128
+    n_in, n_hidden, n_out = shape
+    theta = theta_of(shape)
+    a = n_in * n_hidden
+    W1 = theta[:a].reshape(n_in, n_hidden)
+    w = W1[2 * np.arange(n_hidden), np.arange(n_hidden)].copy()
+    W1[:] = 0
+    W1[2 * np.arange(n_hidden), np.arange(n_hidden)] = w
+    theta[a:a + n_hidden] = 0
+    ws, _, _ = one_step(W, shape, batch, theta)
+    for i in range(W):
+        exact = ws["X"][i][:, ::2] * w.astype(np.float64)
+        assert np.all(np.abs(ws["H"][i] - np.maximum(exact, 0)) <= 2.1 * 2.0**-24 * np.abs(exact))
+    theta = theta_of(shape)
+    norm = np.sqrt((theta[:a].astype(np.float64).reshape(n_in, n_hidden) ** 2).sum(0))
+    theta[a:a + n_hidden] = (-2.2 * norm).astype(np.float32)
+    ws, v, _ = one_step(W, shape, batch, theta)
+    for i in range(W):
+        X, dA = ws["X"][i], ws["dA"][i]
+        assert np.median((dA != 0).sum(0)) <= 4
+        assert np.all(np.abs(v[i, :a].reshape(n_in, n_hidden) - X.T @ dA) <= bound(8, X.T, dA))
+
+
+@pytest.mark.parametrize("which,scale", [("W1", 1e36), ("W1", 1e25), ("W1", 1e-37), ("W2", 1e36), ("W2", 1e25)])
+def test_operands_at_the_ends_of_the_range(which, scale):
+    """Beyond 2^104 the planes overflow and the tile is formed with fp32 products: n terms, n / 2 roundings of 2 each."""
+    W, shape, batch = 1, (256, 192, 4), 128
+    n_in, n_hidden, n_out = shape
+    theta = theta_of(shape)
+    a, b, c = n_in * n_hidden, n_in * n_hidden + n_hidden, n_in * n_hidden + n_hidden + n_hidden * n_out
+    if which == "W1":
+        theta[:a] *= np.float32(scale)
+        theta[a:b] = 0
+    else:
+        theta[b:c] *= np.float32(scale)
+    ws, v, _ = one_step(W, shape, batch, theta)
+    X, dA, W1 = ws["X"][0], ws["dA"][0], theta[:a].astype(np.float64).reshape(n_in, n_hidden)
+    if which == "W1":
+        assert np.all(np.abs(ws["H"][0] - np.maximum(X @ W1, 0)) <= 2.0**-24 * (n_in + 8) * (np.abs(X) @ np.abs(W1)))
+    assert np.isfinite(dA).all() and np.abs(dA).max() > 0
+    assert np.all(np.abs(v[0, :a].reshape(n_in, n_hidden) - X.T @ dA) <= 2.0**-24 * (batch + 8) * (np.abs(X.T) @ np.abs(dA)))
 
 
 def test_an_infinity_in_dA_leaves_the_other_columns_their_gradient():

@@ -13,6 +13,17 @@ def forward_splits(W, n_in, n_hid, batch, cus=256):
     return min(-(-cus // tiles), min(n_in // SLICE // 4, 8))
 
 
+def tile_cols(n_hid):
+    return 128 if n_hid % 128 == 0 else 64
+
+
+def b_operand(K, n_hid, first_col):
+    """(k, column) of every B element that the lanes of a block read in the last slice."""
+    wave, lane, kb, j = np.meshgrid(np.arange(4), np.arange(64), np.arange(2), np.arange(8), indexing="ij")
+    col = first_col + wave % (tile_cols(n_hid) // 32) * 32 + lane % 32
+    return K - SLICE + 16 * kb + 8 * (lane // 32) + j, np.where(col < n_hid, col, col - n_hid)
+
+
 def split_slices(n_in, splits):
     pairs = n_in // SLICE // 2
     return [(2 * (pairs * s // splits), 2 * (pairs * (s + 1) // splits)) for s in range(splits)]
@@ -27,18 +38,83 @@ def test_forward_splits_cover_k_and_stay_inside(W, n_in, n_hid, batch):
     assert all(a[1] == b[0] for a, b in zip(ranges, ranges[1:]))
     for first, end in ranges:
         n = end - first
-        assert n >= 2 and n % 2 == 0                         # two register sets: slices come in pairs
-        loaded = {0, 1} | {s + d for s in range(0, max(n - 2, 0), 2) for d in (2, 3)}
-        assert loaded == set(range(n))
-    BN = 128 if n_hid % 128 == 0 else 64
+        assert n >= 2 and n % 2 == 0                         # two LDS buffers: slices come in pairs
+        loaded = [0] + [s + d for s in range(0, n - 2, 2) for d in (1, 2)] + [n - 1]
+        assert loaded == list(range(n))
     t = np.arange(THREADS)
     rows = (t // 4)[:, None] + 64 * np.arange(2)
     assert sorted(rows[t % 4 == 0].ravel().tolist()) == list(range(128))
     k = (n_in // SLICE - 1) * SLICE + (t % 4) * 8 + 7
     assert (batch - 128 + rows.max()) * n_in + k.max() == batch * n_in - 1
-    col = n_hid - BN + (t % 64) * (BN // 64) + BN // 64 - 1
-    krow = (n_in // SLICE - 1) * SLICE + (t // 64) * 8 + 7
+    krow, col = b_operand(n_in, n_hid, n_hid - tile_cols(n_hid))
     assert krow.max() * n_hid + col.max() == n_in * n_hid - 1
+
+
+@pytest.mark.parametrize("BN", [64, 128])
+def test_b_operand_covers_a_slice_once_per_row_of_waves(BN):
+    """Lane l of wave w: column 32 (w % waves along N) + l % 32, octets l / 32 and 2 + l / 32 of the slice."""
+    seen = {}
+    for wave in range(4):
+        for lane in range(64):
+            for kb in range(2):
+                for j in range(8):
+                    at = (wave // (BN // 32), 16 * kb + 8 * (lane // 32) + j, wave % (BN // 32) * 32 + lane % 32)
+                    seen[at] = seen.get(at, 0) + 1
+    assert seen == {(m, k, c): 1 for m in range(4 // (BN // 32)) for k in range(SLICE) for c in range(BN)}
+
+
+@pytest.mark.parametrize("forward", [True, False])
+def test_a_operand_is_read_where_it_was_written(forward):
+    """A's pieces in LDS: [32-row block][octet][slot]; the eight lanes that write together use eight 16-byte groups."""
+    rows = 128 if forward else 64
+    slot = (lambda r, o: (r + 2 * o) & 31) if forward else (lambda r, o: r)
+    lds = {}
+    for i in range(rows // 64):
+        for t in range(THREADS):
+            row, octet = (t // 4 + 64 * i, t % 4) if forward else (t % 64, t // 64)
+            key = (row // 32, octet, slot(row % 32, octet))
+            assert key not in lds
+            lds[key] = (row, octet)
+        for first in range(0, THREADS, 8):
+            together = [(t // 4 + 64 * i, t % 4) if forward else (t % 64, t // 64) for t in range(first, first + 8)]
+            groups = {slot(r % 32, o) % 8 for r, o in together}
+            assert len(groups) == 8
+    assert len(lds) == rows * 4
+    for block in range(rows // 32):
+        for kb in range(2):
+            for lane in range(64):
+                octet = 2 * kb + lane // 32
+                assert lds[(block, octet, slot(lane % 32, octet))] == (32 * block + lane % 32, octet)
+
+
+@pytest.mark.parametrize("BM,BN", [(128, 128), (128, 64), (64, 128), (64, 64)])
+def test_results_cover_the_tile_once(BM, BN):
+    """Lane l, register r of a wave's 32-row block i: row l % 32, column 8 (r / 4) + 4 (l / 32) + r % 4 of its 32 columns."""
+    nwn = BN // 32
+    mb = BM // 32 // (4 // nwn)
+    got = sorted(((w // nwn * mb + i) * 32 + l % 32, w % nwn * 32 + 8 * (r // 4) + 4 * (l // 32) + r % 4)
+                 for w in range(4) for i in range(mb) for l in range(64) for r in range(16))
+    assert got == [(r, c) for r in range(BM) for c in range(BN)]
+
+
+@pytest.mark.parametrize("n_in,n_hid,batch", SHAPES)
+def test_backward_operands_and_update_stay_inside(n_in, n_hid, batch):
+    """X^T, dA with wrapped columns, and the update's x, v, stored model and mean, for the last worker and tile."""
+    W, BM, BN = 3, 64, tile_cols(n_hid)
+    t = np.arange(THREADS)
+    x_row = (batch // SLICE - 1) * SLICE + (t // 64) * 8 + 7
+    assert x_row.max() * n_in + (n_in - BM) + (t % 64).max() == batch * n_in - 1
+    assert [0] + [s + d for s in range(0, batch // SLICE - 2, 2) for d in (1, 2)] + [batch // SLICE - 1] == list(range(batch // SLICE))
+    stride = (n_in * n_hid + n_hid + 3) // 4 * 4
+    for lead in range(0, 32, 4):
+        for n0 in (0, n_hid - BN):
+            krow, col = b_operand(batch, n_hid, n0 + lead)
+            assert col.min() >= 0 and col.max() < n_hid and krow.max() == batch - 1
+            quad = n0 + lead + (t % (BN // 4)) * 4
+            quad = np.where(quad < n_hid, quad, quad - n_hid)
+            per_pass, iters = THREADS // (BN // 4), BM * BN // 4 // THREADS
+            last = (W - 1) * stride + (n_in - BM + (t // (BN // 4)).max() + (iters - 1) * per_pass) * n_hid + quad.max() + 3
+            assert quad.min() >= 0 and last < (W - 1) * stride + n_in * n_hid
 
 
 @pytest.mark.parametrize("n_hid", [64, 128, 192, 256, 1024])
