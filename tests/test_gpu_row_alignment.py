@@ -12,8 +12,9 @@ W = 3
 HYPER = dict(lr=0.05, weight_decay=5e-4, noise_sigma=0.01, seed=77)
 
 
-def rounds(sizes, extra, momentum, kind):
-    """(x, v, mean) of the real parameters after rounds of every kind; models, h, c drawn by parameter index."""
+def rounds(sizes, extra, momentum, kind, on_device=False):
+    """(x, v, mean) of the real parameters after rounds of every kind; models, h, c drawn by parameter index (large ones
+    on the device)."""
     d = sum(sizes)
     packed = sizes if len(sizes) > 1 else None
     padded, _, _ = P.plan_layout(d, packed)
@@ -21,10 +22,14 @@ def rounds(sizes, extra, momentum, kind):
     dev = torch.device("cuda:0")
     pos = torch.from_numpy(packed_positions(packed, d)).to(dev)
     rng = np.random.default_rng(d)
+    gen = torch.Generator(device=dev).manual_seed(d)
 
     def buf(scale, fill=7.0):
         t = torch.full((W, stride), fill, device=dev)
-        t[:, pos] = torch.from_numpy((scale * rng.standard_normal((W, d))).astype(np.float32)).to(dev)
+        if on_device:
+            t[:, pos] = scale * torch.randn((W, d), device=dev, generator=gen)
+        else:
+            t[:, pos] = torch.from_numpy((scale * rng.standard_normal((W, d))).astype(np.float32)).to(dev)
         return t
     xA, v, h, c = buf(0.5), buf(0.1), buf(1.0), buf(1.0)
     xB, mean = torch.full_like(xA, 7.0), torch.zeros(stride, device=dev)
@@ -64,6 +69,30 @@ def test_rows_off_the_lines_give_the_same_bits(sizes, kind, momentum):
     for extra in (4, 8, 16, 28):                     # three workers: leads of 0, -extra and -2 extra modulo 32
         got = rounds(sizes, extra, momentum, kind)
         assert all(torch.equal(a, b) for a, b in zip(got, want)), extra
+
+
+CACHED_STATE = 224 << 20         # up to here (five arrays) the steps run without the streaming hint
+PANEL_MEAN = 128 << 20           # above, the blocks of a line-6 step run in panels
+
+
+@pytest.mark.parametrize("kind,momentum", [("round", 0.9), ("round", 0.0), ("fp32", 0.9), ("bf16", 0.9)])
+def test_large_states_off_the_lines_give_the_same_bits(kind, momentum):
+    """The same above the size up to which the steps do without the streaming hint: the other instantiations."""
+    sizes = [3, 29, 1_300_001, 1055, 33, 2_750_002]
+    assert 20 * W * sum(sizes) > CACHED_STATE
+    want = rounds(sizes, 0, momentum, kind, on_device=True)
+    got = rounds(sizes, 12, momentum, kind, on_device=True)
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("kind", ["round", "fp32"])
+def test_panels_off_the_lines_give_the_same_bits(kind):
+    """A mean above the size from which line 6, alone or in a step, takes its tiles panel by panel (a short last panel)."""
+    sizes = [34_000_003]
+    assert 4 * sum(sizes) > PANEL_MEAN and sum(sizes) // 256 % 16384 != 0
+    want = rounds(sizes, 0, 0.9, kind, on_device=True)
+    got = rounds(sizes, 20, 0.9, kind, on_device=True)
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
 
 
 @pytest.mark.parametrize("workers", [3, 8, 17])
