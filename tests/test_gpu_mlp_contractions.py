@@ -50,8 +50,8 @@ def test_contractions_and_small_gradients_against_64_bits(W, shape, batch):
         X, H, dA, dZ = ws["X"][i], ws["H"][i], ws["dA"][i], ws["dZ"][i]
         H64 = np.maximum(X @ W1 + b1, 0)
         assert np.all(np.abs(H - H64) <= bound(n_in, X, W1) + 2.0**-22 * (np.abs(b1) + np.abs(H64)))
-        # n_out products, each added with a rounding of at most 2^-24 of the partial sum (largest seen 8 x 2^-24 at 16)
-        assert np.all(np.abs(dA - np.where(H > 0, dZ @ W2.T, 0)) <= (n_out + 4) * 2.0**-24 * (np.abs(dZ) @ np.abs(W2.T)))
+        # four sums of up to four products, two roundings each (largest seen 6.4 x 2^-24, at 16 classes)
+        assert np.all(np.abs(dA - np.where(H > 0, dZ @ W2.T, 0)) <= 2.0**-21 * (np.abs(dZ) @ np.abs(W2.T)))
         assert np.all(np.abs(v[i, :a].reshape(n_in, n_hidden) - X.T @ dA) <= bound(batch, X.T, dA))
         small = (batch + 8) * 2.0**-24                       # a chain of fp32 additions over the batch
         assert np.all(np.abs(v[i, a:b] - dA.sum(0)) <= small * np.abs(dA).sum(0))
@@ -202,7 +202,7 @@ def test_every_row_alignment_gives_the_same_bits(shape, batch):
     W, theta = 3, theta_of(shape)
     d = synth_inputs.mlp_param_count(*shape)
     want = None
-    for extra in (0, 4, 12, 20, 28, 32):
+    for extra, fused_tail in [(e, tail) for e in (0, 4, 12, 20, 28, 32) for tail in (False, True)]:
         stride = (d + 31) // 32 * 32 + extra
         dev = torch.device("cuda:0")
         xA = torch.zeros((W, stride), device=dev)
@@ -212,12 +212,12 @@ def test_every_row_alignment_gives_the_same_bits(shape, batch):
         torch.cuda.synchronize()
         ctx = P.Context(W=W, d=d, stride=stride, xA=xA, xB=xB, v=v, mean=mean, grad=P.GRAD_MLP, mlp=(*shape, batch),
                         compute_stream=s, avg_stream=s, **HYPER)
-        ctx.round(2)
-        ctx.round_fused_tail(2)
+        for _ in range(2):
+            ctx.round_fused_tail(2) if fused_tail else ctx.round(2)
         ctx.sync()
         live = xA if ctx.live_model() == xA.data_ptr() else xB
         got = [t[..., :d].cpu() for t in (live, v, mean)]
         ctx.close()
         if want is None:
             want = got
-        assert all(torch.equal(p, q) for p, q in zip(got, want)), extra
+        assert all(torch.equal(p, q) for p, q in zip(got, want)), (extra, fused_tail)
