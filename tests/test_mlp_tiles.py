@@ -175,3 +175,39 @@ def test_output_layer_chunks_rows_and_blocks(n_hid):
         seen += [c0 + 16 * b for b in blocks]
     assert sorted(seen) == list(range(0, n_hid, 16))
     assert 16 * pitch * 4 + 17536 <= 160 * 1024                        # dynamic and static LDS of a block
+
+
+@pytest.mark.parametrize("n_in,n_hid,batch", SHAPES)
+@pytest.mark.parametrize("n_out", [1, 10, 16])
+def test_output_layer_and_small_update_stay_inside_their_arrays(n_in, n_hid, batch, n_out):
+    """Last worker, tightest buffers: H, dA, dZ rows, the K splits behind H, W2 read by hidden unit and by class, and the
+    next mini-batch."""
+    W, pitch = 3, 16
+    splits = forward_splits(W, n_in, n_hid, batch)
+    group, wave = batch // 16 - 1, 15
+    sample = (W - 1) * batch + group * 16 + wave
+    assert sample == W * batch - 1
+    assert sample * n_hid + n_hid - 1 == W * batch * n_hid - 1                                 # H and dA
+    assert max(splits - 2, 0) * W * batch * n_hid + sample * n_hid + n_hid - 1 < max(splits - 1, 1) * W * batch * n_hid
+    lane = np.arange(64)
+    s16, g = lane % 16, lane // 16
+    W2 = n_in * n_hid + n_hid
+    end = W2 + n_hid * n_out
+    for j in range(4):                                       # the last block of 16 hidden units
+        by_unit = (n_hid - 16 + 4 * g + j) * n_out + s16
+        by_class = (n_hid - 16 + s16) * n_out + 4 * j + g
+        assert W2 + by_unit[s16 < n_out].max() < end and by_unit[s16 < n_out].max() + 1 <= n_hid * n_out
+        ok = 4 * j + g < n_out
+        assert not ok.any() or W2 + by_class[ok].max() < end
+    own = n_hid // 64 - 1                                    # small update: 64 hidden units, quarter of the batch per wave
+    s = (W - 1) * batch + 3 * (batch // 4) + (batch // 4 - 16) + 12 + g
+    assert s.max() == W * batch - 1 and s.max() * pitch + s16.max() == W * batch * pitch - 1
+    assert (s * n_hid + own * 64 + s16 + 48).max() == W * batch * n_hid - 1
+    e = np.arange(64 * n_out)
+    assert own * 64 * n_out + e.max() == n_hid * n_out - 1
+    stride = (end + n_out + 3) // 4 * 4                      # the pads behind the last parameter, at most three
+    assert end + n_out + ((end + n_out + 3) // 4 * 4 - (end + n_out)) <= stride
+    groups = (batch * n_in // 4 + 255) // 256
+    q = (groups - 1) * 256 + np.arange(256)
+    q = q[q < batch * n_in // 4]
+    assert q.max() * 4 + 3 == batch * n_in - 1 and batch // 4 <= 256
