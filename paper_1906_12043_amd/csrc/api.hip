@@ -129,8 +129,13 @@ constexpr uint32_t kPanelTiles = 16384;
 constexpr uint64_t kMeanCacheBytes = 128ull << 20;
 // Steps access a state (both model buffers, v, h, c: 20 bytes per worker-parameter) up to this size without the
 // streaming hint: the next step finds it in the last-level cache.  k = 8 rounds, hint / no hint: W = 8, d = 250 k
-// (40 MB) 83.7 / 66.5 us, W = 16, d = 400 k (128 MB) 220 / 206, d = 700 k (224 MB) 367 / 337 (with three such contexts in
-// turn 355 / 348), d = 1 M (320 MB) 514 / 479 but in turn 518 / 570, d = 2 M (640 MB) 992 / 1125.
+// (40 MB) 84 / 70 us, W = 16, d = 400 k (128 MB) 220 / 207, d = 700 k (224 MB) 367 / 338, d = 1 M (320 MB) 514 / 479 but
+// with three such contexts in turn 518 / 570, d = 2 M (640 MB) 992 / 1125.
+// The count is the same for every kind of context; those without momentum or with the caller's gradient hold less.  At
+// 40 / 128 / 224 MB so counted: no momentum 61 / 60, 156 / 148, 252 / 235; caller's fp32 gradient 76 / 61, 197 / 180,
+// 315 / 291, without momentum 62 / 62, 132 / 124, 205 / 190; 16-bit gradient 74 / 62, 182 / 169, 290 / 269, without
+// momentum 63 / 61, 122 / 112, 187 / 168.  Two to four contexts in turn, 160 to 233 MB each: 4 to 9 % faster without the
+// hint in 26 of 32 cases, within 1 % in three, 9 to 10 % slower in three that no size or kind sets apart.
 constexpr uint64_t kCachedStateBytes = 224ull << 20;
 // one grid dimension holds fewer than 2^32 threads
 constexpr uint64_t kMaxThreadsPerGridDim = 1ull << 32;

@@ -218,9 +218,9 @@ __device__ __forceinline__ double wave_sum_f64(double v)
 }
 
 // R > 0: up to R workers a thread holds V columns of every row in registers and reads each model once; R == 0: any W,
-// two passes over the rows.  (W = 64, d = 2.8 M: two passes 207 us, the second one mostly from memory again, as the rows of
-// the blocks in flight are far more than L2 holds; column pairs in registers 121 us = 5.9 TB/s.  W = 21, d = 4.0 M:
-// 104 -> 59 us; W = 1, where registers for 16 rows cost occupancy: 27 -> 23.)
+// two passes over the rows.  (This kernel alone, W = 64, d = 2.8 M: two passes 202 us, the second one mostly from memory
+// again, as the rows of the blocks in flight are far more than L2 holds; column pairs in registers 123 us = 5.8 TB/s.
+// W = 21, d = 4.0 M: 101 -> 53 us; W = 1, d = 10 M, where registers for 16 rows cost occupancy: 16 -> 12.)
 template <bool WEIGHTED, int R, int V>
 __global__ __launch_bounds__(kStepThreads, R > 16 ? 3 : 4) void consensus_partial_kernel(const Chunk *table, const float *x, uint64_t stride,
                                                                                                  uint32_t W, const float *weights, double *partial)

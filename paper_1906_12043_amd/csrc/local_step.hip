@@ -122,8 +122,9 @@ __global__ __launch_bounds__(64 * NWMAX) void local_step_kernel(const StepParams
     // The tile: elements [begin, begin + n) counted from its chunk.
     // Rows off the 128-byte lines: a worker's row starts on any 16-byte boundary (the stride is the caller's), and a
     // wave that streams 1 KiB off the lines leaves half a line at both ends (plain step, W = 21, d = 4.0 M, rows 48 bytes
-    // off: 390 us = 5.2 TB/s, with this rule 312 us = 6.45 TB/s, rows on lines 308 us).  Where every wave has a row of its own its tiles are therefore moved up to the next line of that row,
-    // `lead` elements; the tensor's first tile also serves the elements before it, in a second pass.
+    // off: 390 us = 5.2 TB/s, with this rule 312 us = 6.45 TB/s, rows on lines 308 us).  Where every wave has a row of its
+    // own its tiles are therefore moved up to the next line of that row, `lead` elements; the tensor's first tile also
+    // serves the elements before it, in a second pass.
     uint32_t begin = first, n = ck.n - first < TILE_ELEMS ? ck.n - first : TILE_ELEMS, lead = 0;
     if (!FORMS_MEAN) {
         const uint32_t row_worker = group * nw + wave;
