@@ -10,6 +10,10 @@ synthetic data.
 Two ways of running the same round are timed:
   separate    cocod_average_begin; cocod_local_steps(k); cocod_average_end_apply
   fused_tail  cocod_average_begin; cocod_local_steps_end_apply(k)   (line 6 inside the last step)
+The built-in quadratic gradient is separable, so the library takes a round's k steps in one launch unless the step
+timing is armed.  The headline and everything else here keeps it armed: one launch and one pass over memory per step, as
+any real gradient needs.  The k-in-one-launch rounds are reported apart, under "k_steps_in_one_launch" (and the graph
+variants of the k sweep, whose launches are not timed, take their k steps that way too).
 Prints ONE JSON line.  `value` = worker-param-updates/s = W*d*k / round time for the variant named in
 config.variant under the overlapped two-stream schedule.  The same line carries: the k sweep (both
 variants, each also replayed from a HIP graph, and under the schedule that forms the mean inside the
@@ -68,11 +72,11 @@ def moved_round_bytes(W, d, k, variant, per_step=STEP_BYTES):
     return W * d * (per_step * (k - 1) + 4 * (1 + 1 / W)) + tail_step_bytes(W, d, k, per_step)
 
 
-def time_rounds(ctx, torch, k, rounds, warmup, variant, want_step_times=True):
+def time_rounds(ctx, torch, k, rounds, warmup, variant, one_launch=False):
     """Seconds per round over `rounds` timed rounds and, measured over the same rounds from the
     kernels' own start/stop timestamps on the compute stream, the average duration in seconds of the
     plain step kernel, of the step kernel that carries line 6 and of the first step that also forms the
-    mean (None where there was no launch)."""
+    mean (None where there was no launch).  one_launch: the k steps of a round in one launch, not timed."""
     import paper_1906_12043_amd as P
     head = variant.startswith("head_")           # Step I inside the round's first step (one stream)
     if head:
@@ -92,7 +96,7 @@ def time_rounds(ctx, torch, k, rounds, warmup, variant, want_step_times=True):
     for _ in range(warmup):
         one_round()
     ctx.sync()
-    want_step_times = want_step_times and not variant.startswith("graph")   # launches in a graph are not timed
+    want_step_times = not one_launch and not variant.startswith("graph")    # launches in a graph are not timed
     ctx.step_timing(rounds * k if want_step_times else 0)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -114,7 +118,8 @@ def time_rounds(ctx, torch, k, rounds, warmup, variant, want_step_times=True):
 
 def timelines(ctx, torch, P, k, rounds):
     """The four timelines that the paper's time-speedup analysis compares, built from the same
-    kernels on one GPU, as average milliseconds per local step (the paper's T_N^av up to the factor N):
+    kernels on one GPU, as average milliseconds per local step (the paper's T_N^av up to the factor N), one launch
+    per local step (its timing armed):
       s_sgd      one step, then blocking average of the models          (communicate every step, sequential)
       local_sgd  k steps, then blocking average                         (communicate every k steps, sequential)
       cocod      the round with the mean overlapped and line 6 separate (every k steps, in parallel)
@@ -123,14 +128,16 @@ def timelines(ctx, torch, P, k, rounds):
     def timed(body, steps_per_iter):
         for _ in range(2):
             body()
-        ctx.sync()
+        ctx.step_timing(rounds * steps_per_iter)
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         for _ in range(rounds):
             body()
         ctx.sync()
         torch.cuda.synchronize()
-        return (time.perf_counter() - t0) / rounds / steps_per_iter * 1e3
+        elapsed = time.perf_counter() - t0
+        ctx.step_timing(0)
+        return elapsed / rounds / steps_per_iter * 1e3
 
     out = {}
     out["s_sgd"] = timed(lambda: (ctx.local_steps(1), ctx.average_apply_fused()), 1)
@@ -176,6 +183,7 @@ def round_event_times(ctx, torch, stream, k, rounds, variant):
     """Median and minimum round time from events recorded on the compute stream around every round
     (every variant ends its round on that stream)."""
     marks = [torch.cuda.Event(enable_timing=True) for _ in range(rounds + 1)]
+    ctx.step_timing(rounds * k)                  # one launch per local step, as in the timed rounds
     ctx.sync()
     marks[0].record(stream)
     for r in range(rounds):
@@ -187,6 +195,7 @@ def round_event_times(ctx, torch, stream, k, rounds, variant):
             ctx.local_steps_end_apply(k)
         marks[r + 1].record(stream)
     ctx.sync()
+    ctx.step_timing(0)
     ms = sorted(marks[r].elapsed_time(marks[r + 1]) for r in range(rounds))
     return {"round_ms_median": ms[len(ms) // 2], "round_ms_min": ms[0]}
 
@@ -434,25 +443,36 @@ def bench_quadratic(workload, k, variant, steps, warmup, full):
             sweep = {}
             for kk in cfg["k"]:
                 pr, ps, ts, hs = time_rounds(ctx, torch, kk, sweep_rounds, 2, name)
-                sweep["k=%d" % kk] = {"ms_per_round": pr * 1e3, "updates_per_s": W * d * kk / pr,
-                                      "model_GBps": model_round_bytes(W, d, kk, per_step) / pr / 1e9,
-                                      "moved_GBps": moved_round_bytes(W, d, kk, name, per_step) / pr / 1e9,
+                passes = 1 if "graph" in name else kk            # of the steps over memory
+                sweep["k=%d" % kk] = {"ms_per_round": pr * 1e3, "updates_per_s": W * d * kk / pr, "step_launches": passes,
+                                      "model_GBps": model_round_bytes(W, d, passes, per_step) / pr / 1e9,
+                                      "moved_GBps": moved_round_bytes(W, d, passes, name, per_step) / pr / 1e9,
                                       "plain_step_ms": ps * 1e3 if ps else None,
                                       "tail_step_ms": ts * 1e3 if ts else None,
                                       "head_step_ms": hs * 1e3 if hs else None}
             variants[name] = sweep
         out["k_sweep"] = variants
+        # the k steps of a round in one launch: what a caller of the built-in gradient gets without step timing
+        variants = {"note": "k steps of the separable built-in gradient in one launch and one pass over memory"}
+        for name in ("separate", "fused_tail", "head_fused_tail"):
+            sweep = {}
+            for kk in cfg["k"]:
+                pr = time_rounds(ctx, torch, kk, sweep_rounds, 2, name, True)[0]
+                sweep["k=%d" % kk] = {"ms_per_round": pr * 1e3, "updates_per_s": W * d * kk / pr,
+                                      "moved_GBps": moved_round_bytes(W, d, 1, name, per_step) / pr / 1e9}
+            variants[name] = sweep
+        out["k_steps_in_one_launch"] = variants
         sched = {}
         for name, code in (("serial", P.SCHED_SERIAL), ("serial_fused_mean_line6", P.SCHED_FUSED), ("overlap", P.SCHED_OVERLAP)):
             ctx.set_schedule(code)
-            sched[name] = time_rounds(ctx, torch, k, sweep_rounds, 2, "separate", False)[0] * 1e3
+            sched[name] = time_rounds(ctx, torch, k, sweep_rounds, 2, "separate")[0] * 1e3
         out["separate_schedule_ms_per_round"] = sched
         # line 6 inside the last step, with the mean (a) beside the first k-1 steps on its own stream,
         # (b) on the compute stream right before the last step, (c) inside the first step
         sched = {}
         for name, code in (("overlap", P.SCHED_OVERLAP), ("serial", P.SCHED_SERIAL), ("head", P.SCHED_HEAD)):
             ctx.set_schedule(code)
-            sched[name] = time_rounds(ctx, torch, k, sweep_rounds, 2, "fused_tail", False)[0] * 1e3
+            sched[name] = time_rounds(ctx, torch, k, sweep_rounds, 2, "fused_tail")[0] * 1e3
         ctx.set_schedule(P.SCHED_OVERLAP)
         out["fused_tail_schedule_ms_per_round"] = sched
         out["timelines_ms_per_local_step"] = timelines(ctx, torch, P, k, sweep_rounds)
@@ -511,7 +531,7 @@ def bench_mlp(k, variant, steps, warmup, full):
     }
     if full:
         other = "separate" if fused else "fused_tail"
-        out[other + "_ms_per_round"] = time_rounds(ctx, torch, k, steps, warmup, other, False)[0] * 1e3
+        out[other + "_ms_per_round"] = time_rounds(ctx, torch, k, steps, warmup, other)[0] * 1e3
         out["graph_ms_per_round"] = time_rounds(ctx, torch, k, steps, warmup, "graph_" + variant)[0] * 1e3
     ctx.close()
     del xA, xB, v, mean
@@ -543,7 +563,8 @@ def kernels_alone(reps=5):
         P.debug_copy(wl.s_compute, wl.h, wl.xB, wl.W * wl.stride)
     ctx.sync()
     wl.fill()
-    ctx.local_steps(reps)                       # plain step, in place
+    for _ in range(reps):                       # plain step, in place
+        ctx.local_steps(1)
     ctx.sync()
     for _ in range(reps):                       # mean, plain step (out of place), line 6 back to back
         ctx.round(1)
@@ -552,15 +573,19 @@ def kernels_alone(reps=5):
         ctx.local_steps(1)
         ctx.average_apply_fused()
     ctx.sync()
+    def two_launches():                         # a round of two steps, each a launch of its own
+        ctx.average_begin()
+        ctx.local_steps(1)
+        ctx.local_steps_end_apply(1)
     for _ in range(reps):                       # line 6 inside the last step: mean, plain step, step with line 6
-        ctx.round_fused_tail(2)
+        two_launches()
     ctx.sync()
     for _ in range(reps):                       # k = 1: the step with line 6 reads the stored models as its input
         ctx.round_fused_tail(1)
     ctx.sync()
     ctx.set_schedule(P.SCHED_HEAD)              # the mean formed inside the round's first step
     for _ in range(reps):
-        ctx.round_fused_tail(2)
+        two_launches()
     ctx.sync()
     for _ in range(reps):                       # k = 1: mean, step and line 6 in one kernel
         ctx.round_fused_tail(1)

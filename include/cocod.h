@@ -68,8 +68,9 @@ typedef enum cocod_schedule {
     COCOD_SCHED_FUSED = 2,     /* mean and line 6 in one kernel after the local steps */
     COCOD_SCHED_HEAD = 3       /* mean formed inside the first local step of the round, which reads every
                                   stored model anyway: Step I costs one 4/W-byte store per parameter and no
-                                  pass of its own; with k = 1 through cocod_local_steps_end_apply the mean,
-                                  the step and line 6 are ONE kernel (built-in quadratic gradient, W <= 131
+                                  pass of its own; where the round's steps are one launch of
+                                  cocod_local_steps_end_apply (k = 1; untimed up to k = 16) the mean,
+                                  the steps and line 6 are ONE kernel (built-in quadratic gradient, W <= 131
                                   workers, d < 2^30; whenever the round's first step is not such a step, the
                                   mean is formed on compute_stream just before line 6 needs it) */
 } cocod_schedule;
@@ -172,6 +173,10 @@ int cocod_destroy(cocod_ctx *ctx);
  * and advances the step counter t by one.  Legal in both states; outside a round
  * it is plain local SGD.  The first step after cocod_average_begin reads the
  * stored model and writes the other model buffer, so storing x_t^i costs no copy.
+ * The built-in quadratic gradient of a coordinate depends on that coordinate alone, so its k steps are
+ * taken up to 16 to a launch, in registers, with the bits of one launch per step (also inside
+ * cocod_local_steps_end_apply and cocod_graph_round); while step timing is armed every step is a
+ * launch of its own.  The other gradients need the whole model between two steps.
  */
 int cocod_local_steps(cocod_ctx *ctx, int k);
 
@@ -212,7 +217,7 @@ int cocod_average_apply_fused(cocod_ctx *ctx);
  * cocod_local_steps(k) followed by cocod_average_end_apply, but the separate pass of line 6 over
  * the models (read x, read x_t, write x) disappears: 8 bytes per parameter less per round (24 at
  * k = 1, where the step reads the stored models anyway).  The join moves in front of the last
- * step, so the mean overlaps the first k-1 steps only.  k = 0 is cocod_average_end_apply.
+ * launch, so the mean overlaps the launches before it only.  k = 0 is cocod_average_end_apply.
  * AVERAGING -> IDLE; COCOD_ERR_STATE if no round is open.
  */
 int cocod_local_steps_end_apply(cocod_ctx *ctx, int k);
@@ -277,8 +282,8 @@ int cocod_is_averaging(const cocod_ctx *ctx);
 int cocod_get_plan(const cocod_ctx *ctx, uint64_t *padded_d, uint32_t *n_chunks, uint32_t *n_buckets);
 
 /*
- * Measurement aid.  cocod_step_timing(ctx, n) with n > 0 makes the next n local-step kernel
- * launches carry the runtime's own start/stop timestamps (events on compute_stream, owned by the
+ * Measurement aid.  cocod_step_timing(ctx, n) with n > 0 makes each of the next n local steps a launch
+ * of its own that carries the runtime's own start/stop timestamps (events on compute_stream, owned by the
  * context); n = 0 switches it off.  cocod_step_timing_read waits for compute_stream, returns the
  * summed kernel durations and the number of launches measured since the last read, and rearms.
  * A local step of the MLP kind is several kernels: its duration runs from the start of the first

@@ -137,6 +137,14 @@ constexpr uint64_t kMeanCacheBytes = 128ull << 20;
 // momentum 63 / 61, 122 / 112, 187 / 168.  Two to four contexts in turn, 160 to 233 MB each: 4 to 9 % faster without the
 // hint in 26 of 32 cases, within 1 % in three, 9 to 10 % slower in three that no size or kind sets apart.
 constexpr uint64_t kCachedStateBytes = 224ull << 20;
+// Local steps per launch with the built-in quadratic gradient.  The gradient of a coordinate depends on nothing but that
+// coordinate, so a wave takes its tile through several steps in registers: 24 bytes per parameter once, not per step (a real
+// gradient needs the whole model between two steps: one launch per step there).  Measured at W = 16, d = 11.2 M, one
+// launch: 1 step 659 us, 2 659, 3 671, 4 751, 8 1181, 16 2066, 32 in two launches 4131; from four steps on the generator and
+// the arithmetic bound it (110 us a step), so more than 16 would only make launches long.  Without momentum 1 step 423 us, 2
+// 442, 4 630; a round of the overlapped schedule with line 6 inside the last step at k = 2 1638 -> 835 us, at W = 12,
+// d = 3.0 M, k = 4 with line 6 apart 668 -> 241, Local SGD at W = 21, d = 4.0 M, k = 2 777 -> 458.
+constexpr int kMaxStepsPerLaunch = 16;
 // one grid dimension holds fewer than 2^32 threads
 constexpr uint64_t kMaxThreadsPerGridDim = 1ull << 32;
 // the mean-forming steps launch up to four 1024-thread blocks per chunk in one grid dimension
@@ -470,8 +478,8 @@ static uint32_t step_state_is_cached(const cocod_ctx *ctx)
     return 20 * ctx->cfg.stride * static_cast<uint64_t>(ctx->cfg.W) <= kCachedStateBytes ? 1u : 0u;
 }
 
-// The next step, if it carries line 6, can also form the round's mean itself (k = 1 under the schedule
-// that folds Step I into Step II: the step reads exactly the stored models).
+// The next launch, if it carries line 6, can also form the round's mean itself (a whole round in one launch under the
+// schedule that folds Step I into Step II: it reads exactly the stored models).
 static bool one_pass_applies(const cocod_ctx *ctx)
 {
     return ctx->schedule == COCOD_SCHED_HEAD && ctx->mean_pending && ctx->store_pending &&
@@ -479,8 +487,17 @@ static bool one_pass_applies(const cocod_ctx *ctx)
            ctx->chunks.size() < kMaxChunksMeanStep;
 }
 
-// One local step on the compute stream; with_line6 fuses line 6 into it (last step of a round).
-static int enqueue_step(cocod_ctx *ctx, bool with_line6, const void *g_ext = nullptr, bool g_bf16 = false)
+// Local steps that the next launch takes, of `left` still to take.
+static uint32_t steps_per_launch(const cocod_ctx *ctx, int left)
+{
+    const bool timed = ctx->timing && ctx->t_used < ctx->t_start.size();      // step timing: one launch per step
+    if (ctx->cfg.grad != COCOD_GRAD_QUADRATIC || timed) return 1u;
+    return static_cast<uint32_t>(left < kMaxStepsPerLaunch ? left : kMaxStepsPerLaunch);
+}
+
+// `steps` local steps on the compute stream in one launch (an MLP step: in its three); with_line6 fuses line 6 into the
+// last one (of a round).
+static int enqueue_step(cocod_ctx *ctx, uint32_t steps, bool with_line6, const void *g_ext = nullptr, bool g_bf16 = false)
 {
     // Keep the stored models intact: the first step of an open round reads them and
     // writes the spare buffer, which then becomes the live one.
@@ -526,6 +543,7 @@ static int enqueue_step(cocod_ctx *ctx, bool with_line6, const void *g_ext = nul
         p.table = ctx->d_chunks;
         p.n_chunks = static_cast<uint32_t>(ctx->chunks.size());
         p.W = ctx->cfg.W;
+        p.steps = steps;
         p.stride = ctx->cfg.stride;
         p.x_in = ctx->live;
         p.x_out = dst;
@@ -553,7 +571,7 @@ static int enqueue_step(cocod_ctx *ctx, bool with_line6, const void *g_ext = nul
                           !with_line6 && ctx->cfg.grad == COCOD_GRAD_QUADRATIC &&
                           cocod::local_step_mean_quads_per_lane(ctx->cfg.W, false) != 0 &&
                           ctx->chunks.size() < kMaxChunksMeanStep;
-        // k = 1 under the same schedule: mean, step and line 6 in one pass over the stored models
+        // a whole round in this launch under the same schedule: mean, steps and line 6 in one pass over the stored models
         const bool one_pass = with_line6 && !g_ext && one_pass_applies(ctx);
         if (head || one_pass) {
             p.mean_out = ctx->cfg.mean;
@@ -574,7 +592,7 @@ static int enqueue_step(cocod_ctx *ctx, bool with_line6, const void *g_ext = nul
         ctx->live = dst;
         ctx->store_pending = false;
     }
-    ctx->step += 1;
+    ctx->step += steps;
     return COCOD_OK;
 }
 
@@ -605,7 +623,7 @@ static int external_step(cocod_ctx *ctx, const void *g, bool bf16, int close_rou
         rc = mean_before_line6(ctx);
         if (rc != COCOD_OK) return rc;
     }
-    rc = enqueue_step(ctx, close_round != 0, g, bf16);
+    rc = enqueue_step(ctx, 1, close_round != 0, g, bf16);
     if (rc == COCOD_OK && close_round) {
         ctx->averaging = false;
         ctx->mean_pending = false;
@@ -629,7 +647,11 @@ int cocod_local_steps(cocod_ctx *ctx, int k)
     if (!ctx) return fail(nullptr, COCOD_ERR_INVALID, "ctx is NULL");
     int rc = check_steps(ctx, k);
     if (rc == COCOD_OK && k > 0) rc = need_builtin_gradient(ctx);
-    for (int s = 0; s < k && rc == COCOD_OK; ++s) rc = enqueue_step(ctx, false);
+    for (int left = k; left > 0 && rc == COCOD_OK;) {
+        const uint32_t n = steps_per_launch(ctx, left);
+        rc = enqueue_step(ctx, n, false);
+        left -= static_cast<int>(n);
+    }
     return rc;
 }
 
@@ -642,15 +664,17 @@ int cocod_local_steps_end_apply(cocod_ctx *ctx, int k)
     if (k == 0) return cocod_average_end_apply(ctx);
     rc = need_builtin_gradient(ctx);
     if (rc != COCOD_OK) return rc;
-    for (int s = 0; s + 1 < k && rc == COCOD_OK; ++s) rc = enqueue_step(ctx, false);
-    if (rc != COCOD_OK) return rc;
-    if (!ctx->dry && !one_pass_applies(ctx)) {
-        // the mean must be complete before the last step starts: it is consumed inside it
-        rc = mean_before_line6(ctx);
+    for (int left = k; left > 0;) {
+        const uint32_t n = steps_per_launch(ctx, left);
+        left -= static_cast<int>(n);
+        if (left == 0 && !ctx->dry && !one_pass_applies(ctx)) {
+            // the mean must be complete before the last launch starts: it is consumed inside it
+            rc = mean_before_line6(ctx);
+            if (rc != COCOD_OK) return rc;
+        }
+        rc = enqueue_step(ctx, n, left == 0);
         if (rc != COCOD_OK) return rc;
     }
-    rc = enqueue_step(ctx, true);
-    if (rc != COCOD_OK) return rc;
     ctx->averaging = false;
     ctx->mean_pending = false;
     ctx->snap = nullptr;

@@ -40,7 +40,8 @@ struct StepParams {
     float lr, momentum, weight_decay, sigma;
     const float *sigma_w; // non-null: device [W], worker i's noise standard deviation instead of sigma
     uint32_t key0, key1; // generator key (seed low, seed high)
-    uint32_t step;       // global step counter t (relative to *step_base when that is set)
+    uint32_t step;       // global step counter t of the first step (relative to *step_base when that is set)
+    uint32_t steps;      // local steps of this launch, >= 1; more than one only with the built-in quadratic gradient
     const uint32_t *step_base;   // non-null inside a replayable graph: device word holding t at the start of the replay
     uint32_t panel_tiles;      // line-6 step only, non-zero: blocks run in panels of this many tiles, worker by worker
                                // inside a panel (for a mean larger than the cache); 0 = grid (tiles, workers)
@@ -49,11 +50,11 @@ struct StepParams {
     const float *weights;      //           (Step I inside Step II's first pass); p_i, nullptr = 1/W
 };
 
-// One local step of all W workers (local_step.hip).  The kind of step follows from the parameters:
+// p.steps local steps of all W workers (local_step.hip).  The kind of launch follows from the parameters:
 //   snap == nullptr, mean_out == nullptr   plain step
 //   snap set                               last step of a round, line 6 applied to its result
 //   mean_out set                           first step of a round that also forms the mean of the models it reads
-//   mean_out and snap (== x_in) set        k = 1: mean, step and line 6 in one pass
+//   mean_out and snap (== x_in) set        a whole round: mean, steps and line 6 in one pass
 // start / stop: optional events that receive the kernel's own begin / end timestamps.
 hipError_t launch_local_step(hipStream_t stream, const StepParams &p, hipEvent_t start = nullptr,
                              hipEvent_t stop = nullptr);

@@ -3,7 +3,8 @@
 //     G = h_ij (x_j - c_ij) + sigma z(seed, i, t, j)        stochastic gradient (or the caller's g)
 //     g = G + lambda x ;  v = mu v + g ;  x = x - gamma v    momentum SGD of the experiments
 // The gradient is never written to memory: the kernel reads x, v, h, c and writes x, v (24 bytes per
-// parameter; 16 when mu = 0 and v is untouched; 20 / 18 with a caller's fp32 / 16-bit gradient).
+// parameter; 16 when mu = 0 and v is untouched; 20 / 18 with a caller's fp32 / 16-bit gradient).  With the quadratic
+// gradient, whose coordinates are independent, a launch takes several steps (p.steps) over the one pass, x and v in registers.
 //
 // Work decomposition.  A tile is Q x 64 consecutive 16-byte quads of one tensor (Q = 1 or 2: four or
 // two tiles per 1024-element chunk of the chunk table, which maps a block to its tensor slice, so one
@@ -20,7 +21,7 @@
 //             puts its row's tile into LDS, the block sums the tile's columns over the workers in order
 //             0..W-1 (the one compensated sum of mean_sum.hpp, so the bits equal those of the stand-alone
 //             mean kernel) and stores the mean: 4/W bytes per parameter instead of a pass of its own.
-//   ONE_PASS  k = 1: Step I, the local step and line 6 in a single sweep (24 + 4/W bytes per
+//   ONE_PASS  the launch is the whole round: Step I, the local steps and line 6 in a single sweep (24 + 4/W bytes per
 //             parameter): as HEAD, and line 6 is applied with the tile's mean before anything is stored.
 //
 // Memory path: every model array is streamed exactly once per step, through buffer instructions whose descriptor
@@ -42,17 +43,17 @@ namespace {
 constexpr uint32_t kXcds = 8;      // accelerator complex dies of the MI355X, each with its own L2
 enum { kModePlain = 0, kModeTail = 1, kModeTailIn = 2, kModeHead = 3, kModeOnePass = 4, kModeLine6 = 5 };
 
-// Normals for the Q memory quads of one lane.  Quad u of lane l covers global indices
-// 4 (q0 + 64 u + l) + shift .. + 3: with shift == 0 exactly generator block q0 + 64 u + l, else the
+// Normals for the Q memory quads of one lane.  Quad u of a lane covers global indices
+// 4 (block0 + 64 u) + shift .. + 3, block0 one more from lane to lane: with shift == 0 exactly generator block block0 + 64 u, else the
 // last 4 - shift normals of that block and the first `shift` of the next one.
 template <int Q>
-__device__ __forceinline__ void noise_for_lane(f4 (&z)[Q], uint64_t q0, uint32_t shift, uint32_t lane, uint32_t worker,
+__device__ __forceinline__ void noise_for_lane(f4 (&z)[Q], uint32_t block0, uint32_t shift, uint32_t lane, uint32_t worker,
                                                uint32_t step, const StepParams &p)
 {
     Normals4 a[Q];
     #pragma unroll
     for (int u = 0; u < Q; ++u)
-        a[u] = box_muller_fast(philox4x32_10(static_cast<uint32_t>(q0 + 64u * u + lane), step, worker, kTagNoise, p.key0, p.key1));
+        a[u] = box_muller_fast(philox4x32_10(block0 + 64u * u, step, worker, kTagNoise, p.key0, p.key1));
     if (shift == 0) {                                                   // block-uniform
         #pragma unroll
         for (int u = 0; u < Q; ++u) z[u] = f4{a[u].z[0], a[u].z[1], a[u].z[2], a[u].z[3]};
@@ -67,7 +68,7 @@ __device__ __forceinline__ void noise_for_lane(f4 (&z)[Q], uint64_t q0, uint32_t
             if (lane == 63u) { b0 = n0; b1 = n1; b2 = n2; }
         } else if (lane == 63u) {                                       // one lane per wave: the block behind the tile
             const Normals4 nb = box_muller_fast(
-                philox4x32_10(static_cast<uint32_t>(q0 + 64u * Q), step, worker, kTagNoise, p.key0, p.key1));
+                philox4x32_10(block0 + 64u * Q - 63u, step, worker, kTagNoise, p.key0, p.key1));
             b0 = nb.z[0]; b1 = nb.z[1]; b2 = nb.z[2];
         }
         if (shift == 1)      z[u] = f4{a[u].z[1], a[u].z[2], a[u].z[3], b0};
@@ -81,10 +82,11 @@ __device__ __forceinline__ void noise_for_lane(f4 (&z)[Q], uint64_t q0, uint32_t
 // mean-forming modes: 1, the block loops over its worker groups itself).
 // Dynamic LDS (mean-forming modes only): W rows of the tile, then (ONE_PASS) the tile of the mean.
 template <bool HAS_V, int GRAD, int MODE, bool WEIGHTED, int NWMAX, int Q, int AUX>
-__global__ __launch_bounds__(64 * NWMAX) void local_step_kernel(const StepParams p)
+__global__ __launch_bounds__(64 * NWMAX, Q == 1 ? 8 : 4) void local_step_kernel(const StepParams p)
 {
     constexpr bool FORMS_MEAN = MODE == kModeHead || MODE == kModeOnePass;
     constexpr bool LINE6 = MODE == kModeTail || MODE == kModeTailIn || MODE == kModeOnePass || MODE == kModeLine6;
+    constexpr bool QUADRATIC = GRAD == kGradQuadNoisy || GRAD == kGradQuadExact;
     constexpr uint32_t PARTS = 4 / Q, TILE_ELEMS = Q * 256;
     extern __shared__ __attribute__((aligned(16))) float lds[];
 
@@ -155,7 +157,7 @@ __global__ __launch_bounds__(64 * NWMAX) void local_step_kernel(const StepParams
             const uint32_t off = (64u * u + lane) * 16u;
             r.v[u] = HAS_V ? load_quad<AUX>(make_rsrc(p.v + row, bytes), off) : f4{0.f, 0.f, 0.f, 0.f};
             r.c[u] = f4{0.f, 0.f, 0.f, 0.f};
-            if (GRAD == kGradQuadNoisy || GRAD == kGradQuadExact) {
+            if (QUADRATIC) {
                 r.h[u] = load_quad<AUX>(make_rsrc(p.h + row, bytes), off);
                 r.c[u] = load_quad<AUX>(make_rsrc(p.c + row, bytes), off);
             } else if (GRAD == kGradExternal) {
@@ -181,25 +183,35 @@ __global__ __launch_bounds__(64 * NWMAX) void local_step_kernel(const StepParams
         const uint64_t row = static_cast<uint64_t>(w) * p.stride + col;
         const __amdgpu_buffer_rsrc_t rx_out = make_rsrc(p.x_out + row, bytes);
         const __amdgpu_buffer_rsrc_t rv = make_rsrc(HAS_V ? p.v + row : p.x_out + row, bytes);
-        f4 z[Q];
-        #pragma unroll
-        for (int u = 0; u < Q; ++u) z[u] = f4{0.f, 0.f, 0.f, 0.f};
-        if (GRAD == kGradQuadNoisy) noise_for_lane<Q>(z, q0, shift, lane, w, step, p);
         const float sigma = GRAD == kGradQuadNoisy ? (p.sigma_w ? p.sigma_w[w] : p.sigma) : 0.0f;
+        f4 x[Q], v[Q];
+        #pragma unroll
+        for (int u = 0; u < Q; ++u) { x[u] = x0[u]; v[u] = r.v[u]; }
+        uint32_t s = 0;
+        do {                                                  // a caller's gradient: one step
+            f4 z[Q];
+            #pragma unroll
+            for (int u = 0; u < Q; ++u) z[u] = f4{0.f, 0.f, 0.f, 0.f};
+            uint32_t block0 = static_cast<uint32_t>(q0) + lane;
+            asm("" : "+v"(block0));                           // or what the generator forms of the counter alone is held in registers across the steps
+            if (GRAD == kGradQuadNoisy) noise_for_lane<Q>(z, block0, shift, lane, w, step + s, p);
+            #pragma unroll
+            for (int u = 0; u < Q; ++u)
+                local_step_quad<HAS_V, QUADRATIC, GRAD == kGradQuadNoisy>(x[u], v[u], r.h[u], r.c[u], z[u], sigma, p.lr, p.momentum, p.weight_decay);
+        } while (QUADRATIC && ++s < p.steps);
         #pragma unroll
         for (int u = 0; u < Q; ++u) {
             const uint32_t e = (64u * u + lane) * 4u, off = e * 4u;
-            f4 x, v;
-            local_step_quad<HAS_V, GRAD == kGradQuadNoisy || GRAD == kGradQuadExact, GRAD == kGradQuadNoisy, LINE6>(
-                x, v, x0[u], r.v[u], r.h[u], r.c[u], z[u], sigma, p.lr, p.momentum, p.weight_decay, snap[u], m[u]);
-            if (e + 4 > n && e < n) {                     // tensor tail: alignment pads keep their old values
-                const uint32_t keep = n - e;              // 1..3 real elements
-                if (keep < 2) { x.y = x0[u].y; v.y = r.v[u].y; }
-                if (keep < 3) { x.z = x0[u].z; v.z = r.v[u].z; }
-                x.w = x0[u].w; v.w = r.v[u].w;
+            if (LINE6) x[u] = line6_quad(m[u], x[u], snap[u]);
+            if (e + 4 > n && e < n) {                     // tensor tail: alignment pads keep their old values, which are
+                const uint32_t keep = n - e;              // still in memory (1..3 real elements)
+                const f4 xo = load_quad<AUX>(make_rsrc(p.x_in + row, bytes), off), vo = HAS_V ? load_quad<AUX>(rv, off) : v[u];
+                if (keep < 2) { x[u].y = xo.y; v[u].y = vo.y; }
+                if (keep < 3) { x[u].z = xo.z; v[u].z = vo.z; }
+                x[u].w = xo.w; v[u].w = vo.w;
             }
-            store_quad<AUX>(rx_out, off, x);
-            if (HAS_V) store_quad<AUX>(rv, off, v);
+            store_quad<AUX>(rx_out, off, x[u]);
+            if (HAS_V) store_quad<AUX>(rv, off, v[u]);
         }
     };
 

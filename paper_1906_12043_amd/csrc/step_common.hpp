@@ -40,32 +40,25 @@ __device__ __forceinline__ f4 line6_quad(const f4 mean, const f4 x, const f4 sna
     return mean + (x - snap);
 }
 
-// One local step of Algorithm 1's Step II on a quad of parameters, with the experiments' optimizer,
-// and optionally line 6 on the result:
+// One local step of Algorithm 1's Step II on a quad of parameters, in place, with the experiments' optimizer:
 //     G = h (x - c) + sigma z      (QUADRATIC; else G = a, the caller's gradient)
 //     g = G + lambda x ;  v = mu v + g ;  x = x - gamma v      (mu = 0: x = x - gamma g)
-//     x = mean + (x - snap)                                      (LINE6)
 // ONE definition for every kernel that takes a step, with every fused multiply-add written out and
 // contraction switched off: left to the compiler, which products get fused depends on the code around
 // them (h (x - c) + sigma z can become fma(sigma, z, .) or fma(h, x - c, .)), and kernels that must
 // agree bit for bit (every mode and launch shape of the step) would differ in the last place.
-template <bool HAS_V, bool QUADRATIC, bool NOISY, bool LINE6>
-__device__ __forceinline__ void local_step_quad(f4 &x, f4 &v, const f4 x0, const f4 v0, const f4 a, const f4 c, const f4 z,
-                                                float sigma, float lr, float momentum, float weight_decay,
-                                                const f4 snap, const f4 mean)
+template <bool HAS_V, bool QUADRATIC, bool NOISY>
+__device__ __forceinline__ void local_step_quad(f4 &x, f4 &v, const f4 a, const f4 c, const f4 z,
+                                                float sigma, float lr, float momentum, float weight_decay)
 {
     #pragma clang fp contract(off)
     #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        float g = QUADRATIC ? a[j] * (x0[j] - c[j]) : a[j];
+        float g = QUADRATIC ? a[j] * (x[j] - c[j]) : a[j];
         if (NOISY) g = __builtin_fmaf(sigma, z[j], g);
-        g = __builtin_fmaf(weight_decay, x0[j], g);
-        float vj = v0[j];
-        if (HAS_V) { vj = __builtin_fmaf(momentum, v0[j], g); g = vj; }
-        float xj = __builtin_fmaf(-lr, g, x0[j]);
-        if (LINE6) xj = mean[j] + (xj - snap[j]);
-        x[j] = xj;
-        v[j] = vj;
+        g = __builtin_fmaf(weight_decay, x[j], g);
+        if (HAS_V) { v[j] = __builtin_fmaf(momentum, v[j], g); g = v[j]; }
+        x[j] = __builtin_fmaf(-lr, g, x[j]);
     }
 }
 
