@@ -244,8 +244,8 @@ int cocod_external_step_bf16(cocod_ctx *ctx, const uint16_t *g, int close_round)
 
 /*
  * One whole pass of the while-loop body of Algorithm 1 (Step I and Step II side by side, then line
- * 6 and line 7) replayed from a HIP graph: the same kernels, in the same order and on the same two
- * branches, as cocod_average_begin + cocod_local_steps(k) + cocod_average_end_apply (fused_tail == 0)
+ * 6 and line 7) replayed from a HIP graph: the same kernels, in the same order and, where the models
+ * are large enough for it to pay, on the same two branches, as cocod_average_begin + cocod_local_steps(k) + cocod_average_end_apply (fused_tail == 0)
  * or cocod_average_begin + cocod_local_steps_end_apply(k) (fused_tail != 0), with bit-identical
  * results, but submitted with ONE call instead of one per kernel and event: for small models, where
  * the launches and not the memory traffic bound a round.  The first call for a given (k, fused_tail,

@@ -145,6 +145,13 @@ constexpr uint64_t kCachedStateBytes = 224ull << 20;
 // 442, 4 630; a round of the overlapped schedule with line 6 inside the last step at k = 2 1638 -> 835 us, at W = 12,
 // d = 3.0 M, k = 4 with line 6 apart 668 -> 241, Local SGD at W = 21, d = 4.0 M, k = 2 777 -> 458.
 constexpr int kMaxStepsPerLaunch = 16;
+// Models of all workers up to this size are averaged on the one branch of a replayed round: reading them takes a few
+// microseconds, fork and join between two branches more, and above all when several contexts replay rounds at a time.
+// Perceptron rounds of k = 2, two branches / one, three contexts in turn (one context alone): W = 4, 768-192-10 (2.4 MB of
+// models) 50 / 25 us (78 / 62), 768-768-10 (9.5 MB) 70 / 69 (109 / 98), W = 8, 2048-512-10 (34 MB) 175 / 179 (213 / 205), W = 16,
+// 3072-1024-10 (202 MB) 575 / 581 (609 / 607).  Rounds of the quadratic gradient, whose steps are one launch behind the mean,
+// are the same either way.
+constexpr uint64_t kGraphBranchBytes = 16ull << 20;
 // one grid dimension holds fewer than 2^32 threads
 constexpr uint64_t kMaxThreadsPerGridDim = 1ull << 32;
 // the mean-forming steps launch up to four 1024-thread blocks per chunk in one grid dimension
@@ -297,6 +304,14 @@ int enqueue_mean(cocod_ctx *ctx, hipStream_t stream)
     return COCOD_OK;
 }
 
+// The overlapped schedule's mean has a branch of its own: the averaging stream, or in a replayed round, which need not use
+// that stream, a branch of the graph where the mean is long enough to pay for the fork and the join.
+bool on_avg_stream(const cocod_ctx *ctx)
+{
+    return ctx->s_avg != ctx->s_compute &&
+           !(ctx->capturing && ctx->cfg.stride * sizeof(float) * ctx->cfg.W <= kGraphBranchBytes);
+}
+
 // Make the open round's mean available to line 6 on the compute stream: enqueue it there if no
 // earlier call has (sequential schedules), or join the averaging stream (overlapped schedule).
 int mean_before_line6(cocod_ctx *ctx)
@@ -305,7 +320,7 @@ int mean_before_line6(cocod_ctx *ctx)
         const int rc = enqueue_mean(ctx, ctx->s_compute);
         if (rc != COCOD_OK) return rc;
         ctx->mean_pending = false;
-    } else if (ctx->schedule == COCOD_SCHED_OVERLAP && ctx->s_avg != ctx->s_compute) {
+    } else if (ctx->schedule == COCOD_SCHED_OVERLAP && on_avg_stream(ctx)) {
         COCOD_HIP(ctx, hipStreamWaitEvent(ctx->s_compute, ctx->ev_mean, 0));
     }
     return COCOD_OK;
@@ -687,12 +702,12 @@ int cocod_average_begin(cocod_ctx *ctx)
     if (ctx->averaging) return fail(ctx, COCOD_ERR_STATE, "cocod_average_begin: a round is already open");
     ctx->snap = ctx->live;
     if (!ctx->dry && ctx->schedule == COCOD_SCHED_OVERLAP) {
-        const bool two_streams = ctx->s_avg != ctx->s_compute;
+        const bool two_streams = on_avg_stream(ctx);
         if (two_streams) {
             COCOD_HIP(ctx, hipEventRecord(ctx->ev_snap, ctx->s_compute));
             COCOD_HIP(ctx, hipStreamWaitEvent(ctx->s_avg, ctx->ev_snap, 0));
         }
-        const int rc = enqueue_mean(ctx, ctx->s_avg);
+        const int rc = enqueue_mean(ctx, two_streams ? ctx->s_avg : ctx->s_compute);
         if (rc != COCOD_OK) return rc;
         if (two_streams) COCOD_HIP(ctx, hipEventRecord(ctx->ev_mean, ctx->s_avg));
     }
