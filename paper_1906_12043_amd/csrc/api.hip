@@ -56,10 +56,14 @@ struct cocod_ctx {
     // replayable rounds: one instantiated graph per (k, variant, schedule, which buffer is live)
     struct RoundGraph { int k; int fused_tail; int schedule; bool live_is_A; uint32_t batch_buf; bool batch_ready; hipGraphExec_t exec; };
     std::vector<RoundGraph> graphs;     // owned
-    uint32_t *d_step = nullptr;         // device copy of t that captured kernels read (owned)
-    uint64_t d_step_value = ~0ull;      // what *d_step holds once the work queued on the compute stream has run
-    bool capturing = false;             // enqueue_step runs under stream capture: step relative to *d_step
+    // Device copies of t that captured kernels read (owned): a round that starts with xA live reads word 0 and its last step
+    // leaves t + k in word 1, which the next round (xB live) reads, and so on.
+    uint32_t *d_step = nullptr;
+    uint64_t d_step_value[2] = {~0ull, ~0ull};   // what they hold once the work queued on the compute stream has run
+    bool capturing = false;             // enqueue_step runs under stream capture: step relative to the word of the round
     uint64_t capture_base = 0;          // value of `step` when the capture began
+    uint32_t capture_steps = 0;         // steps of the round
+    uint32_t capture_word = 0;          // word it reads
     std::string err;
 };
 
@@ -510,6 +514,13 @@ static uint32_t steps_per_launch(const cocod_ctx *ctx, int left)
     return static_cast<uint32_t>(left < kMaxStepsPerLaunch ? left : kMaxStepsPerLaunch);
 }
 
+// Where the launch that ends a captured round leaves t for the next one (no other launch of the round reads that word).
+static uint32_t *step_next_for(const cocod_ctx *ctx, uint32_t steps)
+{
+    const bool last = ctx->capturing && ctx->step - ctx->capture_base + steps == ctx->capture_steps;
+    return last ? ctx->d_step + (ctx->capture_word ^ 1u) : nullptr;
+}
+
 // `steps` local steps on the compute stream in one launch (an MLP step: in its three); with_line6 fuses line 6 into the
 // last one (of a round).
 static int enqueue_step(cocod_ctx *ctx, uint32_t steps, bool with_line6, const void *g_ext = nullptr, bool g_bf16 = false)
@@ -540,7 +551,9 @@ static int enqueue_step(cocod_ctx *ctx, uint32_t steps, bool with_line6, const v
         p.key0 = static_cast<uint32_t>(ctx->cfg.seed);
         p.key1 = static_cast<uint32_t>(ctx->cfg.seed >> 32);
         p.step = static_cast<uint32_t>(ctx->capturing ? ctx->step - ctx->capture_base : ctx->step);
-        p.step_base = ctx->capturing ? ctx->d_step : nullptr;
+        p.step_base = ctx->capturing ? ctx->d_step + ctx->capture_word : nullptr;
+        p.step_next = step_next_for(ctx, steps);
+        p.round_steps = ctx->capture_steps;
         p.snap = with_line6 ? ctx->snap : nullptr;
         p.mean = ctx->cfg.mean;
         const bool timed = ctx->timing && ctx->t_used < ctx->t_start.size();
@@ -577,7 +590,9 @@ static int enqueue_step(cocod_ctx *ctx, uint32_t steps, bool with_line6, const v
         p.key0 = static_cast<uint32_t>(ctx->cfg.seed);
         p.key1 = static_cast<uint32_t>(ctx->cfg.seed >> 32);
         p.step = static_cast<uint32_t>(ctx->capturing ? ctx->step - ctx->capture_base : ctx->step);
-        p.step_base = ctx->capturing ? ctx->d_step : nullptr;
+        p.step_base = ctx->capturing ? ctx->d_step + ctx->capture_word : nullptr;
+        p.step_next = step_next_for(ctx, steps);
+        p.round_steps = ctx->capture_steps;
         p.panel_tiles = panel_tiles_for(ctx);
         p.cached = step_state_is_cached(ctx);
         // Step I inside the round's first step: that step reads exactly the stored models (when there are
@@ -791,6 +806,8 @@ static int capture_round(cocod_ctx *ctx, int k, int fused_tail, hipGraphExec_t *
     ctx->timing = false;
     ctx->capturing = true;
     ctx->capture_base = step;
+    ctx->capture_steps = static_cast<uint32_t>(k);
+    ctx->capture_word = live == ctx->cfg.xA ? 0u : 1u;
     hipError_t e = hipStreamBeginCapture(ctx->s_compute, hipStreamCaptureModeThreadLocal);
     int rc = e == hipSuccess ? COCOD_OK : hip_fail(ctx, e, "hipStreamBeginCapture");
     hipGraph_t graph = nullptr;
@@ -803,10 +820,6 @@ static int capture_round(cocod_ctx *ctx, int k, int fused_tail, hipGraphExec_t *
                 rc = cocod_local_steps(ctx, k);
                 if (rc == COCOD_OK) rc = cocod_average_end_apply(ctx);
             }
-        }
-        if (rc == COCOD_OK && k > 0) {
-            e = cocod::launch_add_word(ctx->s_compute, ctx->d_step, static_cast<uint32_t>(k));
-            if (e != hipSuccess) rc = hip_fail(ctx, e, "launch_add_word");
         }
         e = hipStreamEndCapture(ctx->s_compute, &graph);          // always: leaves the stream usable
         if (rc == COCOD_OK && e != hipSuccess) rc = hip_fail(ctx, e, "hipStreamEndCapture");
@@ -842,7 +855,7 @@ int cocod_graph_round(cocod_ctx *ctx, int k, int fused_tail)
         if (rc == COCOD_OK && !fused_tail) rc = cocod_average_end_apply(ctx);
         return rc;
     }
-    if (!ctx->d_step) COCOD_HIP(ctx, hipMalloc(reinterpret_cast<void **>(&ctx->d_step), sizeof(uint32_t)));
+    if (!ctx->d_step) COCOD_HIP(ctx, hipMalloc(reinterpret_cast<void **>(&ctx->d_step), 2 * sizeof(uint32_t)));
     const bool live_is_A = ctx->live == ctx->cfg.xA;
     const bool mlp = ctx->cfg.grad == COCOD_GRAD_MLP && k > 0;
     const uint32_t batch_buf = mlp ? ctx->batch_buf : 0u;                    // which mini-batch buffer the first step reads,
@@ -856,15 +869,16 @@ int cocod_graph_round(cocod_ctx *ctx, int k, int fused_tail)
         if (rc != COCOD_OK) return rc;
         ctx->graphs.push_back({k, fused_tail, ctx->schedule, live_is_A, batch_buf, batch_ready, exec});
     }
-    if (ctx->d_step_value != ctx->step) {            // eager calls since the last replay moved t
-        COCOD_HIP(ctx, cocod::launch_set_word(ctx->s_compute, ctx->d_step, static_cast<uint32_t>(ctx->step)));
-        ctx->d_step_value = ctx->step;
+    const uint32_t word = live_is_A ? 0u : 1u;
+    if (k > 0 && ctx->d_step_value[word] != ctx->step) {     // eager calls since the last replay moved t
+        COCOD_HIP(ctx, cocod::launch_set_word(ctx->s_compute, ctx->d_step + word, static_cast<uint32_t>(ctx->step)));
+        ctx->d_step_value[word] = ctx->step;
     }
     COCOD_HIP(ctx, hipGraphLaunch(exec, ctx->s_compute));
     if (k > 0) {                                     // what the round's calls would have done to the host state
         float *t = ctx->live; ctx->live = ctx->spare; ctx->spare = t;
         ctx->step += static_cast<uint64_t>(k);
-        ctx->d_step_value = ctx->step;
+        ctx->d_step_value[word ^ 1u] = ctx->step;
         if (mlp) {                                   // k steps alternated the batch buffers; the last drew the next batch
             ctx->batch_last = (batch_buf + static_cast<uint32_t>(k - 1)) & 1u;
             ctx->batch_buf = ctx->batch_last ^ 1u;

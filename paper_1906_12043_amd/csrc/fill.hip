@@ -55,19 +55,12 @@ __global__ __launch_bounds__(kFillThreads) void copy_kernel(const float *src, fl
 }
 
 __global__ void set_word_kernel(uint32_t *word, uint32_t value) { *word = value; }
-__global__ void add_word_kernel(uint32_t *word, uint32_t inc) { *word += inc; }
 
 }  // namespace
 
 hipError_t launch_set_word(hipStream_t stream, uint32_t *word, uint32_t value)
 {
     hipLaunchKernelGGL(set_word_kernel, dim3(1), dim3(1), 0, stream, word, value);
-    return hipGetLastError();
-}
-
-hipError_t launch_add_word(hipStream_t stream, uint32_t *word, uint32_t inc)
-{
-    hipLaunchKernelGGL(add_word_kernel, dim3(1), dim3(1), 0, stream, word, inc);
     return hipGetLastError();
 }
 

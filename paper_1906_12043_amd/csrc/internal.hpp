@@ -43,6 +43,8 @@ struct StepParams {
     uint32_t step;       // global step counter t of the first step (relative to *step_base when that is set)
     uint32_t steps;      // local steps of this launch, >= 1; more than one only with the built-in quadratic gradient
     const uint32_t *step_base;   // non-null inside a replayable graph: device word holding t at the start of the replay
+    uint32_t *step_next;         // non-null: the launch leaves *step_base + round_steps here
+    uint32_t round_steps;
     uint32_t panel_tiles;      // line-6 step only, non-zero: blocks run in panels of this many tiles, worker by worker
                                // inside a panel (for a mean larger than the cache); 0 = grid (tiles, workers)
     uint32_t cached;           // the state stays in the last-level cache from step to step: no streaming hint (not for mean-forming steps)
@@ -99,6 +101,8 @@ struct MlpParams {
     float lr, momentum, weight_decay;
     uint32_t key0, key1, step;
     const uint32_t *step_base;   // as in StepParams
+    uint32_t *step_next;         //
+    uint32_t round_steps;        //
     const float *snap;        // non-null: last step of a round; line 6 is applied to every updated parameter
     const float *mean;        //           before it is stored: x = mean + (x_new - snap)   (mean is [stride])
     // work space owned by the context
@@ -123,9 +127,8 @@ hipError_t launch_mlp_step(hipStream_t stream, const MlpParams &p, hipEvent_t st
 
 hipError_t launch_copy(hipStream_t stream, const float *src, float *dst, uint64_t n_quads);
 
-// *word = value  /  *word += inc : the device copy of the step counter that graph replays read
+// *word = value: the device copy of the step counter that graph replays read
 hipError_t launch_set_word(hipStream_t stream, uint32_t *word, uint32_t value);
-hipError_t launch_add_word(hipStream_t stream, uint32_t *word, uint32_t inc);
 
 hipError_t launch_debug_normals(hipStream_t stream, uint32_t key0, uint32_t key1, uint32_t tag,
                                 uint32_t worker, uint32_t step, uint64_t j0, uint64_t n, int fast,

@@ -89,6 +89,7 @@ __global__ __launch_bounds__(64 * NWMAX, Q == 1 ? 8 : 4) void local_step_kernel(
     constexpr bool QUADRATIC = GRAD == kGradQuadNoisy || GRAD == kGradQuadExact;
     constexpr uint32_t PARTS = 4 / Q, TILE_ELEMS = Q * 256;
     extern __shared__ __attribute__((aligned(16))) float lds[];
+    if (p.step_next && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *p.step_next = *p.step_base + p.round_steps;
 
     // Grid: x = tiles, y = worker groups.  A step with line 6 whose mean does not fit the last-level
     // cache runs on a 1-D grid in PANELS of p.panel_tiles tiles instead: inside a panel the blocks

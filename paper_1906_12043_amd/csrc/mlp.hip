@@ -444,6 +444,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void mlp_gemm_kernel(const MlpPara
     const uint32_t nx = p.n_hid / BN, ny = (EPI == kFwd ? p.batch : p.n_in) / BM, total = nx * ny * p.W * splits;
     uint32_t linear = blockIdx.x;
     if (EPI != kFwd) {                                         // the launch's first blocks update the small parameters
+        if (p.step_next && linear == 0 && threadIdx.x == 0) *p.step_next = *p.step_base + p.round_steps;
         if (linear < small_blocks(p)) {
             small_update_block(p, linear, *reinterpret_cast<SmallUpdateLds *>(smem));
             return;
