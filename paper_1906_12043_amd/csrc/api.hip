@@ -144,9 +144,9 @@ constexpr uint64_t kCachedStateBytes = 224ull << 20;
 // Local steps per launch with the built-in quadratic gradient.  The gradient of a coordinate depends on nothing but that
 // coordinate, so a wave takes its tile through several steps in registers: 24 bytes per parameter once, not per step (a real
 // gradient needs the whole model between two steps: one launch per step there).  Measured at W = 16, d = 11.2 M, one
-// launch: 1 step 659 us, 2 659, 3 671, 4 751, 8 1181, 16 2066, 32 in two launches 4131; from four steps on the generator and
-// the arithmetic bound it (110 us a step), so more than 16 would only make launches long.  Without momentum 1 step 423 us, 2
-// 442, 4 630; a round of the overlapped schedule with line 6 inside the last step at k = 2 1638 -> 835 us, at W = 12,
+// launch: 1 step 656 us, 2 656, 3 657, 4 673, 8 1005, 16 1703; from five steps on the generator and
+// the arithmetic bound it (87 us a step), so more than 16 would only make launches long.  Without momentum 1 step 424 us, 2
+// 432, 4 538; a round of the overlapped schedule with line 6 inside the last step at k = 2 1638 -> 835 us, at W = 12,
 // d = 3.0 M, k = 4 with line 6 apart 668 -> 241, Local SGD at W = 21, d = 4.0 M, k = 2 777 -> 458.
 constexpr int kMaxStepsPerLaunch = 16;
 // Models of all workers up to this size are averaged on the one branch of a replayed round: reading them takes a few

@@ -119,8 +119,11 @@ __global__ __launch_bounds__(64 * NWMAX, Q == 1 ? 8 : 4) void local_step_kernel(
     const Chunk ck = p.table[chunk_id];
     const uint32_t first = part * TILE_ELEMS;                 // first element of the tile inside its chunk
     if (first >= ck.n) return;                                // block-uniform: the tensor ends before this tile
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    const uint32_t step = p.step_base ? *p.step_base + p.step : p.step;      // wave-uniform
+    // Step index and worker are wave-uniform; where the compiler is told so, what the generator forms of them alone is scalar.  Not
+    // the row addresses of the modes without a mean: with those in scalar registers a wave's loads leave in one burst, and
+    // the steps that memory bounds are 2 % slower (W = 16, d = 11.2 M, one step 655 -> 667 us).
+    const uint32_t lane = threadIdx.x & 63u, wave = FORMS_MEAN ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const uint32_t step = __builtin_amdgcn_readfirstlane(p.step_base ? *p.step_base + p.step : p.step);
 
     // The tile: elements [begin, begin + n) counted from its chunk.
     // Rows off the 128-byte lines: a worker's row starts on any 16-byte boundary (the stride is the caller's), and a
@@ -195,7 +198,7 @@ __global__ __launch_bounds__(64 * NWMAX, Q == 1 ? 8 : 4) void local_step_kernel(
             for (int u = 0; u < Q; ++u) z[u] = f4{0.f, 0.f, 0.f, 0.f};
             uint32_t block0 = static_cast<uint32_t>(q0) + lane;
             asm("" : "+v"(block0));                           // or what the generator forms of the counter alone is held in registers across the steps
-            if (GRAD == kGradQuadNoisy) noise_for_lane<Q>(z, block0, shift, lane, w, step + s, p);
+            if (GRAD == kGradQuadNoisy) noise_for_lane<Q>(z, block0, shift, lane, __builtin_amdgcn_readfirstlane(w), step + s, p);
             #pragma unroll
             for (int u = 0; u < Q; ++u)
                 local_step_quad<HAS_V, QUADRATIC, GRAD == kGradQuadNoisy>(x[u], v[u], r.h[u], r.c[u], z[u], sigma, p.lr, p.momentum, p.weight_decay);
