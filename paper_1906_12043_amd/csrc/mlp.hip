@@ -374,7 +374,9 @@ __device__ __forceinline__ void small_update_block(const MlpParams &p, uint32_t 
 }
 
 // ---- the two big contractions ---------------------------------------------------------------------
-enum { kFwd = 0, kBwd = 1, kBwdTail = 2 };   // kBwdTail: the backward product of a round's last step (line 6 in its epilogue)
+// kBwdTail: the backward product of a round's last step (line 6 in its epilogue); kBwdOnly: of its only step, whose input models are
+// the stored ones
+enum { kFwd = 0, kBwd = 1, kBwdTail = 2, kBwdOnly = 3 };
 
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 typedef __bf16 h2 __attribute__((ext_vector_type(2)));
@@ -429,6 +431,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void mlp_gemm_kernel(const MlpPara
 {
     constexpr int NWN = BN / 32, NWM = 4 / NWN, MB = BM / 32 / NWM;      // waves per direction, 32-row blocks per wave
     constexpr int CPITCH = BN + 4;
+    constexpr bool LINE6 = EPI == kBwdTail || EPI == kBwdOnly;
     constexpr int OPERANDS = 2 * sizeof(OperandTile<BM>), TILE = EPI == kFwd ? 0 : BM * CPITCH * 4;
     static_assert(EPI == kFwd || BM == 64, "a lane stages one row");
     static_assert(EPI == kFwd || OPERANDS >= static_cast<int>(sizeof(SmallUpdateLds)), "the small update's sums fit");
@@ -452,7 +455,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void mlp_gemm_kernel(const MlpPara
         linear -= small_blocks(p);
     }
     uint32_t bx, by, bz;
-    if (EPI == kBwdTail && ny % kXcds == 0) {
+    if (LINE6 && ny % kXcds == 0) {
         // the mean is read by every worker: an XCD owns the same eighth of the rows of W1 for all of them
         // (222 -> 206 us at W = 16, 3072-1024-10; measured, like the two figures at the epilogue, with half the products)
         const uint32_t rows = ny / kXcds, r = linear / kXcds;
@@ -684,13 +687,14 @@ __global__ __launch_bounds__(kGemmThreads, 2) void mlp_gemm_kernel(const MlpPara
             *reinterpret_cast<f4 *>(&Ct[(wm * MB + i) * 32 + lane % 32][wn * 32 + 8 * g + 4 * (lane / 32)]) =
                 f4{acc[i][4 * g], acc[i][4 * g + 1], acc[i][4 * g + 2], acc[i][4 * g + 3]};
     // line 6: the stored model and the mean, into the registers that the accumulators have just left (stored model requested
-    // with v, mean one quad at a time below: 203 us, like this 191, W = 16, 3072-1024-10)
+    // with v, mean one quad at a time below: 203 us, like this 191, W = 16, 3072-1024-10).  A round's only step has read the
+    // stored model already (read a second time: a round of one step 330 us instead of 307).
     f4 snap_old[EPI_ITERS], mean[EPI_ITERS];
-    if (EPI == kBwdTail) {
+    if (LINE6) {
         #pragma unroll
         for (int it = 0; it < EPI_ITERS; ++it) {
             const uint64_t down = static_cast<uint64_t>(it * ROWS_PER_PASS) * p.n_hid;
-            snap_old[it] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p.snap + tile_at + down));
+            snap_old[it] = EPI == kBwdOnly ? x_old[it] : __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p.snap + tile_at + down));
             mean[it] = *reinterpret_cast<const f4 *>(p.mean + row_at + down);
         }
     }
@@ -705,7 +709,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void mlp_gemm_kernel(const MlpPara
             __builtin_nontemporal_store(g, reinterpret_cast<f4 *>(p.v + at));
         }
         f4 x_new = x_old[it] - p.lr * g;
-        if (EPI == kBwdTail) x_new = mean[it] + (x_new - snap_old[it]);      // line 6 on the fresh model, same operation order as the separate kernel
+        if (LINE6) x_new = mean[it] + (x_new - snap_old[it]);      // line 6 on the fresh model, same operation order as the separate kernel
         __builtin_nontemporal_store(x_new, reinterpret_cast<f4 *>(p.x_out + at));
     }
 }
@@ -760,8 +764,9 @@ hipError_t launch_mlp_step(hipStream_t stream, const MlpParams &p, hipEvent_t st
                                                          kHeadSamples * (kHeadChunk + 4) * sizeof(float));
     if (lds_ok != hipSuccess) return lds_ok;
     hipLaunchKernelGGL(head_kernel, dim3(p.batch / kHeadSamples, p.W), dim3(64 * kHeadWaves), head_lds, stream, p);
-    if (p.snap) { if (wide) launch_gemm<kBwdTail, 64, 128>(stream, p, nullptr, stop); else launch_gemm<kBwdTail, 64, 64>(stream, p, nullptr, stop); }
-    else        { if (wide) launch_gemm<kBwd, 64, 128>(stream, p, nullptr, stop); else launch_gemm<kBwd, 64, 64>(stream, p, nullptr, stop); }
+    if (!p.snap)               { if (wide) launch_gemm<kBwd, 64, 128>(stream, p, nullptr, stop); else launch_gemm<kBwd, 64, 64>(stream, p, nullptr, stop); }
+    else if (p.snap != p.x_in) { if (wide) launch_gemm<kBwdTail, 64, 128>(stream, p, nullptr, stop); else launch_gemm<kBwdTail, 64, 64>(stream, p, nullptr, stop); }
+    else                       { if (wide) launch_gemm<kBwdOnly, 64, 128>(stream, p, nullptr, stop); else launch_gemm<kBwdOnly, 64, 64>(stream, p, nullptr, stop); }
     return hipGetLastError();
 }
 
