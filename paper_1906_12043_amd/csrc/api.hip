@@ -299,12 +299,17 @@ void release(cocod_ctx *ctx)
     delete ctx;
 }
 
+uint32_t step_state_is_cached(const cocod_ctx *ctx)
+{
+    return 20 * ctx->cfg.stride * static_cast<uint64_t>(ctx->cfg.W) <= kCachedStateBytes ? 1u : 0u;
+}
+
 // Step I arithmetic on `stream`, one launch per bucket.
 int enqueue_mean(cocod_ctx *ctx, hipStream_t stream)
 {
     for (size_t b = 0; b + 1 < ctx->bucket_begin.size(); ++b)
         COCOD_HIP(ctx, cocod::launch_wmean(stream, ctx->snap, ctx->cfg.stride, ctx->cfg.W, ctx->bucket_begin[b],
-                                           ctx->bucket_begin[b + 1], ctx->d_weights, ctx->cfg.mean));
+                                           ctx->bucket_begin[b + 1], ctx->d_weights, ctx->cfg.mean, step_state_is_cached(ctx)));
     return COCOD_OK;
 }
 
@@ -490,11 +495,6 @@ static uint32_t panel_tiles_for(const cocod_ctx *ctx)
     return ctx->padded_d * sizeof(float) > kMeanCacheBytes &&
            (4 * ctx->chunks.size() + kPanelTiles) * static_cast<uint64_t>(ctx->cfg.W) * 64 < kMaxThreadsPerGridDim
                ? kPanelTiles : 0u;
-}
-
-static uint32_t step_state_is_cached(const cocod_ctx *ctx)
-{
-    return 20 * ctx->cfg.stride * static_cast<uint64_t>(ctx->cfg.W) <= kCachedStateBytes ? 1u : 0u;
 }
 
 // The next launch, if it carries line 6, can also form the round's mean itself (a whole round in one launch under the

@@ -42,30 +42,34 @@ __device__ __forceinline__ void st4_stream(float *p, const float4 &a)
     __builtin_nontemporal_store(f4v{a.x, a.y, a.z, a.w}, reinterpret_cast<f4v *>(p));
 }
 
-// Ordered weighted sum over the rows of one column quad.
-template <bool WEIGHTED>
+// Ordered weighted sum over the rows of one column quad.  CACHED: ordinary loads, where the models are read again soon.
+template <bool WEIGHTED, bool CACHED>
 __device__ __forceinline__ float4 column_mean(const float *col, uint64_t stride, uint32_t W, const float *weights)
 {
+    auto load = [](const float *p) { return CACHED ? ld4(p) : ld4_stream(p); };
     MeanSum acc;
     acc.clear();
     uint32_t i = 0;
     for (; i + kRowBatch <= W; i += kRowBatch) {
         float4 r[kRowBatch];
         #pragma unroll
-        for (int b = 0; b < kRowBatch; ++b) r[b] = ld4_stream(col + static_cast<uint64_t>(i + b) * stride);
+        for (int b = 0; b < kRowBatch; ++b) r[b] = load(col + static_cast<uint64_t>(i + b) * stride);
         #pragma unroll
         for (int b = 0; b < kRowBatch; ++b)
             acc.add<WEIGHTED>(WEIGHTED ? weights[i + b] : 1.0f, r[b].x, r[b].y, r[b].z, r[b].w);
     }
     for (; i < W; ++i) {
-        const float4 r = ld4_stream(col + static_cast<uint64_t>(i) * stride);
+        const float4 r = load(col + static_cast<uint64_t>(i) * stride);
         acc.add<WEIGHTED>(WEIGHTED ? weights[i] : 1.0f, r.x, r.y, r.z, r.w);
     }
     acc.finish<WEIGHTED>(W);
     return make_float4(acc.s[0], acc.s[1], acc.s[2], acc.s[3]);
 }
 
-template <bool WEIGHTED>
+// CACHED: a state that stays in the last-level cache (step_state_is_cached): the step beside or behind reads the same models.
+// Rounds of k = 2 with line 6 in the last step, mean in front of the steps, one context, streaming / ordinary loads: W = 8, d = 250 k
+// 13.1 / 12.7 us, d = 1 M 41.8 / 39.4, W = 16, d = 700 k 49.3 / 48.6; three contexts in turn 11.8 / 11.1, 39.0 / 38.6, 54.3 / 53.3.
+template <bool WEIGHTED, bool CACHED>
 __global__ __launch_bounds__(kAvgThreads) void wmean_kernel(const float *snap, uint64_t stride, uint32_t W,
                                                             uint64_t begin, uint64_t n_quads,
                                                             const float *weights, float *mean)
@@ -76,7 +80,7 @@ __global__ __launch_bounds__(kAvgThreads) void wmean_kernel(const float *snap, u
     const uint64_t quad = static_cast<uint64_t>(blockIdx.x) * kAvgThreads + threadIdx.x;
     if (quad >= n_quads) return;
     const uint64_t e = begin + quad * 4;
-    st4(mean + e, column_mean<WEIGHTED>(snap + e, stride, W, weights));
+    st4(mean + e, column_mean<WEIGHTED, CACHED>(snap + e, stride, W, weights));
 }
 
 __device__ __forceinline__ void correct_column(float *xcol, const float *scol, const float4 m, uint64_t stride, uint32_t W)
@@ -135,7 +139,7 @@ __global__ __launch_bounds__(kAvgThreads, mean_correct_waves(R)) void mean_corre
     if (group >= n_groups) return;
     const uint64_t e = begin + group * V;
     if constexpr (R == 0) {
-        const float4 m = column_mean<WEIGHTED>(snap + e, stride, W, weights);
+        const float4 m = column_mean<WEIGHTED, false>(snap + e, stride, W, weights);
         st4(mean + e, m);
         correct_column(x + e, snap + e, m, stride, W);
     } else {
@@ -187,29 +191,6 @@ __global__ __launch_bounds__(kAvgThreads, mean_correct_waves(R)) void mean_corre
 // (the quantity bounded by Lemma 2 of the paper).  A scalar, so this is where wave and LDS reductions
 // belong: per thread a column quad or pair, then a butterfly over the wave, the four wave sums through LDS, one double
 // per block; a second one-block kernel adds the block partials in a fixed order, so the result is deterministic.
-// the same mean with ordinary (cached) loads, for the kernels that read the models a second time
-template <bool WEIGHTED>
-__device__ __forceinline__ float4 column_mean_cached(const float *col, uint64_t stride, uint32_t W, const float *weights)
-{
-    MeanSum acc;
-    acc.clear();
-    uint32_t i = 0;
-    for (; i + kRowBatch <= W; i += kRowBatch) {
-        float4 r[kRowBatch];
-        #pragma unroll
-        for (int b = 0; b < kRowBatch; ++b) r[b] = ld4(col + static_cast<uint64_t>(i + b) * stride);
-        #pragma unroll
-        for (int b = 0; b < kRowBatch; ++b)
-            acc.add<WEIGHTED>(WEIGHTED ? weights[i + b] : 1.0f, r[b].x, r[b].y, r[b].z, r[b].w);
-    }
-    for (; i < W; ++i) {
-        const float4 r = ld4(col + static_cast<uint64_t>(i) * stride);
-        acc.add<WEIGHTED>(WEIGHTED ? weights[i] : 1.0f, r.x, r.y, r.z, r.w);
-    }
-    acc.finish<WEIGHTED>(W);
-    return make_float4(acc.s[0], acc.s[1], acc.s[2], acc.s[3]);
-}
-
 __device__ __forceinline__ double wave_sum_f64(double v)
 {
     #pragma unroll
@@ -261,7 +242,7 @@ __global__ __launch_bounds__(kStepThreads, R > 16 ? 3 : 4) void consensus_partia
                 if (static_cast<uint32_t>(i) < W) add_row(i, r[i]);
         } else {
             static_assert(V == 4, "column quads");
-            const float4 mean = column_mean_cached<WEIGHTED>(col, stride, W, weights);
+            const float4 mean = column_mean<WEIGHTED, true>(col, stride, W, weights);
             m[0] = mean.x; m[1] = mean.y; m[2] = mean.z; m[3] = mean.w;
             uint32_t i = 0;
             for (; i + kRowBatch <= W; i += kRowBatch) {
@@ -331,7 +312,7 @@ __global__ __launch_bounds__(kStepThreads) void objective_partial_kernel(const C
     if (e < ck.n) {
         const uint64_t at = static_cast<uint64_t>(ck.mem_quad) * 4 + e;
         const float uniform = 1.0f / static_cast<float>(W);
-        const float4 m = column_mean_cached<WEIGHTED>(x + at, stride, W, weights);
+        const float4 m = column_mean<WEIGHTED, true>(x + at, stride, W, weights);
         float4 f = make_float4(0.f, 0.f, 0.f, 0.f), g = make_float4(0.f, 0.f, 0.f, 0.f);
         auto add_row = [&](uint32_t i, const float4 &hr, const float4 &cr) {
             const float pw = WEIGHTED ? weights[i] : uniform;
@@ -376,14 +357,16 @@ inline uint32_t blocks_for(uint64_t n_quads) { return static_cast<uint32_t>((n_q
 }  // namespace
 
 hipError_t launch_wmean(hipStream_t stream, const float *snap, uint64_t stride, uint32_t W, uint64_t begin,
-                        uint64_t end, const float *weights, float *mean)
+                        uint64_t end, const float *weights, float *mean, bool cached)
 {
     const uint64_t n_quads = (end - begin) / 4;
     if (n_quads == 0) return hipSuccess;
-    const dim3 grid(blocks_for(n_quads)), block(kAvgThreads);
-    if (weights) hipLaunchKernelGGL((wmean_kernel<true>), grid, block, 0, stream, snap, stride, W, begin, n_quads, weights, mean);
-    else         hipLaunchKernelGGL((wmean_kernel<false>), grid, block, 0, stream, snap, stride, W, begin, n_quads, weights, mean);
-    return hipGetLastError();
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(blocks_for(n_quads)), dim3(kAvgThreads), 0, stream, snap, stride, W, begin, n_quads, weights, mean);
+        return hipGetLastError();
+    };
+    if (cached) return weights ? launch(wmean_kernel<true, true>) : launch(wmean_kernel<false, true>);
+    return weights ? launch(wmean_kernel<true, false>) : launch(wmean_kernel<false, false>);
 }
 
 hipError_t launch_mean_correct(hipStream_t stream, float *x, const float *snap, uint64_t stride, uint32_t W,
