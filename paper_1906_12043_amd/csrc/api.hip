@@ -132,14 +132,16 @@ constexpr uint32_t kPanelTiles = 16384;
 // workers of a line-6 step read it one after the other.
 constexpr uint64_t kMeanCacheBytes = 128ull << 20;
 // Steps access a state (both model buffers, v, h, c: 20 bytes per worker-parameter) up to this size without the
-// streaming hint: the next step finds it in the last-level cache.  k = 8 rounds, hint / no hint: W = 8, d = 250 k
-// (40 MB) 84 / 70 us, W = 16, d = 400 k (128 MB) 220 / 207, d = 700 k (224 MB) 367 / 338, d = 1 M (320 MB) 514 / 479 but
-// with three such contexts in turn 518 / 570, d = 2 M (640 MB) 992 / 1125.
-// The count is the same for every kind of context; those without momentum or with the caller's gradient hold less.  At
-// 40 / 128 / 224 MB so counted: no momentum 61 / 60, 156 / 148, 252 / 235; caller's fp32 gradient 76 / 61, 197 / 180,
-// 315 / 291, without momentum 62 / 62, 132 / 124, 205 / 190; 16-bit gradient 74 / 62, 182 / 169, 290 / 269, without
-// momentum 63 / 61, 122 / 112, 187 / 168.  Two to four contexts in turn, 160 to 233 MB each: 4 to 9 % faster without the
-// hint in 26 of 32 cases, within 1 % in three, 9 to 10 % slower in three that no size or kind sets apart.
+// streaming hint: the next step or round finds it in the last-level cache.  Rounds, hint / no hint in us, one context and
+// three in turn, at W = 8, d = 250 k (40 MB counted so), W = 16, d = 400 k (128 MB), 700 k (224 MB), 1 M (320 MB), 2 M (640 MB):
+//   quadratic, k = 8 (one launch): 17.8/18.9 and 11.6/11.0; 42.0/42.4 and 40.1/39.2; 69/68 and 68/70; 98/96 and 97/102;
+//     193/199 and 199/207.  k = 1: 12.6/12.4 and 12.0/10.8; 32.0/29.7 and 30.0/29.5; 51.8/48.3 and 52.3/53.1; 73/75 and
+//     73/79; 142/156 and 144/159.  Without momentum, k = 2: 10.5/10.5 and 9.7/9.0; 24/23 and 21/20; 38.8/35.8 and
+//     37.2/36.4; 54/55 and 53/56; 102/109 and 103/114.
+//   the caller's gradient, k = 8 (eight launches): 62/49 and 53/52; 182/168 and 174/162; 304/279 and 302/281; 429/397 and
+//     428/439; 835/908 and 868/955.
+// The count is the same for every kind of context; those without momentum or with the caller's gradient hold less.  With a
+// 16-bit gradient, k = 8, 40 / 128 / 224 MB: 74/62, 182/169, 290/269, without momentum 63/61, 122/112, 187/168.
 constexpr uint64_t kCachedStateBytes = 224ull << 20;
 // Local steps per launch with the built-in quadratic gradient.  The gradient of a coordinate depends on nothing but that
 // coordinate, so a wave takes its tile through several steps in registers: 24 bytes per parameter once, not per step (a real
