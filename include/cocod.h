@@ -175,8 +175,8 @@ int cocod_destroy(cocod_ctx *ctx);
  * stored model and writes the other model buffer, so storing x_t^i costs no copy.
  * The built-in quadratic gradient of a coordinate depends on that coordinate alone, so its k steps are
  * taken up to 16 to a launch, in registers, with the bits of one launch per step (also inside
- * cocod_local_steps_end_apply and cocod_graph_round); while step timing is armed every step is a
- * launch of its own.  The other gradients need the whole model between two steps.
+ * cocod_local_steps_end_apply and cocod_graph_round); while step timing is armed every step of an
+ * eager call is a launch of its own (replayed rounds are never timed).  The other gradients need the whole model between two steps.
  */
 int cocod_local_steps(cocod_ctx *ctx, int k);
 
@@ -245,7 +245,8 @@ int cocod_external_step_bf16(cocod_ctx *ctx, const uint16_t *g, int close_round)
 /*
  * One whole pass of the while-loop body of Algorithm 1 (Step I and Step II side by side, then line
  * 6 and line 7) replayed from a HIP graph: the same kernels, in the same order and, where the models
- * are large enough for it to pay, on the same two branches, as cocod_average_begin + cocod_local_steps(k) + cocod_average_end_apply (fused_tail == 0)
+ * are large enough for it to pay, on the same two branches, as cocod_average_begin +
+ * cocod_local_steps(k) + cocod_average_end_apply (fused_tail == 0)
  * or cocod_average_begin + cocod_local_steps_end_apply(k) (fused_tail != 0), with bit-identical
  * results, but submitted with ONE call instead of one per kernel and event: for small models, where
  * the launches and not the memory traffic bound a round.  The first call for a given (k, fused_tail,
