@@ -51,8 +51,8 @@ struct cocod_ctx {
     bool dry = false;
     bool timing = false;                // bracket step launches with start/stop events
     std::vector<hipEvent_t> t_start, t_stop;   // event pool for step timing (owned)
-    std::vector<char> t_kind;           // per timed launch: 0 plain step, 1 step with line 6
-    size_t t_used = 0;
+    std::vector<char> t_kind;           // per timed launch: 0 plain step, 1 step with line 6, 2 step that forms the mean
+    size_t t_used = 0, t_limit = 0;     // steps timed since the last read, steps to time (the pool may hold more events)
     // replayable rounds: one instantiated graph per (k, variant, schedule, which buffer is live)
     struct RoundGraph { int k; int fused_tail; int schedule; bool live_is_A; uint32_t batch_buf; bool batch_ready; hipGraphExec_t exec; };
     std::vector<RoundGraph> graphs;     // owned
@@ -508,11 +508,13 @@ static bool one_pass_applies(const cocod_ctx *ctx)
            ctx->chunks.size() < kMaxChunksMeanStep;
 }
 
+// Step timing: the next local step is one of those that were asked for, a launch of its own with timestamps.
+static bool next_step_is_timed(const cocod_ctx *ctx) { return ctx->timing && ctx->t_used < ctx->t_limit; }
+
 // Local steps that the next launch takes, of `left` still to take.
 static uint32_t steps_per_launch(const cocod_ctx *ctx, int left)
 {
-    const bool timed = ctx->timing && ctx->t_used < ctx->t_start.size();      // step timing: one launch per step
-    if (ctx->cfg.grad != COCOD_GRAD_QUADRATIC || timed) return 1u;
+    if (ctx->cfg.grad != COCOD_GRAD_QUADRATIC || next_step_is_timed(ctx)) return 1u;
     return static_cast<uint32_t>(left < kMaxStepsPerLaunch ? left : kMaxStepsPerLaunch);
 }
 
@@ -558,7 +560,7 @@ static int enqueue_step(cocod_ctx *ctx, uint32_t steps, bool with_line6, const v
         p.round_steps = ctx->capture_steps;
         p.snap = with_line6 ? ctx->snap : nullptr;
         p.mean = ctx->cfg.mean;
-        const bool timed = ctx->timing && ctx->t_used < ctx->t_start.size();
+        const bool timed = next_step_is_timed(ctx);
         COCOD_HIP(ctx, cocod::launch_mlp_step(ctx->s_compute, p, timed ? ctx->t_start[ctx->t_used] : nullptr,
                                               timed ? ctx->t_stop[ctx->t_used] : nullptr));
         ctx->batch_last = buf;
@@ -611,7 +613,7 @@ static int enqueue_step(cocod_ctx *ctx, uint32_t steps, bool with_line6, const v
             ctx->mean_pending = false;
         }
         hipEvent_t t0 = nullptr, t1 = nullptr;
-        if (ctx->timing && ctx->t_used < ctx->t_start.size()) {
+        if (next_step_is_timed(ctx)) {
             t0 = ctx->t_start[ctx->t_used];
             t1 = ctx->t_stop[ctx->t_used];
             ctx->t_kind[ctx->t_used] = head ? 2 : (with_line6 ? 1 : 0);
@@ -955,10 +957,11 @@ int cocod_step_timing(cocod_ctx *ctx, int max_launches)
 {
     if (!ctx) return fail(nullptr, COCOD_ERR_INVALID, "ctx is NULL");
     if (max_launches < 0 || max_launches > (1 << 20)) return fail(ctx, COCOD_ERR_INVALID, "max_launches out of range");
-    ctx->timing = max_launches > 0;
+    ctx->timing = false;
     ctx->t_used = 0;
+    ctx->t_limit = 0;
     if (ctx->dry) return COCOD_OK;
-    while (ctx->t_start.size() < static_cast<size_t>(max_launches)) {
+    while (ctx->t_kind.size() < static_cast<size_t>(max_launches)) {
         hipEvent_t a = nullptr, b = nullptr;
         COCOD_HIP(ctx, hipEventCreate(&a));
         ctx->t_start.push_back(a);
@@ -966,6 +969,8 @@ int cocod_step_timing(cocod_ctx *ctx, int max_launches)
         ctx->t_stop.push_back(b);
         ctx->t_kind.push_back(0);
     }
+    ctx->timing = max_launches > 0;
+    ctx->t_limit = static_cast<size_t>(max_launches);
     return COCOD_OK;
 }
 

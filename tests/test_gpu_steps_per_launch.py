@@ -111,3 +111,23 @@ def test_timed_steps_are_launches_of_their_own():
     plain, tail, head = [n for _, n in ctx.step_timing_read()]
     assert (plain, tail, head) == (4, 1, 0) and ctx.get_step() == 9
     ctx.close()
+
+
+def test_no_more_steps_are_timed_than_were_asked_for():
+    """Armed for fewer steps than before: the event pool of the earlier call does not make it more."""
+    dev = torch.device("cuda:0")
+    t = [torch.zeros((2, 1024), device=dev) for _ in range(5)]
+    s = torch.cuda.Stream(device=dev)
+    torch.cuda.synchronize()
+    ctx = P.Context(W=2, d=1000, stride=1024, xA=t[0], xB=t[1], v=t[2], mean=torch.zeros(1024, device=dev), h=t[3], c=t[4], momentum=0.9,
+                    noise_sigma=0.01, compute_stream=s, avg_stream=s, **HYPER)
+    ctx.step_timing(30)
+    ctx.step_timing(2)
+    for _ in range(2):                                               # reading rearms for two again
+        ctx.local_steps(7)
+        ctx.local_steps(3)
+        assert [n for _, n in ctx.step_timing_read()] == [2, 0, 0]
+    ctx.step_timing(0)
+    ctx.local_steps(3)
+    assert [n for _, n in ctx.step_timing_read()] == [0, 0, 0] and ctx.get_step() == 23
+    ctx.close()
