@@ -71,8 +71,9 @@ typedef enum cocod_schedule {
                                   pass of its own; where the round's steps are one launch of
                                   cocod_local_steps_end_apply (k = 1; untimed up to k = 16) the mean,
                                   the steps and line 6 are ONE kernel (built-in quadratic gradient, W <= 131
-                                  workers, d < 2^30; whenever the round's first step is not such a step, the
-                                  mean is formed on compute_stream just before line 6 needs it) */
+                                  workers, d < 2^30; whenever the round's first step is not such a step, or one
+                                  of several in a launch whose blocks, one for all workers, would leave much of
+                                  the chip idle, the mean is formed on compute_stream just before line 6 needs it) */
 } cocod_schedule;
 
 enum {

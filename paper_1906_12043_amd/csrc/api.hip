@@ -151,6 +151,15 @@ constexpr uint64_t kCachedStateBytes = 224ull << 20;
 // 432, 4 538; a round of the overlapped schedule with line 6 inside the last step at k = 2 1638 -> 835 us, at W = 12,
 // d = 3.0 M, k = 4 with line 6 apart 668 -> 241, Local SGD at W = 21, d = 4.0 M, k = 2 777 -> 458.
 constexpr int kMaxStepsPerLaunch = 16;
+// A launch of several steps that forms the mean itself holds all workers' rows of a tile in one block of at most sixteen waves, one
+// block or two to a compute unit, so with fewer blocks than compute units the others have no part in the steps.  A unit
+// takes 8 element steps a nanosecond; where the steps would wait longer than 10 us for the idle units, the mean stays a
+// kernel of its own (which costs a round 2 to 8 us) and the steps spread over the chip.  Rounds with line 6 inside, one launch
+// per step / all in the mean's launch / mean apart, us: W = 64, d = 1500, k = 8 37 / 46 / 9.1, k = 16 62 / 85 / 11; W = 131,
+// d = 6000, k = 8 46 / 48 / 17; W = 48, d = 14 000, k = 8 42 / 36 / 11; on the other side of the line W = 24, d = 6000, k = 2 11 / 8.1 / 7.3,
+// W = 17, d = 60 000, k = 4 25 / 11.6 / 9.9, W = 131, d = 30 000, k = 2 37 / 25 / 27, W = 16, d = 14 000, k = 8 28 / 8.5 / 7.9.
+// With line 6 apart, W = 64, d = 1500, k = 8 38 / 48 / 18; W = 131, d = 14 000, k = 2 28 / 23 / 33, k = 4, already apart, 40 / 33 / 35.
+constexpr uint64_t kIdleElementSteps = 80000;     // per compute unit
 // Models of all workers up to this size are averaged on the one branch of a replayed round: reading them takes a few
 // microseconds, fork and join between two branches more, and above all when several contexts replay rounds at a time.
 // Perceptron rounds of k = 2, two branches / one, three contexts in turn (one context alone): W = 4, 768-192-10 (2.4 MB of
@@ -499,13 +508,17 @@ static uint32_t panel_tiles_for(const cocod_ctx *ctx)
                ? kPanelTiles : 0u;
 }
 
-// The next launch, if it carries line 6, can also form the round's mean itself (a whole round in one launch under the
-// schedule that folds Step I into Step II: it reads exactly the stored models).
-static bool one_pass_applies(const cocod_ctx *ctx)
+// The next launch, of `steps` steps and with line 6 or without, can also form the round's mean itself: under the schedule that
+// folds Step I into Step II the round's first launch reads exactly the stored models.
+static bool step_forms_mean(const cocod_ctx *ctx, uint32_t steps, bool with_line6)
 {
-    return ctx->schedule == COCOD_SCHED_HEAD && ctx->mean_pending && ctx->store_pending &&
-           ctx->cfg.grad == COCOD_GRAD_QUADRATIC && cocod::local_step_mean_quads_per_lane(ctx->cfg.W, true) != 0 &&
-           ctx->chunks.size() < kMaxChunksMeanStep;
+    if (ctx->schedule != COCOD_SCHED_HEAD || !ctx->mean_pending || !ctx->store_pending ||
+        ctx->cfg.grad != COCOD_GRAD_QUADRATIC || ctx->chunks.size() >= kMaxChunksMeanStep) return false;
+    const uint64_t quads = static_cast<uint64_t>(cocod::local_step_mean_quads_per_lane(ctx->cfg.W, with_line6));
+    if (quads == 0) return false;
+    if (steps == 1) return true;
+    const uint64_t blocks = ctx->chunks.size() * (4 / quads), idle = blocks < ctx->compute_units ? ctx->compute_units - blocks : 0;
+    return steps * ctx->cfg.W * quads * 256 * idle <= kIdleElementSteps * ctx->compute_units;
 }
 
 // Step timing: the next local step is one of those that were asked for, a launch of its own with timestamps.
@@ -599,15 +612,10 @@ static int enqueue_step(cocod_ctx *ctx, uint32_t steps, bool with_line6, const v
         p.round_steps = ctx->capture_steps;
         p.panel_tiles = panel_tiles_for(ctx);
         p.cached = step_state_is_cached(ctx);
-        // Step I inside the round's first step: that step reads exactly the stored models (when there are
-        // too many workers for its LDS tile, the mean stays pending and is formed just before line 6)
-        const bool head = ctx->schedule == COCOD_SCHED_HEAD && ctx->mean_pending && ctx->store_pending && !g_ext &&
-                          !with_line6 && ctx->cfg.grad == COCOD_GRAD_QUADRATIC &&
-                          cocod::local_step_mean_quads_per_lane(ctx->cfg.W, false) != 0 &&
-                          ctx->chunks.size() < kMaxChunksMeanStep;
-        // a whole round in this launch under the same schedule: mean, steps and line 6 in one pass over the stored models
-        const bool one_pass = with_line6 && !g_ext && one_pass_applies(ctx);
-        if (head || one_pass) {
+        // Step I inside the round's first launch, with line 6 in the same one a whole round in one pass over the stored models
+        // (where that does not apply, the mean stays pending and is formed just before line 6)
+        const bool forms_mean = !g_ext && step_forms_mean(ctx, steps, with_line6);
+        if (forms_mean) {
             p.mean_out = ctx->cfg.mean;
             p.weights = ctx->d_weights;
             ctx->mean_pending = false;
@@ -616,7 +624,7 @@ static int enqueue_step(cocod_ctx *ctx, uint32_t steps, bool with_line6, const v
         if (next_step_is_timed(ctx)) {
             t0 = ctx->t_start[ctx->t_used];
             t1 = ctx->t_stop[ctx->t_used];
-            ctx->t_kind[ctx->t_used] = head ? 2 : (with_line6 ? 1 : 0);
+            ctx->t_kind[ctx->t_used] = with_line6 ? 1 : (forms_mean ? 2 : 0);
             ctx->t_used += 1;
         }
         COCOD_HIP(ctx, cocod::launch_local_step(ctx->s_compute, p, t0, t1));
@@ -701,7 +709,7 @@ int cocod_local_steps_end_apply(cocod_ctx *ctx, int k)
     for (int left = k; left > 0;) {
         const uint32_t n = steps_per_launch(ctx, left);
         left -= static_cast<int>(n);
-        if (left == 0 && !ctx->dry && !one_pass_applies(ctx)) {
+        if (left == 0 && !ctx->dry && !step_forms_mean(ctx, n, true)) {
             // the mean must be complete before the last launch starts: it is consumed inside it
             rc = mean_before_line6(ctx);
             if (rc != COCOD_OK) return rc;

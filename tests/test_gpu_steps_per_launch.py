@@ -90,6 +90,56 @@ def test_options_and_worker_counts(W, momentum, sigma, weighted, schedule):
             assert same(run(W, [d], 4, call, schedule, False, **kw), run(W, [d], 4, call, schedule, True, **kw)), (d, call)
 
 
+@pytest.mark.parametrize("call", ["tail", "separate", "graph"])
+@pytest.mark.parametrize("W,d,k", [(64, 3000, 4), (64, 70_001, 4), (64, 70_001, 8), (131, 1500, 3), (131, 1500, 8), (131, 70_001, 16),
+                                   (48, 1283, 3), (48, 1283, 4), (16, 1283, 16)])
+def test_mean_inside_and_apart_from_a_launch_of_several_steps(W, d, k, call):
+    """Under the head schedule, with enough blocks or few enough element steps for the launch to form the mean, and with too
+    few blocks for it."""
+    want = run(W, [d], k, "tail" if call == "graph" else call, P.SCHED_HEAD, True)
+    assert same(run(W, [d], k, call, P.SCHED_HEAD, False), want)
+
+
+@pytest.mark.parametrize("call", ["tail", "separate"])
+@pytest.mark.parametrize("W,d,k", [(64, 1500, 8), (131, 1500, 8), (64, 3000, 16)])
+def test_one_launch_is_no_slower_than_one_launch_per_step_with_few_blocks(W, d, k, call):
+    """Many workers on a short vector under the head schedule: blocks of all workers' rows would leave the chip idle (45 us
+    against 37 with one launch per step at W = 64, d = 1500, k = 8 in such blocks, 9 us otherwise)."""
+    dev = torch.device("cuda:0")
+    stride = (d + 1023) // 1024 * 1024
+    x, xB, v, h, c = [torch.zeros((W, stride), device=dev) for _ in range(5)]
+    mean = torch.zeros(stride, device=dev)
+    s = torch.cuda.Stream(device=dev)
+    torch.cuda.synchronize()
+    ctx = P.Context(W=W, d=d, stride=stride, xA=x, xB=xB, v=v, mean=mean, h=h, c=c, momentum=0.9, noise_sigma=0.01, compute_stream=s,
+                    avg_stream=s, **HYPER)
+    ctx.set_schedule(P.SCHED_HEAD)
+
+    def step_by_step():
+        ctx.average_begin()
+        for i in range(k):
+            ctx.local_steps_end_apply(1) if call == "tail" and i == k - 1 else ctx.local_steps(1)
+        if call == "separate":
+            ctx.average_end_apply()
+
+    def milliseconds(body):
+        times = []
+        for _ in range(9):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record(s)
+            for _ in range(50):
+                body()
+            b.record(s)
+            s.synchronize()
+            times.append(a.elapsed_time(b))
+        return sorted(times)[4]
+    together = milliseconds(lambda: ctx.round_fused_tail(k) if call == "tail" else ctx.round(k))
+    single = milliseconds(step_by_step)
+    ctx.close()
+    print("W=%d d=%d k=%d %s: %.1f us together, %.1f us step by step" % (W, d, k, call, together * 20, single * 20))
+    assert together < single
+
+
 @pytest.mark.parametrize("call", ["tail", "separate"])
 @pytest.mark.parametrize("sizes,extra", [([3, 1_300_001, 1055, 2_750_002], 0), ([4_050_001], 12), ([34_000_003], 0)])
 def test_streaming_and_panels(sizes, extra, call):
