@@ -102,6 +102,18 @@ class GpuWorkers:
         self.ctx.close()
 
 
+def one_round(ctx, k, fused_tail, step_by_step=False):
+    """A round, its local steps in one call (the quadratic gradient's up to sixteen to a launch) or one call and launch each."""
+    if not step_by_step or k == 0:
+        ctx.round_fused_tail(k) if fused_tail else ctx.round(k)
+        return
+    ctx.average_begin()
+    for i in range(k):
+        ctx.local_steps_end_apply(1) if fused_tail and i == k - 1 else ctx.local_steps(1)
+    if not fused_tail:
+        ctx.average_end_apply()
+
+
 def rel_err(got, want):
     """max |got - want| / (1 + |want|): the parity measure of the target."""
     return float(np.max(np.abs(got - want) / (1.0 + np.abs(want))))

@@ -30,8 +30,11 @@ def edge_columns(d, starts=()):
 
 
 def subset_parity(cfg, k, n_random=100_000, tensor_numel=None, bucket_bytes=0, stable_rounds=None, fused_tail=False,
-                  graph=False, schedule=None):
+                  graph=False, schedule=None, step_by_step=False):
     """Runs cfg["rounds"] rounds on the GPU (full size) and in the oracle (sampled columns).
+
+    step_by_step: every local step a launch of its own, timed, as the benchmark's headline runs it (else a round's steps are
+    one launch); the launches counted at the end say which kernels ran.
 
     stable_rounds: for an iteration whose round map is expanding (see the k = 8 case below) the
     1e-5 bar is checked after that many rounds; at the end the GPU must be as close to the fp64
@@ -52,6 +55,8 @@ def subset_parity(cfg, k, n_random=100_000, tensor_numel=None, bucket_bytes=0, s
     mirror = orc.QuadraticOracle(h, c, idx=cols, kind="f32", **hyper_of(cfg)) if stable_rounds else None
     if schedule is not None:
         g.ctx.set_schedule(schedule)
+    if step_by_step:
+        g.ctx.step_timing(cfg["rounds"] * k)
     for r in range(cfg["rounds"]):
         if graph:
             g.ctx.graph_round(k, fused_tail)   # the round replayed from a HIP graph
@@ -66,6 +71,11 @@ def subset_parity(cfg, k, n_random=100_000, tensor_numel=None, bucket_bytes=0, s
                 assert rel_err(g.x(ii), o.x) <= TOL
     ex, ev, em = rel_err(g.x(ii), o.x), rel_err(g.vel(ii), o.v), rel_err(g.avg(ii), o.mean)
     print("%d columns, k=%d, %d rounds: rel err x %.3g v %.3g mean %.3g" % (cols.size, k, cfg["rounds"], ex, ev, em))
+    if step_by_step:                           # plain steps, steps with line 6, first steps that form the mean
+        n = cfg["rounds"]
+        heads = n if schedule == P.SCHED_HEAD and (k > 1 or not fused_tail) else 0
+        tails = n if fused_tail else 0
+        assert [c for _, c in g.ctx.step_timing_read()] == [n * k - tails - heads, tails, heads]
     g.close()
     if mirror is None:
         assert ex <= TOL and em <= TOL and ev <= 10 * TOL
@@ -96,35 +106,38 @@ def test_resnet18_size_full_vector_three_rounds():
     assert abs(cons - want_cons) <= 1e-5 * want_cons and abs(f - want_f) <= 1e-5 * want_f and abs(g2 - want_g2) <= 1e-5 * want_g2
 
 
-@pytest.mark.parametrize("k", [1, 2, 4])
-def test_resnet18_size_fifty_rounds_sampled(k):
-    subset_parity(synth_inputs.CONFIGS["C2_resnet18"], k)
+@pytest.mark.parametrize("k,step_by_step", [(1, False), (2, False), (4, False), (2, True), (4, True)])
+def test_resnet18_size_fifty_rounds_sampled(k, step_by_step):
+    subset_parity(synth_inputs.CONFIGS["C2_resnet18"], k, step_by_step=step_by_step)
 
 
+@pytest.mark.parametrize("step_by_step", [False, True])
 @pytest.mark.parametrize("fused_tail", [False, True])
-def test_vgg16_size_twenty_rounds_sampled(fused_tail):
-    # with line 6 inside the last step this size also takes the worker-fastest block order (mean > cache)
-    subset_parity(synth_inputs.CONFIGS["C3_vgg16"], 2, fused_tail=fused_tail)
+def test_vgg16_size_twenty_rounds_sampled(fused_tail, step_by_step):
+    # with line 6 inside the last step this size also takes its blocks panel by panel (mean > cache); that step reads the stored
+    # models as its input where it is the round's only launch, beside it step by step
+    subset_parity(synth_inputs.CONFIGS["C3_vgg16"], 2, fused_tail=fused_tail, step_by_step=step_by_step)
 
 
-@pytest.mark.parametrize("k", [1, 2])
-def test_resnet18_size_fifty_rounds_sampled_line6_in_last_step(k):
-    subset_parity(synth_inputs.CONFIGS["C2_resnet18"], k, fused_tail=True)
+@pytest.mark.parametrize("k,step_by_step", [(1, False), (2, False), (2, True)])
+def test_resnet18_size_fifty_rounds_sampled_line6_in_last_step(k, step_by_step):
+    subset_parity(synth_inputs.CONFIGS["C2_resnet18"], k, fused_tail=True, step_by_step=step_by_step)
 
 
 def bucketed_sizes(cfg):
     return synth_inputs.tensor_sizes(cfg["seed"], cfg["n_tensors"], cfg["d"], cfg["tensor_lo"], cfg["tensor_hi"])
 
 
-@pytest.mark.parametrize("graph,schedule", [(True, None), (False, P.SCHED_HEAD), (True, P.SCHED_HEAD)])
-def test_resnet18_size_fifty_rounds_sampled_graph_and_head_schedule(graph, schedule):
+@pytest.mark.parametrize("graph,schedule,step_by_step", [(True, None, False), (False, P.SCHED_HEAD, False), (True, P.SCHED_HEAD, False),
+                                                         (False, P.SCHED_HEAD, True)])
+def test_resnet18_size_fifty_rounds_sampled_graph_and_head_schedule(graph, schedule, step_by_step):
     """The benchmark's other launch configurations at full size: rounds replayed from a graph, and the
-    mean formed inside the first local step."""
-    subset_parity(synth_inputs.CONFIGS["C2_resnet18"], 2, fused_tail=True, graph=graph, schedule=schedule)
+    mean formed inside the first local step (step by step) or a whole round of two steps in ONE kernel."""
+    subset_parity(synth_inputs.CONFIGS["C2_resnet18"], 2, fused_tail=True, graph=graph, schedule=schedule, step_by_step=step_by_step)
 
 
 def test_resnet18_size_fifty_rounds_sampled_one_pass_rounds():
-    """k = 1 under the head schedule: Step I, the local step and line 6 in ONE kernel per round."""
+    """k = 1 under the head schedule: Step I, the local step and line 6 in ONE kernel per round, as for every k up to 16."""
     subset_parity(synth_inputs.CONFIGS["C2_resnet18"], 1, fused_tail=True, schedule=P.SCHED_HEAD)
 
 
@@ -134,11 +147,19 @@ def test_bucketed_tensor_list_sampled_head_schedule_from_graph():
                   schedule=P.SCHED_HEAD)
 
 
-@pytest.mark.parametrize("k,fused_tail", [(1, False), (2, False), (4, False), (2, True)])
-def test_bucketed_tensor_list_sampled(k, fused_tail):
+def test_bucketed_tensor_list_sampled_head_schedule_step_by_step():
+    """The mean inside the first step, line 6 inside the second."""
+    cfg = synth_inputs.CONFIGS["C5_bucketed"]
+    subset_parity(cfg, 2, tensor_numel=bucketed_sizes(cfg), bucket_bytes=cfg["bucket_bytes"], fused_tail=True,
+                  schedule=P.SCHED_HEAD, step_by_step=True)
+
+
+@pytest.mark.parametrize("k,fused_tail,step_by_step", [(1, False, False), (2, False, False), (4, False, False), (2, True, False),
+                                                       (4, False, True), (2, True, True)])
+def test_bucketed_tensor_list_sampled(k, fused_tail, step_by_step):
     cfg = synth_inputs.CONFIGS["C5_bucketed"]
     subset_parity(cfg, k, n_random=50_000, tensor_numel=bucketed_sizes(cfg), bucket_bytes=cfg["bucket_bytes"],
-                  fused_tail=fused_tail)
+                  fused_tail=fused_tail, step_by_step=step_by_step)
 
 
 def test_bucketed_tensor_list_sampled_k8_expanding_round_map():

@@ -7,7 +7,7 @@ import torch
 import paper_1906_12043_amd as P
 import synth_inputs
 from oracle import cocod_oracle as orc
-from tests.gpu_harness import GpuWorkers, rel_err
+from tests.gpu_harness import GpuWorkers, one_round, rel_err
 
 pytestmark = pytest.mark.gpu
 TOL = 1e-5
@@ -145,8 +145,9 @@ def test_single_worker_first_round_is_exactly_plain_sgd():
     a.close(); b.close()
 
 
+@pytest.mark.parametrize("step_by_step", [False, True])
 @pytest.mark.parametrize("W", [4, 16, 64])
-def test_identical_workers_without_noise_follow_one_worker_bit_for_bit(W):
+def test_identical_workers_without_noise_follow_one_worker_bit_for_bit(W, step_by_step):
     """Same h, c on every worker and no noise: the mean of W equal values is exact for a power of two,
     so every worker retraces the single-worker rounds bit for bit."""
     d, k = 5001, 2
@@ -157,7 +158,7 @@ def test_identical_workers_without_noise_follow_one_worker_bit_for_bit(W):
     o = orc.QuadraticOracle(h1, c1, **hyper)
     for r in range(4):
         for g in (one, many):
-            g.ctx.round(k) if r % 2 else g.ctx.round_fused_tail(k)
+            one_round(g.ctx, k, r % 2 == 0, step_by_step)
         o.round(k)
     x1, xm = one.x_raw()[:, :d], many.x_raw()[:, :d]
     assert all(torch.equal(xm[i], x1[0]) for i in range(W))
@@ -202,7 +203,8 @@ def test_weighted_mean():
     g.close()
 
 
-def test_heterogeneous_workers_weighted_mean_and_per_worker_noise():
+@pytest.mark.parametrize("step_by_step", [False, True])
+def test_heterogeneous_workers_weighted_mean_and_per_worker_noise(step_by_step):
     """Workers with mini-batch sizes M_i: mean weights M_i / sum M and noise sigma / sqrt(M_i)."""
     W, k = 5, 3
     sizes = [1030, 7, 4099, 2]
@@ -215,10 +217,7 @@ def test_heterogeneous_workers_weighted_mean_and_per_worker_noise():
     g = GpuWorkers(W, d, h=h, c=c, tensor_numel=sizes, weights=p, noise_sigma_w=sigma_w, **hyper)
     o = orc.QuadraticOracle(h, c, weights=p, noise_sigma_w=sigma_w, **hyper)
     for r in range(4):
-        if r % 2:
-            g.ctx.round_fused_tail(k)
-        else:
-            g.ctx.round(k)
+        one_round(g.ctx, k, r % 2 == 1, step_by_step)
         o.round(k)
         check_state(g, o, what="round %d" % r)
     assert abs(g.ctx.consensus_distance() - o.consensus_distance()) <= 1e-5 * o.consensus_distance()
@@ -251,11 +250,13 @@ def test_overlapped_round_is_bit_identical_to_serialised_rounds():
         assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1]), (schedule, two)
 
 
+@pytest.mark.parametrize("step_by_step", [False, True])
 @pytest.mark.parametrize("weights,mu,sigma", [(None, 0.9, 0.01), ([0.1, 0.2, 0.3, 0.15, 0.25], 0.9, 0.01), (None, 0.0, 0.01),
                                               ([0.1, 0.2, 0.3, 0.15, 0.25], 0.0, 0.0), (None, 0.9, 0.0)])
-def test_mean_formed_inside_the_first_step_gives_the_same_bits(weights, mu, sigma):
+def test_mean_formed_inside_the_first_step_gives_the_same_bits(weights, mu, sigma, step_by_step):
     """COCOD_SCHED_HEAD against the two-stream schedule: packed list with every start alignment, k = 0
-    (no step to ride on), 1 (first step is the last), 2, 3, both ways of applying line 6, mean included."""
+    (no step to ride on), 1 (first step is the last), 2, 3, both ways of applying line 6, mean included.  The mean is
+    formed in the first step of a round, step by step, or in the launch that takes all of them."""
     W = 5
     sizes = [5, 4096, 1, 3, 8191, 64, 4097, 2, 3000, 7]
     d = sum(sizes)
@@ -268,10 +269,7 @@ def test_mean_formed_inside_the_first_step_gives_the_same_bits(weights, mu, sigm
     for k in (2, 3, 1, 0, 2, 1):
         for fused_tail in (False, True):
             for w in (a, b):
-                if fused_tail:
-                    w.ctx.round_fused_tail(k)
-                else:
-                    w.ctx.round(k)
+                one_round(w.ctx, k, fused_tail, step_by_step)
                 w.ctx.sync()
             o.round(k)
             for name in ("live", "v", "mean") if mu else ("live", "mean"):
@@ -281,12 +279,13 @@ def test_mean_formed_inside_the_first_step_gives_the_same_bits(weights, mu, sigm
     a.close(); b.close()
 
 
+@pytest.mark.parametrize("step_by_step", [False, True])
 @pytest.mark.parametrize("W,d", [(16, 20_011), (17, 9_001), (40, 6_003), (65, 3_001), (70, 2_500), (131, 1_100), (140, 1_030), (1, 5_000)])
-def test_head_schedule_for_every_worker_count_class(W, d):
+def test_head_schedule_for_every_worker_count_class(W, d, step_by_step):
     """The mean-forming first step keeps the tile of all W workers in LDS: one column quad per lane up
     to 16 workers, two up to 65, one again up to 131 (the LDS budget), and beyond that the mean is
-    formed by a pass of its own.  Every class, k = 1 (mean, step and line 6 in one pass) and k = 2,
-    against the two-stream schedule bit for bit, mean included, and against the oracle."""
+    formed by a pass of its own.  Every class, k = 1 (mean, step and line 6 in one pass) and k = 2, both steps in one launch
+    and step by step, against the two-stream schedule bit for bit, mean included, and against the oracle."""
     hyper = dict(lr=0.05, momentum=0.9, weight_decay=5e-4, noise_sigma=0.01, seed=79)
     h, c = synth_inputs.quadratic_data(17, W, d)
     a = GpuWorkers(W, d, h=h, c=c, **hyper)
@@ -295,7 +294,7 @@ def test_head_schedule_for_every_worker_count_class(W, d):
     o = orc.QuadraticOracle(h, c, **hyper)
     for k, fused_tail in ((1, True), (2, True), (1, False), (2, False), (1, True)):
         for w in (a, b):
-            w.ctx.round_fused_tail(k) if fused_tail else w.ctx.round(k)
+            one_round(w.ctx, k, fused_tail, step_by_step)
         o.round(k)
         assert np.array_equal(a.x(), b.x()) and np.array_equal(a.vel(), b.vel()) and np.array_equal(a.avg(), b.avg()), (k, fused_tail)
     check_state(b, o, what="head schedule W=%d" % W)
@@ -339,9 +338,9 @@ def test_checkpoint_resume_is_bit_identical():
     a.close(); r.close()
 
 
-@pytest.mark.parametrize("k", [1, 2, 3])
+@pytest.mark.parametrize("k,step_by_step", [(1, False), (2, False), (3, False), (2, True), (3, True)])
 @pytest.mark.parametrize("packed", [False, True])
-def test_line6_inside_last_step_is_bit_identical_to_separate_kernels(k, packed):
+def test_line6_inside_last_step_is_bit_identical_to_separate_kernels(k, packed, step_by_step):
     W, rounds = 5, 4
     sizes = [5, 4096, 1, 3, 8191, 64, 4097, 2, 10000, 7] if packed else None
     d = sum(sizes) if packed else 50_003
@@ -352,14 +351,14 @@ def test_line6_inside_last_step_is_bit_identical_to_separate_kernels(k, packed):
     o = orc.QuadraticOracle(h, c, **hyper)
     for r in range(rounds):
         a.ctx.round(k)
-        b.ctx.round_fused_tail(k)
+        one_round(b.ctx, k, True, step_by_step)
         o.round(k)
         assert not b.ctx.is_averaging() and b.ctx.get_step() == a.ctx.get_step()
     assert np.array_equal(a.x(), b.x()) and np.array_equal(a.vel(), b.vel())
     check_state(b, o, what="fused tail k=%d" % k)
     for sched in (P.SCHED_SERIAL, P.SCHED_FUSED):           # mean taken on the compute stream just before the last step
         b.ctx.set_schedule(sched)
-        a.ctx.round(k); b.ctx.round_fused_tail(k)
+        a.ctx.round(k); one_round(b.ctx, k, True, step_by_step)
         assert np.array_equal(a.x(), b.x())
     b.ctx.average_begin(); b.ctx.local_steps_end_apply(0)    # k = 0: plain line 6
     a.ctx.average_begin(); a.ctx.average_end_apply()

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import paper_1906_12043_amd as P
-from tests.gpu_harness import packed_positions
+from tests.gpu_harness import one_round, packed_positions
 
 pytestmark = pytest.mark.gpu
 W = 3
@@ -39,8 +39,10 @@ def rounds(sizes, extra, momentum, kind, on_device=False):
     ctx = P.Context(W=W, d=d, stride=stride, xA=xA, xB=xB, v=v if momentum else None, mean=mean, h=h, c=c, momentum=momentum,
                     tensor_numel=packed, compute_stream=s, avg_stream=s, **HYPER)
     if kind == "round":
-        ctx.round(2)                                 # plain steps, line 6 alone
-        ctx.round_fused_tail(2)                      # line 6 inside the last step
+        ctx.round(2)                                 # plain steps in one launch, line 6 alone
+        one_round(ctx, 2, False, True)               # plain steps, out of place and in place
+        ctx.round_fused_tail(2)                      # line 6 inside the only launch
+        one_round(ctx, 2, True, True)                # line 6 inside the last step
         ctx.round_fused_tail(1)                      # line 6 inside the only step
     else:
         step, g = (ctx.external_step, h) if kind == "fp32" else (ctx.external_step_bf16, g16)
@@ -99,7 +101,7 @@ def test_panels_off_the_lines_give_the_same_bits(kind):
 @pytest.mark.parametrize("d", [5, 1025, 9000, 70_001])
 def test_mean_forming_steps_off_the_lines_give_the_same_bits(workers, d):
     """Off the lines these steps take their tiles XCD by XCD, with another store policy; tiles in numbers that do and do
-    not divide by the eight dies, k = 1 (one pass) and k = 2 (mean in the first step)."""
+    not divide by the eight dies, k = 1 and 2 in one pass and k = 2 with the mean in the first step."""
     dev = torch.device("cuda:0")
     rng = np.random.default_rng(d)
     base = [torch.from_numpy(rng.standard_normal((workers, d)).astype(np.float32)).to(dev) for _ in range(4)]
@@ -117,6 +119,7 @@ def test_mean_forming_steps_off_the_lines_give_the_same_bits(workers, d):
         ctx.set_schedule(P.SCHED_HEAD)
         ctx.round_fused_tail(1)
         ctx.round_fused_tail(2)
+        one_round(ctx, 2, True, True)
         ctx.sync()
         live = xA if ctx.live_model() == xA.data_ptr() else xB
         got = [live[:, :d].cpu(), v[:, :d].cpu(), mean[:d].cpu()]
