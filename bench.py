@@ -11,9 +11,9 @@ Two ways of running the same round are timed:
   separate    cocod_average_begin; cocod_local_steps(k); cocod_average_end_apply
   fused_tail  cocod_average_begin; cocod_local_steps_end_apply(k)   (line 6 inside the last step)
 The built-in quadratic gradient is separable, so the library takes a round's k steps in one launch unless the step
-timing is armed.  The headline and everything else here keeps it armed: one launch and one pass over memory per step, as
-any real gradient needs.  The k-in-one-launch rounds are reported apart, under "k_steps_in_one_launch" (and the graph
-variants of the k sweep, whose launches are not timed, take their k steps that way too).
+timing is armed.  The headline and the other eager figures of that gradient keep it armed: one launch and one pass over
+memory per step, as any real gradient needs.  The k-in-one-launch rounds are reported apart, under "k_steps_in_one_launch"
+(and the graph variants of the k sweep, whose launches are not timed, take their k steps that way too).
 Prints ONE JSON line.  `value` = worker-param-updates/s = W*d*k / round time for the variant named in
 config.variant under the overlapped two-stream schedule.  The same line carries: the k sweep (both
 variants, each also replayed from a HIP graph, and under the schedule that forms the mean inside the
@@ -72,11 +72,11 @@ def moved_round_bytes(W, d, k, variant, per_step=STEP_BYTES):
     return W * d * (per_step * (k - 1) + 4 * (1 + 1 / W)) + tail_step_bytes(W, d, k, per_step)
 
 
-def time_rounds(ctx, torch, k, rounds, warmup, variant, one_launch=False):
+def time_rounds(ctx, torch, k, rounds, warmup, variant, timed=True):
     """Seconds per round over `rounds` timed rounds and, measured over the same rounds from the
     kernels' own start/stop timestamps on the compute stream, the average duration in seconds of the
     plain step kernel, of the step kernel that carries line 6 and of the first step that also forms the
-    mean (None where there was no launch).  one_launch: the k steps of a round in one launch, not timed."""
+    mean (None where there was no launch).  timed=False: no timestamps, and the quadratic gradient's k steps in one launch."""
     import paper_1906_12043_amd as P
     head = variant.startswith("head_")           # Step I inside the round's first step (one stream)
     if head:
@@ -96,7 +96,7 @@ def time_rounds(ctx, torch, k, rounds, warmup, variant, one_launch=False):
     for _ in range(warmup):
         one_round()
     ctx.sync()
-    want_step_times = not one_launch and not variant.startswith("graph")    # launches in a graph are not timed
+    want_step_times = timed and not variant.startswith("graph")             # launches in a graph are not timed
     ctx.step_timing(rounds * k if want_step_times else 0)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -457,7 +457,7 @@ def bench_quadratic(workload, k, variant, steps, warmup, full):
         for name in ("separate", "fused_tail", "head_fused_tail"):
             sweep = {}
             for kk in cfg["k"]:
-                pr = time_rounds(ctx, torch, kk, sweep_rounds, 2, name, True)[0]
+                pr = time_rounds(ctx, torch, kk, sweep_rounds, 2, name, timed=False)[0]
                 sweep["k=%d" % kk] = {"ms_per_round": pr * 1e3, "updates_per_s": W * d * kk / pr,
                                       "moved_GBps": moved_round_bytes(W, d, 1, name, per_step) / pr / 1e9}
             variants[name] = sweep
@@ -531,7 +531,7 @@ def bench_mlp(k, variant, steps, warmup, full):
     }
     if full:
         other = "separate" if fused else "fused_tail"
-        out[other + "_ms_per_round"] = time_rounds(ctx, torch, k, steps, warmup, other)[0] * 1e3
+        out[other + "_ms_per_round"] = time_rounds(ctx, torch, k, steps, warmup, other, timed=False)[0] * 1e3
         out["graph_ms_per_round"] = time_rounds(ctx, torch, k, steps, warmup, "graph_" + variant)[0] * 1e3
     ctx.close()
     del xA, xB, v, mean

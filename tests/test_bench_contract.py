@@ -3,6 +3,8 @@ import os
 import subprocess
 import sys
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -50,3 +52,23 @@ def test_traffic_constants_are_the_counter_figures_of_the_committed_profile():
     W, d = 16, 11_200_000
     assert abs(plain[1] * 1e9 - 24 * W * d) < 1e5
     assert abs(tail[1] * 1e9 - bench.tail_step_bytes(W, d, 2)) < 1e5 and abs(tail_k1[1] * 1e9 - bench.tail_step_bytes(W, d, 1)) < 1e5
+
+
+@pytest.mark.gpu
+def test_only_the_perceptrons_own_round_is_timed_step_by_step(monkeypatch):
+    """The figures beside it are of rounds without timestamps, as in every earlier line."""
+    sys.path.insert(0, ROOT)
+    import bench
+    calls, real = [], bench.time_rounds
+
+    def spy(ctx, torch, k, rounds, warmup, variant, **kw):
+        armed, step_timing = [], ctx.step_timing
+        ctx.step_timing = lambda n: (armed.append(n), step_timing(n))[1]
+        out = real(ctx, torch, k, rounds, warmup, variant, **kw)
+        del ctx.step_timing
+        calls.append((variant, any(armed)))
+        return out
+    monkeypatch.setattr(bench, "time_rounds", spy)
+    line = bench.bench_mlp(2, "fused_tail", 3, 1, True)
+    assert calls == [("fused_tail", True), ("separate", False), ("graph_fused_tail", False)]
+    assert line["separate_ms_per_round"] > 0 and line["graph_ms_per_round"] > 0
