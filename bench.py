@@ -93,10 +93,11 @@ def time_rounds(ctx, torch, k, rounds, warmup, variant, timed=True):
             ctx.average_end_apply()
         else:
             ctx.local_steps_end_apply(k)
+    want_step_times = timed and not variant.startswith("graph")             # launches in a graph are not timed
+    ctx.step_timing(warmup * k if want_step_times else 0)                   # warm up with the launches that are timed
     for _ in range(warmup):
         one_round()
     ctx.sync()
-    want_step_times = timed and not variant.startswith("graph")             # launches in a graph are not timed
     ctx.step_timing(rounds * k if want_step_times else 0)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -126,8 +127,10 @@ def timelines(ctx, torch, P, k, rounds):
       cocod_fused_tail  the same with line 6 inside the last step
     Blocking average = cocod_average_apply_fused while idle: every worker lands on the mean of the current models."""
     def timed(body, steps_per_iter):
+        ctx.step_timing(2 * steps_per_iter)
         for _ in range(2):
             body()
+        ctx.sync()
         ctx.step_timing(rounds * steps_per_iter)
         torch.cuda.synchronize()
         t0 = time.perf_counter()

@@ -54,6 +54,37 @@ def test_traffic_constants_are_the_counter_figures_of_the_committed_profile():
     assert abs(tail[1] * 1e9 - bench.tail_step_bytes(W, d, 2)) < 1e5 and abs(tail_k1[1] * 1e9 - bench.tail_step_bytes(W, d, 1)) < 1e5
 
 
+@pytest.mark.parametrize("variant", ["fused_tail", "separate", "head_fused_tail"])
+@pytest.mark.parametrize("timed", [True, False])
+def test_warm_up_rounds_take_the_launches_that_are_timed(variant, timed):
+    """Armed step timing makes every step a launch of its own: the warm-up rounds are armed, or not, as the timed ones."""
+    sys.path.insert(0, ROOT)
+    import bench
+
+    class Fake:                                       # stands for a context and for torch.cuda
+        def __init__(self):
+            self.left, self.rounds = 0, []
+
+        def step_timing(self, n):
+            self.left = n
+
+        def steps(self, k):
+            self.rounds.append(min(self.left, k))
+            self.left -= min(self.left, k)
+        local_steps = local_steps_end_apply = steps
+
+        def step_timing_read(self):
+            return [(1.0, 1)] * 3
+
+        def nothing(self, *args):
+            pass
+        set_schedule = average_begin = average_end_apply = sync = synchronize = nothing
+    fake = Fake()
+    fake.cuda = fake
+    bench.time_rounds(fake, fake, 3, 5, 2, variant, timed=timed)
+    assert fake.rounds == [3 if timed else 0] * 7 and fake.left == 0
+
+
 @pytest.mark.gpu
 def test_only_the_perceptrons_own_round_is_timed_step_by_step(monkeypatch):
     """The figures beside it are of rounds without timestamps, as in every earlier line."""
