@@ -62,7 +62,10 @@ typedef enum cocod_grad_kind {
 
 /* How Step I is scheduled relative to Step II (the arithmetic is the same in all of them). */
 typedef enum cocod_schedule {
-    COCOD_SCHED_OVERLAP = 0,   /* mean on avg_stream, concurrent with the local steps (the paper's scheme) */
+    COCOD_SCHED_OVERLAP = 0,   /* mean on avg_stream, concurrent with the local steps (the paper's scheme); with line
+                                  6 inside them, concurrent with all launches but the last, which waits for it: where
+                                  that is the only one (see cocod_local_steps_end_apply) nothing runs beside the
+                                  mean, and COCOD_SCHED_HEAD or a replayed round spares the hand-overs between streams */
     COCOD_SCHED_SERIAL = 1,    /* mean on compute_stream after the local steps, then line 6 (sequential, as
                                   the paper's Local-SGD timeline) */
     COCOD_SCHED_FUSED = 2,     /* mean and line 6 in one kernel after the local steps */
@@ -177,7 +180,8 @@ int cocod_destroy(cocod_ctx *ctx);
  * The built-in quadratic gradient of a coordinate depends on that coordinate alone, so its k steps are
  * taken up to 16 to a launch, in registers, with the bits of one launch per step (also inside
  * cocod_local_steps_end_apply and cocod_graph_round); while step timing is armed every step of an
- * eager call is a launch of its own (replayed rounds are never timed).  The other gradients need the whole model between two steps.
+ * eager call is a launch of its own (replayed rounds are never timed).  The other gradients need the
+ * whole model between two steps.
  */
 int cocod_local_steps(cocod_ctx *ctx, int k);
 
@@ -216,9 +220,11 @@ int cocod_average_apply_fused(cocod_ctx *ctx);
  * has just computed, before storing it (x = x^_t + ((x - gamma v) - x_t^i) in the step kernel's
  * registers), and closes the round.  Same arithmetic, in the same order, as
  * cocod_local_steps(k) followed by cocod_average_end_apply, but the separate pass of line 6 over
- * the models (read x, read x_t, write x) disappears: 8 bytes per parameter less per round (24 at
- * k = 1, where the step reads the stored models anyway).  The join moves in front of the last
- * launch, so the mean overlaps the launches before it only.  k = 0 is cocod_average_end_apply.
+ * the models (read x, read x_t, write x) disappears: 8 bytes per parameter less per round, 12 where
+ * the round's steps are one launch, which reads the stored models anyway (k = 1, and untimed up to
+ * k = 16 with the built-in quadratic gradient).  The join moves in front of the last launch, so the
+ * mean overlaps the launches before it only: none of them where the only launch is the last.
+ * k = 0 is cocod_average_end_apply.
  * AVERAGING -> IDLE; COCOD_ERR_STATE if no round is open.
  */
 int cocod_local_steps_end_apply(cocod_ctx *ctx, int k);
@@ -288,10 +294,14 @@ int cocod_get_plan(const cocod_ctx *ctx, uint64_t *padded_d, uint32_t *n_chunks,
  * of its own that carries the runtime's own start/stop timestamps (events on compute_stream, owned by the
  * context); n = 0 switches it off.  cocod_step_timing_read waits for compute_stream, returns the
  * summed kernel durations and the number of launches measured since the last read, and rearms.
+ * It times steps, not the launches that an untimed call makes of them: with the built-in quadratic
+ * gradient, whose steps share launches, an armed round moves more bytes than an unarmed one and
+ * takes longer.  The duration of an unarmed call is the caller's to take, with events of its own on
+ * compute_stream.
  * A local step of the MLP kind is several kernels: its duration runs from the start of the first
  * to the end of the last.
  * Index 0 of both arrays: plain local steps; index 1: steps that carry line 6
- * (cocod_local_steps_end_apply's last step, the one-pass k = 1 step included); index 2: first steps
+ * (cocod_local_steps_end_apply's last step, one that also forms the mean included); index 2: first steps
  * of a round that also form the mean (COCOD_SCHED_HEAD).
  */
 int cocod_step_timing(cocod_ctx *ctx, int max_launches);

@@ -158,13 +158,20 @@ constexpr int kMaxStepsPerLaunch = 16;
 // per step / all in the mean's launch / mean apart, us: W = 64, d = 1500, k = 8 37 / 46 / 9.1, k = 16 62 / 85 / 11; W = 131,
 // d = 6000, k = 8 46 / 48 / 17; W = 48, d = 14 000, k = 8 42 / 36 / 11; on the other side of the line W = 24, d = 6000, k = 2 11 / 8.1 / 7.3,
 // W = 17, d = 60 000, k = 4 25 / 11.6 / 9.9, W = 131, d = 30 000, k = 2 37 / 25 / 27, W = 16, d = 14 000, k = 8 28 / 8.5 / 7.9.
+// With enough blocks the launch is taken whatever W is, for it is always faster than one launch per step; against the mean apart
+// and one launch for the steps, round of k = 2 / 4 / 8 / 16, us: W = 4, d = 32 M 511 / 533 / 748 / 1249 against 591 / 610 / 845 / 1357,
+// W = 16, d = 8 M 548 / 580 / 786 / 1264 against 585 / 605 / 833 / 1351, W = 17, d = 7.5 M 623 / 724 / 941 / 1489 against 584 / 604 / 832 /
+// 1355, W = 32, d = 4 M 572 / 597 / 796 / 1289 against 566 / 577 / 820 / 1339, W = 64, d = 2 M 582 / 593 / 841 / 1445 against 564 / 576 / 817 /
+// 1340, W = 131, d = 977 k 573 / 589 / 824 / 1378 against 557 / 570 / 812 / 1332; rows off the lines, k = 2, W = 4 609 against 616, W = 16 629
+// against 609, W = 64 636 against 572.
 // With line 6 apart, W = 64, d = 1500, k = 8 38 / 48 / 18; W = 131, d = 14 000, k = 2 28 / 23 / 33, k = 4, already apart, 40 / 33 / 35.
 constexpr uint64_t kIdleElementSteps = 80000;     // per compute unit
 // Models of all workers up to this size are averaged on the one branch of a replayed round: reading them takes a few
 // microseconds, fork and join between two branches more, and above all when several contexts replay rounds at a time.
 // Perceptron rounds of k = 2, two branches / one, three contexts in turn (one context alone): W = 4, 768-192-10 (2.4 MB of
-// models) 50 / 25 us (78 / 62), 768-768-10 (9.5 MB) 70 / 69 (109 / 98), W = 8, 2048-512-10 (34 MB) 175 / 179 (213 / 205), W = 16,
-// 3072-1024-10 (202 MB) 575 / 581 (609 / 607).  Rounds of the quadratic gradient, whose steps are one launch behind the mean,
+// models) 54 / 42 us (78 / 61; three contexts in turn take anything from 24 to 42 on one branch, process by process), 768-768-10
+// (9.5 MB) 70 / 69 (109 / 98), W = 8, 2048-512-10 (34 MB) 175 / 179 (213 / 205), W = 16, 3072-1024-10 (202 MB) 575 / 581
+// (609 / 607).  Rounds of the quadratic gradient, whose steps are one launch behind the mean,
 // are the same either way.
 constexpr uint64_t kGraphBranchBytes = 16ull << 20;
 // one grid dimension holds fewer than 2^32 threads

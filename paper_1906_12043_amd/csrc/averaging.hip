@@ -69,6 +69,12 @@ __device__ __forceinline__ float4 column_mean(const float *col, uint64_t stride,
 // CACHED: a state that stays in the last-level cache (step_state_is_cached): the step beside or behind reads the same models.
 // Rounds of k = 2 with line 6 in the last step, mean in front of the steps, one context, streaming / ordinary loads: W = 8, d = 250 k
 // 13.1 / 12.7 us, d = 1 M 41.8 / 39.4, W = 16, d = 700 k 49.3 / 48.6; three contexts in turn 11.8 / 11.1, 39.0 / 38.6, 54.3 / 53.3.
+// The caller's fp32 gradient, mean beside the first step, k = 1: W = 8, d = 1 M 55.3 / 52.8, three contexts 37.2 / 37.4; W = 16,
+// d = 400 k 46.2 / 44.2, 36.7 / 36.7; d = 700 k 62.1 / 59.7, 49.0 / 49.9; mean in front of the step W = 8, d = 250 k 10.8 / 10.1, 10.8 / 9.7,
+// W = 16, d = 700 k 43.3 / 41.8, 43.9 / 45.1; k = 2 and k = 8 the same or up to 4 % faster.  So where three contexts together are far
+// beyond the cache a round of one step loses 2 %, and one by itself gains 4.  Perceptron rounds, mean beside the forward product,
+// k = 1 and 2: W = 16, 768-512-10 83.9 / 82.8, 128.2 / 126.5, three contexts 65.8 / 65.0, 110.8 / 109.2; from a graph, k = 2, W = 4,
+// 768-768-10 98.0 / 95.2, 67.9 / 66.2.
 template <bool WEIGHTED, bool CACHED>
 __global__ __launch_bounds__(kAvgThreads) void wmean_kernel(const float *snap, uint64_t stride, uint32_t W,
                                                             uint64_t begin, uint64_t n_quads,

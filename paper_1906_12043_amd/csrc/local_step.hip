@@ -14,9 +14,10 @@
 // comes from the next lane or the wave's own next pass), so block shape is free:
 //   PLAIN / TAIL   single-wave blocks, grid (tiles, workers).  Measured on MI355X at W = 16, d = 11.2 M:
 //             6.6 TB/s against 6.05 TB/s for the same step in 4-wave blocks and 5.8 in 16-wave blocks;
-//             small independent blocks stream best on this chip.  TAIL is the round's last step
-//             with line 6 applied to the fresh model before it is stored, x = mean + (x_new - x_stored).
-//   HEAD      the round's first step also forms Step I's weighted mean of the models it reads.  One
+//             small independent blocks stream best on this chip.  TAIL is the round's last launch
+//             with line 6 applied to the fresh model before it is stored, x = mean + (x_new - x_stored);
+//             TAIL_IN where that is also its first, which reads the stored model as its input.
+//   HEAD      the round's first launch also forms Step I's weighted mean of the models it reads.  One
 //             block = one tile of ALL W workers, one wave per worker row (16 rows at a time): every wave
 //             puts its row's tile into LDS, the block sums the tile's columns over the workers in order
 //             0..W-1 (the one compensated sum of mean_sum.hpp, so the bits equal those of the stand-alone
@@ -24,9 +25,9 @@
 //   ONE_PASS  the launch is the whole round: Step I, the local steps and line 6 in a single sweep (24 + 4/W bytes per
 //             parameter): as HEAD, and line 6 is applied with the tile's mean before anything is stored.
 //
-// Memory path: every model array is streamed exactly once per step, through buffer instructions whose descriptor
+// Memory path: every model array is streamed exactly once per launch, through buffer instructions whose descriptor
 // covers exactly the tile (step_common.hpp).  Where the state is larger than the 256 MB last-level cache the accesses
-// carry the non-temporal hint; a smaller one is found there again by the next step and is accessed without it
+// carry the non-temporal hint; a smaller one is found there again by the next launch and is accessed without it
 // (step_state_is_cached).  The mean is shared by the W workers of a column and is read with an ordinary cached load.
 #include "internal.hpp"
 #include "step_common.hpp"
@@ -120,9 +121,11 @@ __global__ __launch_bounds__(64 * NWMAX, Q == 1 ? 8 : 4) void local_step_kernel(
     const Chunk ck = p.table[chunk_id];
     const uint32_t first = part * TILE_ELEMS;                 // first element of the tile inside its chunk
     if (first >= ck.n) return;                                // block-uniform: the tensor ends before this tile
-    // Step index and worker are wave-uniform; where the compiler is told so, what the generator forms of them alone is scalar.  Not
-    // the row addresses of the modes without a mean: with those in scalar registers a wave's loads leave in one burst, and
-    // the steps that memory bounds are 2 % slower (W = 16, d = 11.2 M, one step 655 -> 667 us).
+    // Step index and worker are wave-uniform; where the compiler is told so, what the generator forms of them alone is scalar (W = 16,
+    // d = 11.2 M, 16 steps in one launch 1726 -> 1695 us, without momentum 1510 -> 1483).  In the mean-forming modes the wave index
+    // is told, and with it the row addresses are scalar too (whole round in one pass, k = 4 844 -> 788, k = 8 1158 -> 1072).  Not
+    // in the others: with those in scalar registers a wave's loads leave in one burst, and the steps that memory
+    // bounds are 2 % slower (one step 655 -> 667 us).
     const uint32_t lane = threadIdx.x & 63u, wave = FORMS_MEAN ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6, nw = blockDim.x >> 6;
     const uint32_t step = __builtin_amdgcn_readfirstlane(p.step_base ? *p.step_base + p.step : p.step);
 

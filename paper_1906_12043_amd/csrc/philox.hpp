@@ -14,9 +14,8 @@ namespace cocod {
 struct Words4 { uint32_t w[4]; };
 
 // a ^ b ^ c in one instruction (which the compiler does not find: it folds pairs first).  The generator and the arithmetic bound
-// steps taken four and more to a launch.  With this, the scalar parts below and the counters of local_step.hip, W = 16, d = 11.2 M,
-// momentum: 4 steps 721 -> 673 us, 8 steps 1133 -> 1005, 16 steps 2014 -> 1703; without momentum 4 steps 615 -> 538; a round in one
-// pass of k = 4 903 -> 800.
+// steps taken four and more to a launch: W = 16, d = 11.2 M, momentum, 4 / 8 / 16 steps 702 / 1090 / 1866 -> 670 / 992 / 1695 us, without
+// momentum 574 / 928 / 1659 -> 533 / 842 / 1483.
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
 
 __device__ __forceinline__ Words4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
@@ -28,7 +27,8 @@ __device__ __forceinline__ Words4 philox4x32_10(uint32_t c0, uint32_t c1, uint32
         const uint64_t pa = static_cast<uint64_t>(0xD2511F53u) * c0;
         const uint64_t pb = static_cast<uint64_t>(0xCD9E8D57u) * c2;
         // Where the counter's last three words are wave-uniform, as in every use, so are n0 of the first round and what is made
-        // of it in the second: written for the scalar unit.
+        // of it in the second: written for the scalar unit (the same launches of 8 / 16 steps 1011 / 1712 -> 992 / 1695 us,
+        // without momentum 871 / 1535 -> 842 / 1483).
         const uint32_t ha = static_cast<uint32_t>(pa >> 32), hb = static_cast<uint32_t>(pb >> 32);
         const uint32_t n0 = r == 0 ? hb ^ c1 ^ k0 : xor3(hb, c1, k0);
         const uint32_t n2 = r == 1 ? (ha ^ k1) ^ c3 : xor3(ha, c3, k1);
@@ -46,7 +46,8 @@ __device__ __forceinline__ Words4 philox4x32_10(uint32_t c0, uint32_t c1, uint32
 
 // top 24 bits -> [0,1) on a 2^-24 grid (exact in fp32)
 __device__ __forceinline__ float u_half_open(uint32_t r) { return static_cast<float>(r >> 8) * 0x1p-24f; }
-// top 24 bits plus one -> (0,1], exact as well
+// top 24 bits plus one -> (0,1], exact as well (one instruction less than adding first: the same launches of 16 steps 1703 -> 1695 us,
+// without momentum 1521 -> 1483)
 __device__ __forceinline__ float u_open_zero(uint32_t r) { return __builtin_fmaf(static_cast<float>(r >> 8), 0x1p-24f, 0x1p-24f); }
 
 struct Normals4 { float z[4]; };
